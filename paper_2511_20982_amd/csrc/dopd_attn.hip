@@ -272,12 +272,12 @@ namespace {
 
 // Fills the work-order fields of `a` for chunk lengths cu_host (and, on the
 // paged path, cached prefixes prefix_host) and returns the prefill's block
-// count: items are (q tile, request, head), with at most 64 requests in the
-// XCD-aware order (requests ranked by the keys their last row sees, dealt to
-// the XCDs in contiguous slices), else heaviest q tile first.
+// count: items are (q tile, request, head), with at most kPfMaxOrdered
+// requests in the XCD-aware order, else heaviest q tile first.
 template <bool PAGED>
-dopd_status plan_prefill_bf16(dopd::PrefillArgs& a, const int32_t* cu_host,
-                              const int32_t* prefix_host, int32_t nreq, int64_t* blocks_out) {
+dopd_status plan_prefill_bf16(dopd::PrefillArgs& a, int d, const int32_t* cu_host,
+                              const int32_t* prefix_host, int32_t nreq, int elem_bytes,
+                              bool split_requests, int64_t* blocks_out) {
   int max_len = 0;
   int64_t tiles = 0;
   for (int32_t r = 0; r < nreq; ++r) {
@@ -287,40 +287,19 @@ dopd_status plan_prefill_bf16(dopd::PrefillArgs& a, const int32_t* cu_host,
   }
   a.nreq = nreq;
   a.max_tiles = (max_len + dopd::kPfBM - 1) / dopd::kPfBM;
-  a.hslots = (a.hq + dopd::kPfHeadsPerWG - 1) / dopd::kPfHeadsPerWG;
-  const int64_t items = tiles * a.hslots;
+  const int64_t items = tiles * a.hq;
   if (items > INT32_MAX / 2) return DOPD_ERR_INVALID_SHAPE;
   int64_t blocks = items;
   a.xcd_order = 0;
-  a.n_items = (int)items;
-  a.tiles_total = (int)tiles;
-  a.per_xcd = 0;
   a.xcds = 1;
-  std::memset(a.ord, 0, sizeof(a.ord));
   if (nreq <= dopd::kPfMaxOrdered) {
-    // requests by decreasing key count (stable), dealt to XCDs in contiguous slices
-    auto keys = [&](int r) {
-      return (int64_t)(cu_host[r + 1] - cu_host[r]) + (PAGED ? prefix_host[r] : 0);
-    };
-    int order[dopd::kPfMaxOrdered];
-    for (int32_t r = 0; r < nreq; ++r) order[r] = r;
-    std::stable_sort(order, order + nreq, [&](int x, int y) { return keys(x) > keys(y); });
-    for (int32_t r = 0; r < nreq; ++r) a.ord[r] = order[r];
-    // slots per block, as the kernel groups them
-    const int g = a.hq / a.hkv;
-    const int gs = (g % dopd::kPfHeadsPerWG == 0) ? g / dopd::kPfHeadsPerWG : 1;
-    int sum = 0;
-    for (int32_t i = 0; i < nreq; ++i) {
-      const int r = order[i];
-      sum += gs * ((cu_host[r + 1] - cu_host[r] + dopd::kPfBM - 1) / dopd::kPfBM);
-      a.incl[i] = sum;
-    }
-    for (int32_t r = 0; r <= nreq; ++r) a.cu_h[r] = cu_host[r];
-    for (int32_t r = 0; r < nreq; ++r) a.prefix_h[r] = PAGED ? prefix_host[r] : 0;
     a.xcd_order = 1;
     a.xcds = machine_shape().xcds;
-    a.per_xcd = dopd::pf_per_xcd((int)items, a.xcds);
-    blocks = (int64_t)a.per_xcd * a.xcds;
+    dopd::pf_build_order(a.order, cu_host, PAGED ? prefix_host : nullptr, nreq, a.hq, a.hkv,
+                         (int64_t)2 * d * elem_bytes, a.xcds, split_requests);
+    for (int32_t r = 0; r <= nreq; ++r) a.cu_h[r] = cu_host[r];
+    for (int32_t r = 0; r < nreq; ++r) a.prefix_h[r] = PAGED ? prefix_host[r] : 0;
+    blocks = (int64_t)dopd::pf_order_places(a.order) * a.xcds;
   }
   blocks *= a.nsplit;  // (nsplit > 1 only on the paged path)
   if (blocks > INT32_MAX / 2) return DOPD_ERR_INVALID_SHAPE;
@@ -336,7 +315,8 @@ template <bool PAGED, bool KV8 = false>
 dopd_status launch_prefill_bf16(dopd::PrefillArgs a, int d, const int32_t* cu_host,
                                 const int32_t* prefix_host, int32_t nreq, hipStream_t strm) {
   int64_t blocks = 0;
-  const dopd_status pst = plan_prefill_bf16<PAGED>(a, cu_host, prefix_host, nreq, &blocks);
+  const dopd_status pst =
+      plan_prefill_bf16<PAGED>(a, d, cu_host, prefix_host, nreq, KV8 ? 1 : 2, true, &blocks);
   if (pst != DOPD_OK) return pst;
   if (blocks == 0) return DOPD_OK;
   if (d == 64)
@@ -889,7 +869,7 @@ static dopd_status pd_step_impl(const dopd_attn_shape* s, const void* q_dec,
     p.pf = prefill_args(&sb, q, out_pre, lse_pre, cu);
     p.pf.k = (const uint16_t*)k;
     p.pf.v = (const uint16_t*)v;
-    st = plan_prefill_bf16<false>(p.pf, cu_host, nullptr, num_pre, &pf_blocks);
+    st = plan_prefill_bf16<false>(p.pf, d, cu_host, nullptr, num_pre, 2, false, &pf_blocks);
     if (st != DOPD_OK) return st;
     p.wp = write_pack_args(k, v, k_pool, v_pool, pre_page_table, pt_stride, cu, num_pre, hkv,
                            handoff_offsets, handoff_out);

@@ -23,10 +23,10 @@
 // row sum beyond 2^20 (a tile far above it) takes the tile max, rescales O
 // and l and forms p again.  Diagonal and ragged tiles take the max and mask
 // with a select.
-// Work order: with at most 64 requests, each XCD takes a contiguous slice of
-// (KV head, request longest first, q tile descending, query head) so the q tiles
-// that read the same K/V run together under one L2; otherwise heaviest q
-// tiles first.
+// Work order: with at most 64 requests, every XCD takes its share (whole KV
+// heads where they divide) of each request in turn, longest first, so that the
+// XCDs finish together and the q tiles that read the same K/V run together
+// under one L2; otherwise heaviest q tiles first.
 #pragma once
 #include <type_traits>
 
@@ -43,20 +43,13 @@ struct PrefillArgs {
   float* lse;          // [T][Hq] or null
   const int32_t* cu;   // [nreq + 1]
   int nreq, hq, hkv, max_tiles;
-  int hslots;          // head slots = ceil(hq / kPfHeadsPerWG)
   float scale_log2;
-  // XCD-aware order (used when nreq <= kPfMaxOrdered): the work list is
-  // (slot block, request by decreasing length, q tile descending, slot of the
-  // block); XCD x = workgroup % xcds takes the contiguous slice
-  // [x * per_xcd, (x+1) * per_xcd), so the q tiles that share a request's K/V
-  // run together on one XCD and share its L2.
-  int xcd_order, n_items, per_xcd, tiles_total, xcds;
-  int ord[64];         // requests by decreasing length
-  // With the XCD order: incl[i] = sum over positions p <= i of the order of
-  // (slots per block) x (q tiles of request ord[p]); copies of cu and prefix.
-  int incl[64];
-  int cu_h[65];
-  int prefix_h[64];
+  // XCD-aware order (used when nreq <= kPfMaxOrdered) and, with it, copies of
+  // cu and prefix; else heaviest q tiles first, found from cu.
+  int xcd_order, xcds;
+  PfOrder order;
+  int cu_h[kPfMaxOrdered + 1];
+  int prefix_h[kPfMaxOrdered];
   // Chunk prefill over the paged cache (the paged instantiation only): the
   // chunk rows of request r are q[cu[r] .. cu[r+1]), its keys are the cached
   // positions 0 .. prefix[r] + chunk length - 1, read through the page table.
@@ -71,8 +64,9 @@ struct PrefillArgs {
   // scale multiplies the softmax scale, the V scale the output.
   const float* k_scale;
   const float* v_scale;
-  // Key splits of the paged kernel (nsplit > 1): workgroup b computes split
-  // b % nsplit of item b / nsplit, keys of tiles [t_s, t_{s+1}) with
+  // Key splits of the paged kernel (nsplit > 1): the splits of an item are
+  // consecutive places of its XCD (without the XCD order consecutive
+  // workgroups); split s computes the keys of tiles [t_s, t_{s+1}) with
   // t_s = min(s * ntiles / nsplit, nfull) (the last split also takes every
   // tile a row of the item does not see in full), and writes the
   // un-normalised (o, m, l) of its rows to split slot s of part_o / part_ml,
@@ -84,11 +78,8 @@ struct PrefillArgs {
   int part_rows;              // T of the call
 };
 
-constexpr int kPfMaxOrdered = 64;
-
 constexpr int kPfBM = kPfTileRows;  // query rows per workgroup (32 per wave)
-constexpr int kPfHeadsPerWG = 1;    // heads per workgroup
-constexpr int kPfThreads = kPfHeadsPerWG * (kPfBM / 32) * 64;
+constexpr int kPfThreads = (kPfBM / 32) * 64;
 constexpr int kPfBN = kPfTileKeys;  // keys per tile
 
 // Number of BM-row q tiles of request rr.
@@ -96,10 +87,10 @@ __device__ __forceinline__ int pf_tiles(const int32_t* cu, int rr) {
   return (cu[rr + 1] - cu[rr] + kPfBM - 1) / kPfBM;
 }
 
-// Maps a workgroup index to (q tile, request, head slot), q tiles in
-// decreasing index order (tile i of a request attends to ~ (i+1) key tiles).
+// Maps a workgroup index to (q tile, request, head), q tiles in decreasing
+// index order (tile i of a request attends to ~ (i+1) key tiles).
 __device__ __forceinline__ bool pf_find_item_lpt(const PrefillArgs& a, int b, int& tile,
-                                                 int& req, int& slot) {
+                                                 int& req, int& h) {
   const int l = lane_id();
   const bool small = a.nreq <= 64;
   const int nt_l = (small && l < a.nreq) ? pf_tiles(a.cu, l) : 0;
@@ -108,49 +99,50 @@ __device__ __forceinline__ bool pf_find_item_lpt(const PrefillArgs& a, int b, in
       const int nt = small ? nt_l : ((r0 + l < a.nreq) ? pf_tiles(a.cu, r0 + l) : 0);
       const unsigned long long hit = __ballot(nt > i);
       const int cnt = __popcll(hit);
-      if (b < cnt * a.hslots) {
-        const int kth = b / a.hslots;
+      if (b < cnt * a.hq) {
+        const int kth = b / a.hq;
         // position of the kth set bit
         const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(hit >> 32),
                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)hit, 0u));
         const unsigned long long sel = __ballot(nt > i && before == kth);
         req = r0 + __ffsll((long long)sel) - 1;
-        slot = b % a.hslots;
+        h = b % a.hq;
         tile = i;
         return true;
       }
-      b -= cnt * a.hslots;
+      b -= cnt * a.hq;
     }
   }
   return false;
 }
 
-// XCD-aware mapping (see PrefillArgs).  Slots are grouped in blocks of the
-// slots that read one KV head (GQA) when the group size allows it.
-__device__ __forceinline__ bool pf_find_item_xcd(const PrefillArgs& a, int b, int& tile,
-                                                 int& req, int& slot) {
-  if (!pf_xcd_valid(b, a.xcds, a.per_xcd, a.n_items)) return false;
-  const int n = pf_xcd_item(b, a.xcds, a.per_xcd);
-  const int g = a.hq / a.hkv;
-  const int gs = (g % kPfHeadsPerWG == 0) ? g / kPfHeadsPerWG : 1;  // slots per block
-  const int per_blk = gs * a.tiles_total;
-  const int blk = n / per_blk;
-  const int rem = n - blk * per_blk;
+// XCD-aware mapping: place s of XCD x (see PfOrder).
+__device__ __forceinline__ bool pf_find_item_xcd(const PrefillArgs& a, int x, int s, int& tile,
+                                                 int& req, int& h) {
   const int l = lane_id();
-  const unsigned long long hit = __ballot(l < a.nreq && rem < a.incl[l]);
+  const unsigned long long hit = __ballot(l < a.order.n && s < a.order.incl[l]);
+  if (hit == 0) return false;
   const int k = __builtin_amdgcn_readfirstlane(__ffsll((long long)hit) - 1);
-  const int before = k > 0 ? a.incl[k - 1] : 0;
-  const int local = rem - before;
-  req = __builtin_amdgcn_readfirstlane(a.ord[k]);
-  tile = (a.incl[k] - before) / gs - 1 - local / gs;
-  slot = blk * gs + local % gs;
+  const int local = s - (k > 0 ? a.order.incl[k - 1] : 0);
+  const int g = a.hq / a.hkv, nt = a.order.nt[k];
+  int head = 0, idx = 0;
+  if (!pf_entry_item(a.order.rot[k], x, local, nt, g, a.hkv, a.xcds, head, idx)) return false;
+  req = a.order.req[k];
+  tile = a.order.tile0[k] + nt - 1 - idx / g;
+  h = head * g + idx % g;
   return true;
 }
 
-__device__ __forceinline__ bool pf_find_item(const PrefillArgs& a, int b, int& tile, int& req,
-                                             int& slot) {
-  return a.xcd_order ? pf_find_item_xcd(a, b, tile, req, slot)
-                     : pf_find_item_lpt(a, b, tile, req, slot);
+// Item and key split of workgroup b of the prefill.
+__device__ __forceinline__ bool pf_find_item(const PrefillArgs& a, int b, int nsplit, int& tile,
+                                             int& req, int& h, int& split) {
+  if (a.xcd_order) {
+    const int s = b / a.xcds;
+    split = s % nsplit;
+    return pf_find_item_xcd(a, b % a.xcds, s / nsplit, tile, req, h);
+  }
+  split = b % nsplit;
+  return pf_find_item_lpt(a, b / nsplit, tile, req, h);
 }
 
 // LDS of one prefill workgroup: K and V tiles, double-buffered, BN x D bf16
@@ -186,9 +178,8 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs& a, int bid,
   auto kbuf = [&](int b) { return b ? sK1 : sK0; };
   auto vbuf = [&](int b) { return b ? sV1 : sV0; };
 
-  const int split = PAGED ? bid % a.nsplit : 0;
-  int tile, r, h;
-  if (!pf_find_item(a, PAGED ? bid / a.nsplit : bid, tile, r, h))
+  int tile, r, h, split;
+  if (!pf_find_item(a, bid, PAGED ? a.nsplit : 1, tile, r, h, split))
     return;  // uniform across the workgroup
   // The item is wave-uniform; say so, so that what derives from it stays scalar.
   tile = __builtin_amdgcn_readfirstlane(tile);

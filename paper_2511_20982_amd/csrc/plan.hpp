@@ -137,16 +137,73 @@ inline int decode_merge_list(const int32_t* ctx, int32_t n, int hkv, int64_t tot
 }
 
 // ---- prefill work order ----------------------------------------------------
-// With the XCD-aware order the work list of n_items items is dealt to the
-// XCDs in contiguous slices of per_xcd items; the hardware dispatcher sends
-// workgroup b to XCD b % xcds, so workgroup b takes item
-// (b % xcds) * per_xcd + b / xcds (none when past the list).
+// n_items items dealt to the XCDs in contiguous slices of per_xcd items; the
+// hardware dispatcher sends workgroup b to XCD b % xcds, so workgroup b takes
+// item (b % xcds) * per_xcd + b / xcds (none when past the list).
 constexpr int pf_per_xcd(int n_items, int xcds) { return (n_items + xcds - 1) / xcds; }
 constexpr int pf_xcd_item(int b, int xcds, int per_xcd) {
   return (b % xcds) * per_xcd + b / xcds;
 }
 constexpr bool pf_xcd_valid(int b, int xcds, int per_xcd, int n_items) {
   return b / xcds < per_xcd && pf_xcd_item(b, xcds, per_xcd) < n_items;
+}
+
+// The XCD-aware order (at most kPfMaxOrdered requests): a list of entries,
+// each a run of q tiles of one request, heaviest entry first; every entry's
+// items (KV head, q tile descending, query head of the group) are dealt over
+// all XCDs, so each XCD works through the same entries in the same order and
+// the XCDs finish together whatever the lengths.  (Against one contiguous
+// slice of a (KV head, request, q tile) list per XCD, where a slice restarted
+// with the long requests at every head and, with fewer heads than XCDs, one
+// XCD held the long requests and the next the short ones: 16 chunks of 512
+// over mixed prefixes, 32/32 heads, 424 -> 369 us; 8 short prompts, 28/4
+// heads, 39 -> 34 us; 16 long prompts, 32/32 heads, unchanged at 1.67 ms.)
+// Workgroup b is place b / xcds
+// of XCD b % xcds; entry k takes the places [incl[k - 1], incl[k]) of every XCD.
+constexpr int kPfMaxOrdered = 64;
+struct PfOrder {
+  int n;                       // entries
+  int req[kPfMaxOrdered];      // request of the entry
+  int tile0[kPfMaxOrdered];    // its first (lowest) q tile
+  int nt[kPfMaxOrdered];       // its q tiles
+  int incl[kPfMaxOrdered];     // places per XCD up to and with this entry
+  int rot[kPfMaxOrdered];      // XCD (of those that share a head) its first item goes to
+};
+
+// Places an entry of nt q tiles takes on each XCD.  XCDs in a whole multiple
+// of the KV heads: xcds / hkv XCDs share a head's items alternately; otherwise
+// contiguous slices of the entry's items (whole heads when hkv is a multiple
+// of xcds), so that the items that read one head's K/V share an L2.
+constexpr int pf_entry_places(int nt, int g, int hkv, int xcds) {
+  return xcds % hkv == 0 ? pf_per_xcd(nt * g, xcds / hkv) : pf_per_xcd(nt * g * hkv, xcds);
+}
+
+// Item at place `local` of an entry of nt q tiles on XCD x: KV head and index
+// in the head's (q tile descending, query head) list, or false when there is
+// none.  rot moves the XCD that takes the first item, so that entries whose
+// items do not divide evenly give the odd ones to XCDs in turn.
+constexpr bool pf_entry_item(int rot, int x, int local, int nt, int g, int hkv, int xcds, int& head,
+                             int& idx) {
+  if (xcds % hkv == 0) {
+    const int share = xcds / hkv;
+    head = x / share;
+    idx = local * share + (x + share - rot) % share;
+    return idx < nt * g;
+  }
+  const int per = pf_entry_places(nt, g, hkv, xcds), b = local * xcds + (x + xcds - rot) % xcds;
+  if (!pf_xcd_valid(b, xcds, per, nt * g * hkv)) return false;
+  const int i = pf_xcd_item(b, xcds, per);
+  head = i / (nt * g);
+  idx = i % (nt * g);
+  return true;
+}
+
+// The rot of the entry after one of nt q tiles with `rot`.
+constexpr int pf_entry_next_rot(int rot, int nt, int g, int hkv, int xcds) {
+  if (xcds % hkv == 0) return (rot + nt * g) % (xcds / hkv);
+  if (hkv % xcds == 0) return 0;
+  const int per = pf_entry_places(nt, g, hkv, xcds);
+  return (rot + (nt * g * hkv + per - 1) / per) % xcds;
 }
 
 // Key splits of the paged prefill: the requested count (at most kPfMaxSplits),
@@ -159,6 +216,66 @@ constexpr int kPfMaxSplits = 16;
 constexpr int kPfAutoSplits = 8;
 constexpr int kPfTileRows = 128;  // query rows per work item
 constexpr int kPfTileKeys = 64;   // keys per tile
+
+// Builds the order for chunk lengths cu_host and cached prefixes prefix_host
+// (null: none); nreq <= kPfMaxOrdered.  An entry is a whole request, longest
+// keys first: the q tiles that read one head's K/V then run together under one
+// L2.  When the K/V bytes one XCD reads fit its L2 and the call has at most
+// kPfMaxOrdered (request, q tile) pairs, every pair is an entry of its own,
+// heaviest first (the list a longest-first dispatch wants), if split_requests:
+// the fused step does not (its decode slices fill the slots that light items
+// free early; mixed step 224 us with whole requests, 228 us split).
+constexpr int64_t kPfL2Bytes = 4 << 20;
+
+inline void pf_build_order(PfOrder& o, const int32_t* cu_host, const int32_t* prefix_host,
+                           int32_t nreq, int hq, int hkv, int64_t kv_token_bytes, int xcds,
+                           bool split_requests = true) {
+  const int g = hq / hkv;
+  auto len = [&](int r) { return cu_host[r + 1] - cu_host[r]; };
+  auto prefix = [&](int r) { return prefix_host ? prefix_host[r] : 0; };
+  auto tiles = [&](int r) { return (len(r) + kPfTileRows - 1) / kPfTileRows; };
+  int64_t pairs = 0, keys = 0;
+  for (int32_t r = 0; r < nreq; ++r) {
+    pairs += tiles(r);
+    if (len(r) > 0) keys += (int64_t)len(r) + prefix(r);
+  }
+  const int heads_per_xcd = (hkv + xcds - 1) / xcds;
+  const bool split = split_requests && pairs <= kPfMaxOrdered &&
+                     keys * heads_per_xcd * kv_token_bytes <= kPfL2Bytes;
+  int64_t weight[kPfMaxOrdered];  // keys the entry's last row sees
+  o.n = 0;
+  auto add = [&](int r, int t0, int nt, int64_t w) {
+    int i = o.n++;
+    for (; i > 0 && weight[i - 1] < w; --i) {  // stable insertion, heaviest first
+      weight[i] = weight[i - 1];
+      o.req[i] = o.req[i - 1];
+      o.tile0[i] = o.tile0[i - 1];
+      o.nt[i] = o.nt[i - 1];
+    }
+    weight[i] = w;
+    o.req[i] = r;
+    o.tile0[i] = t0;
+    o.nt[i] = nt;
+  };
+  for (int32_t r = 0; r < nreq; ++r) {
+    if (tiles(r) == 0) continue;
+    if (!split) {
+      add(r, 0, tiles(r), (int64_t)prefix(r) + len(r));
+    } else {
+      for (int t = 0; t < tiles(r); ++t)
+        add(r, t, 1, (int64_t)prefix(r) + std::min(len(r), (t + 1) * kPfTileRows));
+    }
+  }
+  int sum = 0, rot = 0;
+  for (int k = 0; k < o.n; ++k) {
+    o.incl[k] = sum += pf_entry_places(o.nt[k], g, hkv, xcds);
+    o.rot[k] = rot;
+    rot = pf_entry_next_rot(rot, o.nt[k], g, hkv, xcds);
+  }
+}
+
+// Places per XCD of the whole order.
+inline int pf_order_places(const PfOrder& o) { return o.n > 0 ? o.incl[o.n - 1] : 0; }
 
 inline int prefill_paged_splits(int hq, bool splittable, const int32_t* cu_host,
                                 const int32_t* prefix_host, int32_t nreq, int32_t num_splits,

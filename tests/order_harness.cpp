@@ -1,0 +1,92 @@
+// CPU check of the prefill's XCD-aware order (paper_2511_20982_amd/csrc/plan.hpp)
+// at a given XCD count: every (request, q tile, head) item is taken by exactly
+// one place, every index stays in range, heads stay on the XCDs the rule gives
+// them, and the XCDs get equal shares.
+// Usage: order_harness <xcds>; prints "ok <cases>" or the first failure.
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <random>
+#include <tuple>
+#include <vector>
+
+#include "../paper_2511_20982_amd/csrc/plan.hpp"
+
+using namespace dopd;
+
+static int fail(const char* what, long a, long b) {
+  std::printf("FAIL %s (%ld, %ld)\n", what, a, b);
+  return 1;
+}
+
+static int check(const std::vector<int32_t>& lens, const std::vector<int32_t>& prefix, int hq, int hkv,
+                 int64_t kv_bytes, int xcds) {
+  const int n = (int)lens.size(), g = hq / hkv;
+  std::vector<int32_t> cu(n + 1, 0);
+  for (int r = 0; r < n; ++r) cu[r + 1] = cu[r] + lens[r];
+  PfOrder o;
+  pf_build_order(o, cu.data(), prefix.empty() ? nullptr : prefix.data(), n, hq, hkv, kv_bytes, xcds);
+  if (o.n < 0 || o.n > kPfMaxOrdered) return fail("entries", o.n, n);
+  std::map<std::tuple<int, int, int>, int> seen;
+  std::vector<long> got(xcds, 0);
+  std::vector<std::map<int, int>> heads(xcds);
+  int64_t last = -1;
+  for (int k = 0; k < o.n; ++k) {
+    const int r = o.req[k];
+    if (r < 0 || r >= n || o.nt[k] < 1 || o.tile0[k] < 0) return fail("entry", k, r);
+    const int64_t w = (prefix.empty() ? 0 : prefix[r]) +
+                      std::min<int64_t>(lens[r], (int64_t)(o.tile0[k] + o.nt[k]) * kPfTileRows);
+    if (last >= 0 && w > last) return fail("entries not heaviest first", k, (long)w);
+    last = w;
+    const int places = o.incl[k] - (k ? o.incl[k - 1] : 0);
+    for (int x = 0; x < xcds; ++x)
+      for (int local = 0; local < places; ++local) {
+        int head = -1, idx = -1;
+        if (!pf_entry_item(o.rot[k], x, local, o.nt[k], g, hkv, xcds, head, idx)) continue;
+        const int tile = o.tile0[k] + o.nt[k] - 1 - idx / g, h = head * g + idx % g;
+        if (head < 0 || head >= hkv || idx < 0 || idx >= o.nt[k] * g) return fail("item", head, idx);
+        if (tile < 0 || tile >= (lens[r] + kPfTileRows - 1) / kPfTileRows) return fail("tile", tile, lens[r]);
+        ++seen[{r, tile, h}];
+        ++got[x];
+        heads[x][head] = 1;
+      }
+  }
+  long items = 0;
+  for (int r = 0; r < n; ++r) items += (long)((lens[r] + kPfTileRows - 1) / kPfTileRows) * hq;
+  if ((long)seen.size() != items) return fail("items not covered", (long)seen.size(), items);
+  for (auto& s : seen)
+    if (s.second != 1) return fail("item taken more than once", std::get<0>(s.first), std::get<1>(s.first));
+  if (hkv % xcds == 0 || xcds % hkv == 0) {
+    long lo = got[0], hi = got[0];
+    for (int x = 0; x < xcds; ++x) {
+      lo = std::min(lo, got[x]);
+      hi = std::max(hi, got[x]);
+      if (hkv >= xcds ? (int)heads[x].size() > hkv / xcds : (int)heads[x].size() > 1)
+        return fail("heads of an XCD", x, (long)heads[x].size());
+    }
+    if (hi - lo > 1) return fail("unequal shares", lo, hi);  // the odd items go round in turn
+  }
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  if (argc != 2) return 2;
+  const int xcds = std::atoi(argv[1]);
+  std::mt19937 rng(7);
+  int cases = 0;
+  const int heads[][2] = {{32, 32}, {64, 8}, {28, 4}, {8, 2}, {5, 1}, {6, 3}, {12, 12}, {10, 5}, {16, 16}, {24, 24}};
+  for (auto& h : heads)
+    for (int t = 0; t < 24; ++t) {
+      const int n = t < 4 ? 1 : 1 + (int)(rng() % 64);
+      std::vector<int32_t> lens(n), prefix;
+      for (auto& x : lens) x = t % 5 == 0 ? 512 : (int)(rng() % (t % 3 ? 700 : 3000));
+      if (t % 2)
+        for (int r = 0; r < n; ++r) prefix.push_back((int)(rng() % 5000));
+      for (int64_t kv : {256, 512})
+        if (check(lens, prefix, h[0], h[1], kv, xcds)) return 1;
+      ++cases;
+    }
+  if (check({128}, {}, 32, 32, 512, xcds) || check({0, 1, 0, 129}, {}, 28, 4, 512, xcds)) return 1;
+  std::printf("ok %d\n", cases + 2);
+  return 0;
+}
