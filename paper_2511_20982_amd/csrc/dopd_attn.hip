@@ -291,15 +291,14 @@ dopd_status plan_prefill_bf16(dopd::PrefillArgs& a, int d, const int32_t* cu_hos
   if (items > INT32_MAX / 2) return DOPD_ERR_INVALID_SHAPE;
   int64_t blocks = items;
   a.xcd_order = 0;
-  a.xcds = 1;
+  a.by_split = dopd::fast_div((uint32_t)a.nsplit);
   if (nreq <= dopd::kPfMaxOrdered) {
-    a.xcd_order = 1;
-    a.xcds = machine_shape().xcds;
     dopd::pf_build_order(a.order, cu_host, PAGED ? prefix_host : nullptr, nreq, a.hq, a.hkv,
-                         (int64_t)2 * d * elem_bytes, a.xcds, split_requests);
-    for (int32_t r = 0; r <= nreq; ++r) a.cu_h[r] = cu_host[r];
-    for (int32_t r = 0; r < nreq; ++r) a.prefix_h[r] = PAGED ? prefix_host[r] : 0;
-    blocks = (int64_t)dopd::pf_order_places(a.order) * a.xcds;
+                         (int64_t)2 * d * elem_bytes, machine_shape().xcds, split_requests);
+    if (dopd::pf_order_fits(a.order, a.nsplit)) {
+      a.xcd_order = 1;
+      blocks = (int64_t)dopd::pf_order_places(a.order) * a.order.xcds;
+    }
   }
   blocks *= a.nsplit;  // (nsplit > 1 only on the paged path)
   if (blocks > INT32_MAX / 2) return DOPD_ERR_INVALID_SHAPE;
@@ -881,7 +880,7 @@ static dopd_status pd_step_impl(const dopd_attn_shape* s, const void* q_dec,
   p.n_wp = (int)(pages * hkv);
   // Block ranges; the prefill range starts on a multiple of the XCD count so
   // its XCD-aware order holds (blocks in the gaps exit at once).
-  const int64_t xc = std::max(1, p.pf.xcds);
+  const int64_t xc = std::max(1, p.pf.order.xcds);
   auto round_up = [&](int64_t x) { return (x + xc - 1) / xc * xc; };
   int64_t total;
   if (schedule == DOPD_PD_PREFILL_FIRST) {

@@ -40,7 +40,7 @@ template <int D, bool KV8 = false>
 __global__ __launch_bounds__(kPfThreads, 2) void pd_step_kernel(PdStepArgs s) {
   __shared__ __attribute__((aligned(16))) uint16_t sK0[pf_tile_elems<D>()], sK1[pf_tile_elems<D>()];
   __shared__ __attribute__((aligned(16))) uint16_t sV0[pf_tile_elems<D>()], sV1[pf_tile_elems<D>()];
-  __shared__ __attribute__((aligned(16))) uint16_t sQ[pf_q_lds_elems<D, false>()];
+  __shared__ __attribute__((aligned(16))) uint16_t sQ[pf_q_lds_elems<D>()];
   static_assert(2 * dec_wave_o_bytes<D>() <= (int)sizeof(sK0) &&
                     dec_wave_o_bytes<D>() <= (int)sizeof(sK1) && kDecMlBytes <= (int)sizeof(sQ),
                 "decode merge buffers fit the prefill tiles");

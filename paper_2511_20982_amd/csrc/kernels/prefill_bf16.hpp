@@ -44,12 +44,10 @@ struct PrefillArgs {
   const int32_t* cu;   // [nreq + 1]
   int nreq, hq, hkv, max_tiles;
   float scale_log2;
-  // XCD-aware order (used when nreq <= kPfMaxOrdered) and, with it, copies of
-  // cu and prefix; else heaviest q tiles first, found from cu.
-  int xcd_order, xcds;
+  // XCD-aware order (nreq <= kPfMaxOrdered); else heaviest q tiles first,
+  // found from cu.
+  int xcd_order;
   PfOrder order;
-  int cu_h[kPfMaxOrdered + 1];
-  int prefix_h[kPfMaxOrdered];
   // Chunk prefill over the paged cache (the paged instantiation only): the
   // chunk rows of request r are q[cu[r] .. cu[r+1]), its keys are the cached
   // positions 0 .. prefix[r] + chunk length - 1, read through the page table.
@@ -73,6 +71,7 @@ struct PrefillArgs {
   // [nsplit][T][Hq][D] and [nsplit][T][Hq][2] (m in the exp2 domain); the
   // merge kernel combines them.
   int nsplit;
+  FastDiv by_split;
   float* part_o;
   float* part_ml;
   int part_rows;              // T of the call
@@ -116,45 +115,63 @@ __device__ __forceinline__ bool pf_find_item_lpt(const PrefillArgs& a, int b, in
   return false;
 }
 
-// XCD-aware mapping: place s of XCD x (see PfOrder).
-__device__ __forceinline__ bool pf_find_item_xcd(const PrefillArgs& a, int x, int s, int& tile,
-                                                 int& req, int& h) {
-  const int l = lane_id();
-  const unsigned long long hit = __ballot(l < a.order.n && s < a.order.incl[l]);
-  if (hit == 0) return false;
-  const int k = __builtin_amdgcn_readfirstlane(__ffsll((long long)hit) - 1);
-  const int local = s - (k > 0 ? a.order.incl[k - 1] : 0);
-  const int g = a.hq / a.hkv, nt = a.order.nt[k];
-  int head = 0, idx = 0;
-  if (!pf_entry_item(a.order.rot[k], x, local, nt, g, a.hkv, a.xcds, head, idx)) return false;
-  req = a.order.req[k];
-  tile = a.order.tile0[k] + nt - 1 - idx / g;
-  h = head * g + idx % g;
+// A work item: q tile, query head, key split, and the request's rows.
+struct PfItem {
+  int tile, req, h, split;
+  int seq0, len, prefix;
+};
+
+// Item of workgroup b of the prefill; false when it has none.  With the XCD
+// order every lane reads one entry of the list from the arguments and the
+// chosen one is broadcast: one trip to memory before the item's own loads.
+template <bool PAGED>
+__device__ __forceinline__ bool pf_find_item(const PrefillArgs& a, int b, PfItem& it) {
+  if (a.xcd_order) {
+    const PfEntry e = a.order.e[lane_id()];
+    int s = fast_quot(b, a.order.by_xcds);
+    const int x = b - s * a.order.xcds;
+    it.split = 0;
+    if constexpr (PAGED) {
+      const int s0 = fast_quot(s, a.by_split);
+      it.split = s - s0 * a.nsplit;
+      s = s0;
+    }
+    const unsigned long long hit = __ballot(s < e.incl);  // (0 past the list)
+    if (hit == 0) return false;
+    const int k = __ffsll((long long)hit) - 1;
+    auto of = [&](int v) { return __builtin_amdgcn_readlane(v, k); };
+    const int local = s - (k > 0 ? __builtin_amdgcn_readlane(e.incl, k - 1) : 0);
+    int back = 0;
+    if (!pf_entry_item(a.order, of(e.rot), of(e.nt), x, local, back, it.h)) return false;
+    it.tile = of(e.tile0) + of(e.nt) - 1 - back;
+    it.req = of(e.req);
+    it.seq0 = of(e.seq0);
+    it.len = of(e.len);
+    it.prefix = of(e.prefix);
+    return true;
+  }
+  int tile, req, h;
+  it.split = PAGED ? b % a.nsplit : 0;
+  if (!pf_find_item_lpt(a, PAGED ? b / a.nsplit : b, tile, req, h)) return false;
+  it.tile = __builtin_amdgcn_readfirstlane(tile);
+  it.req = __builtin_amdgcn_readfirstlane(req);
+  it.h = __builtin_amdgcn_readfirstlane(h);
+  it.seq0 = __builtin_amdgcn_readfirstlane(a.cu[it.req]);
+  it.len = __builtin_amdgcn_readfirstlane(a.cu[it.req + 1]) - it.seq0;
+  it.prefix = PAGED ? __builtin_amdgcn_readfirstlane(a.prefix[it.req]) : 0;
   return true;
 }
 
-// Item and key split of workgroup b of the prefill.
-__device__ __forceinline__ bool pf_find_item(const PrefillArgs& a, int b, int nsplit, int& tile,
-                                             int& req, int& h, int& split) {
-  if (a.xcd_order) {
-    const int s = b / a.xcds;
-    split = s % nsplit;
-    return pf_find_item_xcd(a, b % a.xcds, s / nsplit, tile, req, h);
-  }
-  split = b % nsplit;
-  return pf_find_item_lpt(a, b / nsplit, tile, req, h);
-}
-
 // LDS of one prefill workgroup: K and V tiles, double-buffered, BN x D bf16
-// each, and (dense kernel) a copy of Q operands KS/2 .. KS-1 of every lane,
+// each, and a copy of Q operands KS/2 .. KS-1 of every lane,
 // [ks - KS/2][thread][8] (16 KiB at d = 128: two workgroups still fit a CU).
 // The diagonal steps read those from LDS, so the registers are free there and
 // the compiler does not spill the Q operands to scratch (whose reloads would
 // wait for the step's tile loads).
 template <int D>
 constexpr int pf_tile_elems() { return kPfBN * D; }
-template <int D, bool PAGED>
-constexpr int pf_q_lds_elems() { return PAGED ? 8 : (D / 32) * kPfThreads * 8; }
+template <int D>
+constexpr int pf_q_lds_elems() { return (D / 32) * kPfThreads * 8; }
 
 // One prefill work item (q tile, request, head; with key splits one split of
 // it): workgroup `bid` of the prefill's own numbering.  The LDS buffers are
@@ -178,29 +195,16 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs& a, int bid,
   auto kbuf = [&](int b) { return b ? sK1 : sK0; };
   auto vbuf = [&](int b) { return b ? sV1 : sV0; };
 
-  int tile, r, h, split;
-  if (!pf_find_item(a, bid, PAGED ? a.nsplit : 1, tile, r, h, split))
-    return;  // uniform across the workgroup
-  // The item is wave-uniform; say so, so that what derives from it stays scalar.
-  tile = __builtin_amdgcn_readfirstlane(tile);
-  r = __builtin_amdgcn_readfirstlane(r);
-  h = __builtin_amdgcn_readfirstlane(h);
+  PfItem item;
+  if (!pf_find_item<PAGED>(a, bid, item)) return;  // uniform across the workgroup
+  const int tile = item.tile, r = item.req, h = item.h, split = item.split;
   {
     const int tid = threadIdx.x, l = lane_id();
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = a.hq / a.hkv, kvh = h / g;
-    // With the XCD order the lengths come from the copies in the arguments
-    // (scalar loads, read whatever the order: a select between the two
-    // sources would become one generic load that waits on memory).
-    int seq0 = a.cu_h[min(r, kPfMaxOrdered)];
-    int L = a.cu_h[min(r + 1, kPfMaxOrdered)] - seq0;
-    int P = PAGED ? a.prefix_h[min(r, kPfMaxOrdered - 1)] : 0;
-    if (!a.xcd_order) {
-      seq0 = __builtin_amdgcn_readfirstlane(a.cu[r]);
-      L = __builtin_amdgcn_readfirstlane(a.cu[r + 1]) - seq0;
-      // Cached tokens before the chunk: query row i sits at key position P + i.
-      if constexpr (PAGED) P = __builtin_amdgcn_readfirstlane(a.prefix[r]);
-    }
+    const int seq0 = item.seq0, L = item.len;
+    // Cached tokens before the chunk: query row i sits at key position P + i.
+    const int P = PAGED ? item.prefix : 0;
     const int q0 = tile * BM;
     const int kv_end = P + min(L, q0 + BM);   // keys of this item: [0, kv_end)
     const int ntiles = (kv_end + BN - 1) / BN;
@@ -236,11 +240,9 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs& a, int bid,
             bf16x8, *reinterpret_cast<const u32x4*>(qp + (KV8 ? 32 * (ks / 2) + 8 * (ks % 2) : 16 * ks)));
     }
 
-    if constexpr (!PAGED) {  // (this lane's own slots: no barrier needed)
 #pragma unroll
-      for (int ks = KS / 2; ks < KS; ++ks)
-        *reinterpret_cast<bf16x8*>(sQ + ((ks - KS / 2) * kPfThreads + tid) * 8) = qop[ks];
-    }
+    for (int ks = KS / 2; ks < KS; ++ks)  // (this lane's own slots: no barrier needed)
+      *reinterpret_cast<bf16x8*>(sQ + ((ks - KS / 2) * kPfThreads + tid) * 8) = qop[ks];
     f32x16 oacc[ET];
 #pragma unroll
     for (int et = 0; et < ET; ++et)
@@ -470,30 +472,18 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs& a, int bid,
       }
       return ps0 + ps1;
     };
-    auto qk = [&](int buf, f32x16* s) {
+    // S^T of the first tile, and (from_lds) of the diagonal steps, which take
+    // Q operands KS/2 .. from this lane's copy in LDS.
+    auto qk = [&](int buf, f32x16* s, auto from_lds) {
       bf16x8 ka[2][KS];
       kread_all(buf, ka);
       zero2(s);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-        for (int tt = 0; tt < 2; ++tt)
-          s[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[tt][ks], qop[ks], s[tt], 0, 0, 0);
-    };
-    // S^T for the diagonal steps of the dense kernel: Q operands KS/2 .. from
-    // this lane's copy in LDS.
-    auto qk_lq = [&](int buf, f32x16* s) {
-      bf16x8 ka[2][KS];
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) ka[tt][ks] = kread(buf, tt, ks);
-      zero2(s);
-#pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         const bf16x8 qv =
-            ks < KS / 2 ? qop[ks]
-                        : *reinterpret_cast<const bf16x8*>(sQ + ((ks - KS / 2) * kPfThreads + tid) * 8);
+            from_lds && ks >= KS / 2
+                ? *reinterpret_cast<const bf16x8*>(sQ + ((ks - KS / 2) * kPfThreads + tid) * 8)
+                : qop[ks];
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt)
           s[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[tt][ks], qv, s[tt], 0, 0, 0);
@@ -512,9 +502,9 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs& a, int bid,
         for (int et = 0; et < ET; ++et)
           oacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[kk][et], pb[kk], oacc[et], 0, 0, 0);
       // Interleaving hints for the dense kernel's P.V only (its V operands
-      // come from two transposing reads each).  Measured: hints on the QK
-      // products cost the dense kernel 2-3 %, and any hints cost the paged
-      // kernel 8 % (404 against 148 bytes of spill per lane).
+      // come from two transposing reads each); on the paged kernel's P.V they
+      // bring a spill back into the steady steps (312 -> 346 us on 16 chunks
+      // of 512 over mixed prefixes).
       if constexpr (!PAGED) {
         __builtin_amdgcn_sched_group_barrier(kDsRead, 2 * ET, 0);
 #pragma unroll
@@ -558,6 +548,20 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs& a, int bid,
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt)
           sn[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[tt][ks], qop[ks], sn[tt], 0, 0, 0);
+      // The paged bf16 kernel spreads the K reads over the products: all 16
+      // read ahead, one Q operand was spilled, and its reload in every step
+      // waited for the step's tile loads as well (4 chunks of 512 behind 8000
+      // cached tokens, 64/8 heads, 555 -> 522 us; the dense kernel has no
+      // spill there and measured the same either way).
+      if constexpr (PAGED && !KV8) {
+        constexpr int kAhead = KS + 2;  // reads before the first product, of 2 KS
+        __builtin_amdgcn_sched_group_barrier(kDsRead, kAhead, 0);
+#pragma unroll
+        for (int i = 0; i < (2 * KS - kAhead + 1) / 2; ++i) {
+          __builtin_amdgcn_sched_group_barrier(kMfma, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(kDsRead, 2, 0);
+        }
+      }
       float psum = exponent(sc);
       if (__ballot(!(psum <= __builtin_exp2f(kSumLazy)))) {  // wave-uniform, rare
         rescale_to(row_max(sc));
@@ -639,7 +643,7 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs& a, int bid,
       load_v(0, 0);
     }
     __syncthreads();
-    if (wave_active && jb < je) qk(0, sa);  // every active row sees key jb * BN
+    if (wave_active && jb < je) qk(0, sa, std::false_type{});  // every active row sees key jb * BN
     // The steady-state steps form p against the running max without taking
     // the tile's max, so start it at the first tile's max (unmasked there).
     if (wave_active && jb < nfull && jb < je) m_run = row_max(sa);
@@ -660,16 +664,16 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs& a, int bid,
     };
     auto even = [] { return 0; };
     auto odd = [] { return 1; };
-    // The dense kernel raises the wave's priority over its softmax and the
-    // next tile's QK products, so its VALU work issues first and the other
-    // workgroup's P.V MFMAs fill the slots it leaves (measured 1-2 % faster;
-    // the paged kernel measured slower with it).
+    // The wave's priority is raised over the softmax and the next tile's QK
+    // products, so its VALU work issues first and the other workgroup's P.V
+    // MFMAs fill the slots it leaves (measured 1-2 % faster dense, 3-5 % over
+    // E4M3 and bf16 pages).
     auto step_full = [&](f32x16* sc, f32x16* sn, auto par) {
       prefetch(j, par);
       if (wave_active) {
-        if constexpr (!PAGED) __builtin_amdgcn_s_setprio(1);
+        __builtin_amdgcn_s_setprio(1);
         half_qk(sc, sn, par() ^ 1);
-        if constexpr (!PAGED) __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_s_setprio(0);
         pv(par());
       }
       if (j + 1 < je) clear_dead_v(par() ^ 1, j + 1);
@@ -695,8 +699,7 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs& a, int bid,
         pv(par());
       }
       if (wave_active && j + 1 < je && (j + 1) * BN <= P + row_w + 31) {
-        if constexpr (PAGED) qk(par() ^ 1, sa);
-        else qk_lq(par() ^ 1, sa);
+        qk(par() ^ 1, sa, std::true_type{});
       }
       if (j + 1 < je) clear_dead_v(par() ^ 1, j + 1);
       __syncthreads();
@@ -767,7 +770,7 @@ template <int D, bool PAGED, bool KV8 = false>
 __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16_kernel(PrefillArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t sK0[pf_tile_elems<D>()], sK1[pf_tile_elems<D>()];
   __shared__ __attribute__((aligned(16))) uint16_t sV0[pf_tile_elems<D>()], sV1[pf_tile_elems<D>()];
-  __shared__ __attribute__((aligned(16))) uint16_t sQ[pf_q_lds_elems<D, PAGED>()];
+  __shared__ __attribute__((aligned(16))) uint16_t sQ[pf_q_lds_elems<D>()];
   prefill_workgroup<D, PAGED, KV8>(a, (int)blockIdx.x, sK0, sK1, sV0, sV1, sQ);
 }
 

@@ -148,59 +148,74 @@ constexpr bool pf_xcd_valid(int b, int xcds, int per_xcd, int n_items) {
   return b / xcds < per_xcd && pf_xcd_item(b, xcds, per_xcd) < n_items;
 }
 
+// x / d by a multiplication, exact for x * d < 2^32 (the planner checks).
+struct FastDiv {
+  uint32_t d, m;
+};
+constexpr FastDiv fast_div(uint32_t d) { return {d, d > 1 ? (uint32_t)(((uint64_t)1 << 32) / d + 1) : 0}; }
+constexpr int fast_quot(int x, const FastDiv& f) {
+  return f.d > 1 ? (int)(((uint64_t)(uint32_t)x * f.m) >> 32) : x;
+}
+
 // The XCD-aware order (at most kPfMaxOrdered requests): a list of entries,
 // each a run of q tiles of one request, heaviest entry first; every entry's
-// items (KV head, q tile descending, query head of the group) are dealt over
-// all XCDs, so each XCD works through the same entries in the same order and
-// the XCDs finish together whatever the lengths.  (Against one contiguous
-// slice of a (KV head, request, q tile) list per XCD, where a slice restarted
-// with the long requests at every head and, with fewer heads than XCDs, one
-// XCD held the long requests and the next the short ones: 16 chunks of 512
-// over mixed prefixes, 32/32 heads, 424 -> 369 us; 8 short prompts, 28/4
-// heads, 39 -> 34 us; 16 long prompts, 32/32 heads, unchanged at 1.67 ms.)
-// Workgroup b is place b / xcds
-// of XCD b % xcds; entry k takes the places [incl[k - 1], incl[k]) of every XCD.
+// items are dealt over all XCDs, so each XCD works through the same entries in
+// the same order and the XCDs finish together whatever the lengths.  (Against
+// one contiguous slice of a (KV head, request, q tile) list per XCD, where a
+// slice restarted with the long requests at every head and, with fewer heads
+// than XCDs, one XCD held the long requests and the next the short ones: 16
+// chunks of 512 over mixed prefixes, 32/32 heads, 424 -> 369 us; 8 short
+// prompts, 28/4 heads, 39 -> 34 us; 16 long prompts, 32/32 heads, 1.70 -> 1.67
+// ms.)  Workgroup b is place b / xcds of XCD b % xcds; entry k takes the
+// places [e[k - 1].incl, e[k].incl) of every XCD.
+//   hkv a multiple of xcds: an XCD takes whole heads, its items in the order
+//     (q tile descending, KV head, query head);
+//   xcds a multiple of hkv: `share` XCDs take one head's (q tile descending,
+//     query head) list alternately;
+//   otherwise: contiguous slices of the (KV head, q tile descending, query
+//     head) list.
 constexpr int kPfMaxOrdered = 64;
+struct PfEntry {        // 32 bytes, read by one lane of the kernel
+  int incl;             // places per XCD up to and with this entry
+  int req, seq0, len, prefix;  // the request, its first row, rows, cached tokens
+  int tile0, nt;        // lowest q tile of the run, q tiles
+  int rot;              // XCD that takes the first item (where items do not divide evenly)
+};
 struct PfOrder {
-  int n;                       // entries
-  int req[kPfMaxOrdered];      // request of the entry
-  int tile0[kPfMaxOrdered];    // its first (lowest) q tile
-  int nt[kPfMaxOrdered];       // its q tiles
-  int incl[kPfMaxOrdered];     // places per XCD up to and with this entry
-  int rot[kPfMaxOrdered];      // XCD (of those that share a head) its first item goes to
+  int n;                // entries
+  int sliced;           // the third way above
+  int xcds, hkv, g;
+  FastDiv by_xcds, by_share, by_width;  // width: query heads an XCD takes of one q tile
+  PfEntry e[kPfMaxOrdered];
 };
 
-// Places an entry of nt q tiles takes on each XCD.  XCDs in a whole multiple
-// of the KV heads: xcds / hkv XCDs share a head's items alternately; otherwise
-// contiguous slices of the entry's items (whole heads when hkv is a multiple
-// of xcds), so that the items that read one head's K/V share an L2.
+// Places an entry of nt q tiles takes on each XCD.
 constexpr int pf_entry_places(int nt, int g, int hkv, int xcds) {
   return xcds % hkv == 0 ? pf_per_xcd(nt * g, xcds / hkv) : pf_per_xcd(nt * g * hkv, xcds);
 }
 
-// Item at place `local` of an entry of nt q tiles on XCD x: KV head and index
-// in the head's (q tile descending, query head) list, or false when there is
-// none.  rot moves the XCD that takes the first item, so that entries whose
-// items do not divide evenly give the odd ones to XCDs in turn.
-constexpr bool pf_entry_item(int rot, int x, int local, int nt, int g, int hkv, int xcds, int& head,
-                             int& idx) {
-  if (xcds % hkv == 0) {
-    const int share = xcds / hkv;
-    head = x / share;
-    idx = local * share + (x + share - rot) % share;
-    return idx < nt * g;
+// Item at place `local` of an entry (rot, nt) on XCD x: q tile counted from
+// the last of the run, and query head; false when there is none.
+constexpr bool pf_entry_item(const PfOrder& o, int rot, int nt, int x, int local, int& back, int& h) {
+  if (!o.sliced) {
+    const int share = (int)o.by_share.d, width = (int)o.by_width.d;
+    const int xs = fast_quot(x, o.by_share), y = x - xs * share + share - rot;
+    const int i = local * share + (y >= share ? y - share : y);
+    back = fast_quot(i, o.by_width);
+    h = xs * width + i - back * width;
+    return back < nt;
   }
-  const int per = pf_entry_places(nt, g, hkv, xcds), b = local * xcds + (x + xcds - rot) % xcds;
-  if (!pf_xcd_valid(b, xcds, per, nt * g * hkv)) return false;
-  const int i = pf_xcd_item(b, xcds, per);
-  head = i / (nt * g);
-  idx = i % (nt * g);
+  const int per = pf_entry_places(nt, o.g, o.hkv, o.xcds), b = local * o.xcds + (x + o.xcds - rot) % o.xcds;
+  if (!pf_xcd_valid(b, o.xcds, per, nt * o.g * o.hkv)) return false;
+  const int i = pf_xcd_item(b, o.xcds, per), head = i / (nt * o.g), idx = i % (nt * o.g);
+  back = idx / o.g;
+  h = head * o.g + idx % o.g;
   return true;
 }
 
 // The rot of the entry after one of nt q tiles with `rot`.
 constexpr int pf_entry_next_rot(int rot, int nt, int g, int hkv, int xcds) {
-  if (xcds % hkv == 0) return (rot + nt * g) % (xcds / hkv);
+  if (xcds % hkv == 0) return (int)(((int64_t)rot + (int64_t)nt * g) % (xcds / hkv));
   if (hkv % xcds == 0) return 0;
   const int per = pf_entry_places(nt, g, hkv, xcds);
   return (rot + (nt * g * hkv + per - 1) / per) % xcds;
@@ -231,6 +246,15 @@ inline void pf_build_order(PfOrder& o, const int32_t* cu_host, const int32_t* pr
                            int32_t nreq, int hq, int hkv, int64_t kv_token_bytes, int xcds,
                            bool split_requests = true) {
   const int g = hq / hkv;
+  const int heads_per_xcd = (hkv + xcds - 1) / xcds;
+  o.n = 0;
+  o.sliced = hkv % xcds != 0 && xcds % hkv != 0;
+  o.xcds = xcds;
+  o.hkv = hkv;
+  o.g = g;
+  o.by_xcds = fast_div((uint32_t)xcds);
+  o.by_share = fast_div((uint32_t)(xcds % hkv == 0 ? xcds / hkv : 1));
+  o.by_width = fast_div((uint32_t)(heads_per_xcd * g));
   auto len = [&](int r) { return cu_host[r + 1] - cu_host[r]; };
   auto prefix = [&](int r) { return prefix_host ? prefix_host[r] : 0; };
   auto tiles = [&](int r) { return (len(r) + kPfTileRows - 1) / kPfTileRows; };
@@ -239,23 +263,17 @@ inline void pf_build_order(PfOrder& o, const int32_t* cu_host, const int32_t* pr
     pairs += tiles(r);
     if (len(r) > 0) keys += (int64_t)len(r) + prefix(r);
   }
-  const int heads_per_xcd = (hkv + xcds - 1) / xcds;
   const bool split = split_requests && pairs <= kPfMaxOrdered &&
                      keys * heads_per_xcd * kv_token_bytes <= kPfL2Bytes;
   int64_t weight[kPfMaxOrdered];  // keys the entry's last row sees
-  o.n = 0;
   auto add = [&](int r, int t0, int nt, int64_t w) {
     int i = o.n++;
     for (; i > 0 && weight[i - 1] < w; --i) {  // stable insertion, heaviest first
       weight[i] = weight[i - 1];
-      o.req[i] = o.req[i - 1];
-      o.tile0[i] = o.tile0[i - 1];
-      o.nt[i] = o.nt[i - 1];
+      o.e[i] = o.e[i - 1];
     }
     weight[i] = w;
-    o.req[i] = r;
-    o.tile0[i] = t0;
-    o.nt[i] = nt;
+    o.e[i] = PfEntry{0, r, cu_host[r], len(r), prefix(r), t0, nt, 0};
   };
   for (int32_t r = 0; r < nreq; ++r) {
     if (tiles(r) == 0) continue;
@@ -268,14 +286,21 @@ inline void pf_build_order(PfOrder& o, const int32_t* cu_host, const int32_t* pr
   }
   int sum = 0, rot = 0;
   for (int k = 0; k < o.n; ++k) {
-    o.incl[k] = sum += pf_entry_places(o.nt[k], g, hkv, xcds);
-    o.rot[k] = rot;
-    rot = pf_entry_next_rot(rot, o.nt[k], g, hkv, xcds);
+    o.e[k].incl = sum += pf_entry_places(o.e[k].nt, g, hkv, xcds);
+    o.e[k].rot = rot;
+    rot = pf_entry_next_rot(rot, o.e[k].nt, g, hkv, xcds);
   }
 }
 
 // Places per XCD of the whole order.
-inline int pf_order_places(const PfOrder& o) { return o.n > 0 ? o.incl[o.n - 1] : 0; }
+inline int pf_order_places(const PfOrder& o) { return o.n > 0 ? o.e[o.n - 1].incl : 0; }
+
+// Do the order's divisions by multiplication hold for it with nsplit key splits?
+inline bool pf_order_fits(const PfOrder& o, int nsplit) {
+  const int64_t places = (int64_t)pf_order_places(o) * nsplit, top = (int64_t)1 << 32;
+  return places * o.xcds * std::max(o.xcds, nsplit) < top &&
+         (places + 1) * o.by_share.d * o.by_width.d < top;
+}
 
 inline int prefill_paged_splits(int hq, bool splittable, const int32_t* cu_host,
                                 const int32_t* prefix_host, int32_t nreq, int32_t num_splits,

@@ -32,19 +32,22 @@ static int check(const std::vector<int32_t>& lens, const std::vector<int32_t>& p
   std::vector<std::map<int, int>> heads(xcds);
   int64_t last = -1;
   for (int k = 0; k < o.n; ++k) {
-    const int r = o.req[k];
-    if (r < 0 || r >= n || o.nt[k] < 1 || o.tile0[k] < 0) return fail("entry", k, r);
+    const PfEntry& e = o.e[k];
+    const int r = e.req;
+    if (r < 0 || r >= n || e.nt < 1 || e.tile0 < 0) return fail("entry", k, r);
+    if (e.seq0 != cu[r] || e.len != lens[r] || e.prefix != (prefix.empty() ? 0 : prefix[r]))
+      return fail("entry's rows", k, r);
     const int64_t w = (prefix.empty() ? 0 : prefix[r]) +
-                      std::min<int64_t>(lens[r], (int64_t)(o.tile0[k] + o.nt[k]) * kPfTileRows);
+                      std::min<int64_t>(lens[r], (int64_t)(e.tile0 + e.nt) * kPfTileRows);
     if (last >= 0 && w > last) return fail("entries not heaviest first", k, (long)w);
     last = w;
-    const int places = o.incl[k] - (k ? o.incl[k - 1] : 0);
+    const int places = e.incl - (k ? o.e[k - 1].incl : 0);
     for (int x = 0; x < xcds; ++x)
       for (int local = 0; local < places; ++local) {
-        int head = -1, idx = -1;
-        if (!pf_entry_item(o.rot[k], x, local, o.nt[k], g, hkv, xcds, head, idx)) continue;
-        const int tile = o.tile0[k] + o.nt[k] - 1 - idx / g, h = head * g + idx % g;
-        if (head < 0 || head >= hkv || idx < 0 || idx >= o.nt[k] * g) return fail("item", head, idx);
+        int back = -1, h = -1;
+        if (!pf_entry_item(o, e.rot, e.nt, x, local, back, h)) continue;
+        const int tile = e.tile0 + e.nt - 1 - back, head = h / g;
+        if (h < 0 || h >= hq || back < 0 || back >= e.nt) return fail("item", h, back);
         if (tile < 0 || tile >= (lens[r] + kPfTileRows - 1) / kPfTileRows) return fail("tile", tile, lens[r]);
         ++seen[{r, tile, h}];
         ++got[x];
@@ -69,11 +72,23 @@ static int check(const std::vector<int32_t>& lens, const std::vector<int32_t>& p
   return 0;
 }
 
+static int check_fast_div() {
+  std::mt19937_64 rng(3);
+  for (uint32_t d : {1u, 2u, 3u, 6u, 7u, 8u, 28u, 56u, 64u, 100u, 4096u, 65535u})
+    for (int i = 0; i < 20000; ++i) {
+      const uint64_t top = std::min<uint64_t>(((uint64_t)1 << 32) / d, INT32_MAX);
+      const int x = i < 200 ? i : i < 400 ? (int)(top - 1 - (i - 200)) : (int)(rng() % top);
+      if (x >= 0 && fast_quot(x, fast_div(d)) != x / (int)d) return fail("fast_quot", x, d);
+    }
+  return 0;
+}
+
 int main(int argc, char** argv) {
   if (argc != 2) return 2;
   const int xcds = std::atoi(argv[1]);
   std::mt19937 rng(7);
   int cases = 0;
+  if (check_fast_div()) return 1;
   const int heads[][2] = {{32, 32}, {64, 8}, {28, 4}, {8, 2}, {5, 1}, {6, 3}, {12, 12}, {10, 5}, {16, 16}, {24, 24}};
   for (auto& h : heads)
     for (int t = 0; t < 24; ++t) {
