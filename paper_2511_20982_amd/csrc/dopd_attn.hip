@@ -126,6 +126,41 @@ dopd_status check_decode_host(const dopd_attn_shape* s, const int32_t* ctx_host,
   return DOPD_OK;
 }
 
+// ---- fp32 attention ----------------------------------------------------------
+dopd::AttnF32Args f32_args(const dopd_attn_shape* s, const void* q, const void* k, const void* v,
+                           void* out, float* lse, int32_t nreq) {
+  dopd::AttnF32Args f;
+  std::memset(&f, 0, sizeof(f));
+  f.q = (const float*)q;
+  f.k = (const float*)k;
+  f.v = (const float*)v;
+  f.out = (float*)out;
+  f.lse = lse;
+  f.nreq = nreq;
+  f.hq = s->num_q_heads;
+  f.hkv = s->num_kv_heads;
+  f.scale = s->softmax_scale;
+  return f;
+}
+
+// The fp32 kernel over chunks of cu_host (null: one row per request).
+template <bool PAGED>
+dopd_status launch_f32(const dopd::AttnF32Args& f, int d, const int32_t* cu_host, hipStream_t strm) {
+  const int64_t g = f.hq / f.hkv;
+  int64_t blocks = 0;
+  for (int32_t r = 0; r < f.nreq; ++r) {
+    const int64_t rows = cu_host ? (int64_t)cu_host[r + 1] - cu_host[r] : 1;
+    blocks += (rows * g + dopd::kF32Cols - 1) / dopd::kF32Cols * f.hkv;
+  }
+  if (blocks > INT32_MAX / 2) return DOPD_ERR_INVALID_SHAPE;
+  const dim3 grid((unsigned)blocks);
+  if (d == 64)
+    hipLaunchKernelGGL((dopd::attn_f32_kernel<64, PAGED>), grid, dim3(64 * dopd::f32_waves<64>()), 0, strm, f);
+  else
+    hipLaunchKernelGGL((dopd::attn_f32_kernel<128, PAGED>), grid, dim3(64 * dopd::f32_waves<128>()), 0, strm, f);
+  return launch_status();
+}
+
 // How the decode's partials are merged: not at all (every (request, KV head)
 // is one segment), by the kernel over the listed (r, c) (count > 0), or by
 // the kernel that finds them itself (the list does not fit its arguments).
@@ -386,19 +421,12 @@ dopd_status dopd_prefill_attn(const dopd_attn_shape* s, const void* q, const voi
     if (cu_host[r + 1] < cu_host[r]) return DOPD_ERR_INVALID_SHAPE;
   const int64_t T = cu_host[nreq];
   if (T == 0) return DOPD_OK;
-  const int hq = s->num_q_heads, hkv = s->num_kv_heads, d = s->head_dim;
+  const int d = s->head_dim;
   hipStream_t strm = as_stream(stream);
   if (s->dtype == DOPD_FP32) {
-    dim3 grid((unsigned)T, (unsigned)hq);
-    if (d == 64)
-      hipLaunchKernelGGL(dopd::prefill_f32_kernel<64>, grid, dim3(64), 0, strm, (const float*)q,
-                         (const float*)k, (const float*)v, (float*)out, lse, cu, nreq, hq, hkv,
-                         s->softmax_scale);
-    else
-      hipLaunchKernelGGL(dopd::prefill_f32_kernel<128>, grid, dim3(64), 0, strm, (const float*)q,
-                         (const float*)k, (const float*)v, (float*)out, lse, cu, nreq, hq, hkv,
-                         s->softmax_scale);
-    return launch_status();
+    dopd::AttnF32Args f = f32_args(s, q, k, v, out, lse, nreq);
+    f.cu = cu;
+    return launch_f32<false>(f, d, cu_host, strm);
   }
   dopd::PrefillArgs a = prefill_args(s, q, out, lse, cu);
   a.k = (const uint16_t*)k;
@@ -433,19 +461,15 @@ static dopd_status prefill_paged_impl(const dopd_attn_shape* s, const void* q, c
   }
   const int64_t T = cu_host[nreq];
   if (T == 0) return DOPD_OK;
-  const int hq = s->num_q_heads, hkv = s->num_kv_heads, d = s->head_dim;
+  const int hq = s->num_q_heads, d = s->head_dim;
   hipStream_t strm = as_stream(stream);
   if (s->dtype == DOPD_FP32) {
-    dim3 grid((unsigned)T, (unsigned)hq);
-    if (d == 64)
-      hipLaunchKernelGGL(dopd::prefill_paged_f32_kernel<64>, grid, dim3(64), 0, strm,
-                         (const float*)q, (const float*)k_pool, (const float*)v_pool, page_table,
-                         pt_stride, cu, prefix, nreq, hq, hkv, s->softmax_scale, (float*)out, lse);
-    else
-      hipLaunchKernelGGL(dopd::prefill_paged_f32_kernel<128>, grid, dim3(64), 0, strm,
-                         (const float*)q, (const float*)k_pool, (const float*)v_pool, page_table,
-                         pt_stride, cu, prefix, nreq, hq, hkv, s->softmax_scale, (float*)out, lse);
-    return launch_status();
+    dopd::AttnF32Args f = f32_args(s, q, k_pool, v_pool, out, lse, nreq);
+    f.cu = cu;
+    f.prefix = prefix;
+    f.page_table = page_table;
+    f.pt_stride = pt_stride;
+    return launch_f32<true>(f, d, cu_host, strm);
   }
   dopd::PrefillArgs a = prefill_args(s, q, out, lse, cu);
   a.k_pool = (const uint16_t*)k_pool;
@@ -644,23 +668,16 @@ dopd_status dopd_decode_attn(const dopd_attn_shape* s, const void* q, const void
   for (int32_t r = 0; r < nreq; ++r)
     if ((int64_t)(ctx_host[r] + dopd::kPage - 1) / dopd::kPage > pt_stride)
       return DOPD_ERR_INVALID_SHAPE;
-  const int hq = s->num_q_heads, hkv = s->num_kv_heads, d = s->head_dim;
-  hipStream_t strm = as_stream(stream);
   if (s->dtype == DOPD_FP32) {
-    dim3 grid((unsigned)nreq, (unsigned)hq);
-    if (d == 64)
-      hipLaunchKernelGGL(dopd::decode_f32_kernel<64>, grid, dim3(64), 0, strm, (const float*)q,
-                         (const float*)k_pool, (const float*)v_pool, pt, pt_stride, ctx, hq, hkv,
-                         s->softmax_scale, (float*)out, lse);
-    else
-      hipLaunchKernelGGL(dopd::decode_f32_kernel<128>, grid, dim3(64), 0, strm, (const float*)q,
-                         (const float*)k_pool, (const float*)v_pool, pt, pt_stride, ctx, hq, hkv,
-                         s->softmax_scale, (float*)out, lse);
-    return launch_status();
+    dopd::AttnF32Args f = f32_args(s, q, k_pool, v_pool, out, lse, nreq);
+    f.ctx = ctx;
+    f.page_table = pt;
+    f.pt_stride = pt_stride;
+    return launch_f32<true>(f, s->head_dim, nullptr, as_stream(stream));
   }
   return launch_decode_bf16<false>(s, q, k_pool, v_pool, nullptr, nullptr, pt, pt_stride, ctx,
                                    ctx_host, nreq, split_tokens, out, lse, workspace,
-                                   workspace_bytes, strm);
+                                   workspace_bytes, as_stream(stream));
 }
 
 dopd_status dopd_decode_attn_fp8(const dopd_attn_shape* s, const void* q, const void* k_pool,

@@ -1,133 +1,246 @@
-// fp32 attention (prefill and decode): one wave per (query row, head), lanes
-// split the head dimension, keys are visited in order with an online softmax
-// in fp32.  Used for the fp32 parity configuration; the bf16 paths are the
-// performance paths.
+// fp32 attention (prefill, chunk prefill and decode): fp32 operands, products
+// and sums throughout, on the fp32 matrix instruction.
+//
+// The query rows of one request that read one KV head form columns: column ci
+// is chunk row ci / g, query head c * g + ci % g (a decode step is a chunk of
+// one row), and sees cached positions 0 .. prefix + ci / g.  A workgroup takes
+// 16 columns; its W waves take the 16-key tiles w, w + W, ... and merge through
+// LDS.  Per tile and wave
+//   S^T[16 keys][16 cols] = K[16][d] . Q^T[d][16]     d / 4 v_mfma_f32_16x16x4_f32
+//   O^T[d][16 cols]      += V^T[d][16] . P^T[16][16]  (d / 16) x 4 of them
+// A contraction index may be permuted when both operands agree: a lane reads a
+// run of d / 4 elements of one K row, and the S^T accumulator (keys 4 (l / 16)
+// + 0..3) is the P^T operand as it stands.  The next tile's loads are in flight
+// while a tile is computed.
+//
+// Bound by latency at small sizes: the columns share each K/V load and the
+// waves share the keys, so a 120-key row is two tiles deep (one wave per (row,
+// head) that visited key after key took 0.3 - 0.45 us a key: prefill of four
+// prompts of up to 120 tokens, 8/2 heads, d 64, 37 us, their decode 55 us).
+//
+// Keys past a column's limit are masked by select in S^T, and V of positions
+// past the request's last key is replaced by 0.  A tile some columns see and
+// others do not whose V holds a NaN or an infinity is added key by key with
+// selects, so that no column takes 0 * inf from a key it does not see.
 #pragma once
 #include "common.hpp"
 
 namespace dopd {
 
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
+// Elements of the caller's fp32 arrays are aligned to 4 bytes only.
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ f32x4 load_f32x4(const float* p) { return *reinterpret_cast<const f32x4_a4*>(p); }
 
-// Attends one query row held as q[e = lane + 64*i] against n keys.
-// key(j, i) / val(j, i) return element lane + 64*i of key/value j.
-template <int D, class KeyFn, class ValFn>
-__device__ __forceinline__ void attend_row_f32(const float (&qv)[D / 64], int n, float scale,
-                                               KeyFn key, ValFn val, float (&o)[D / 64],
-                                               float& lse_out) {
-  float m = -INFINITY, l = 0.f;
+struct AttnF32Args {
+  const float* q;             // [T][Hq][D]
+  const float* k;             // fresh rows [T][Hkv][D], or the pool [P][Hkv][16][D]
+  const float* v;             // fresh rows [T][Hkv][D], or the pool [P][Hkv][D][16]
+  const int32_t* page_table;  // pools only: [nreq][pt_stride]
+  // Chunk rows of request r: [cu[r], cu[r + 1]); null: one row each, row r.
+  const int32_t* cu;
+  // Keys before the chunk: prefix[r] (null: 0).  One row each: ctx[r] - 1.
+  const int32_t* prefix;
+  const int32_t* ctx;
+  float* out;                 // [T][Hq][D]
+  float* lse;                 // [T][Hq] or null
+  int pt_stride, nreq, hq, hkv;
+  float scale;
+};
+
+constexpr int kF32Cols = 16;  // columns of a workgroup
+constexpr int kF32Keys = 16;  // keys of a tile (one page)
+
+// Waves of a workgroup: eight at d = 64; four at d = 128, whose two buffered
+// tiles take more than the registers eight would have.
+template <int D>
+constexpr int f32_waves() { return D == 64 ? 8 : 4; }
+
+template <int D, bool PAGED, int W = f32_waves<D>()>
+__global__ __launch_bounds__(64 * W) void attn_f32_kernel(AttnF32Args a) {
+  constexpr int KR = D / 4;     // elements of a K row one lane holds
+  constexpr int NT = D / 16;    // O^T tiles of 16 dims
+  constexpr int OP = D + 4;     // padded row of the merge buffer
+  __shared__ float s_o[W][kF32Cols][OP];
+  __shared__ float s_m[W][kF32Cols], s_l[W][kF32Cols];
+  const int tid = threadIdx.x, l = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int hq = a.hq, hkv = a.hkv, g = hq / hkv;
+
+  // Block: (request, column tile, KV head), the last column tiles (the most
+  // keys) of a request first.
+  auto rows_of = [&](int r) { return a.cu ? a.cu[r + 1] - a.cu[r] : 1; };
+  auto tiles_of = [&](int r) { return (rows_of(r) * g + kF32Cols - 1) / kF32Cols; };
+  int r, local;
+  if (!find_owner((int)blockIdx.x, a.nreq, [&](int x) { return tiles_of(x) * hkv; }, r, local))
+    return;  // uniform
+  r = __builtin_amdgcn_readfirstlane(r);
+  local = __builtin_amdgcn_readfirstlane(local);
+  const int L = rows_of(r), row0 = a.cu ? a.cu[r] : r;
+  const int P = a.ctx ? a.ctx[r] - 1 : (a.prefix ? a.prefix[r] : 0);
+  const int c = local % hkv;
+  const int ncols = L * g;
+  const int col0 = (tiles_of(r) - 1 - local / hkv) * kF32Cols;
+  const int cl = l & 15, qg = l >> 4;
+  const int ci = min(col0 + cl, ncols - 1);  // (columns past the end repeat the last; not stored)
+  const int limit = P + ci / g;              // last key this lane's column sees
+  const int first_limit = P + col0 / g;      // last key every column sees
+  const int nkeys = P + (min(col0 + kF32Cols, ncols) - 1) / g + 1;
+  const int ntiles = (nkeys + kF32Keys - 1) / kF32Keys;
+
+  // Q^T operand of step i: Q[col][KR qg + i].
+  float qv[KR];
+  {
+    const float* qp = a.q + ((int64_t)(row0 + ci / g) * hq + c * g + ci % g) * D + KR * qg;
 #pragma unroll
-  for (int i = 0; i < D / 64; ++i) o[i] = 0.f;
-  for (int j = 0; j < n; ++j) {
-    float part = 0.f;
+    for (int i = 0; i < KR; i += 4) {
+      const f32x4 x = load_f32x4(qp + i);
 #pragma unroll
-    for (int i = 0; i < D / 64; ++i) part += qv[i] * key(j, i);
-    const float s = wave_sum(part) * scale;
-    const float m_new = fmaxf(m, s);
-    const float alpha = expf(m - m_new);
-    const float p = expf(s - m_new);
-    l = l * alpha + p;
+      for (int j = 0; j < 4; ++j) qv[i + j] = x[j];
+    }
+  }
+
+  // Dim of O^T tile n, row x: fresh V rows are read NT dims at a time, pool
+  // rows (dim-major) a dim at a time.
+  auto dim_of = [](int n, int x) { return PAGED ? 16 * n + x : NT * x + n; };
+  const int32_t* pt = PAGED ? a.page_table + (int64_t)r * a.pt_stride : nullptr;
+  struct Tile {
+    f32x4 k[KR / 4];  // K[key l % 16][KR qg + 0 ..]
+    f32x4 v[NT];      // v[n][j] = V[key 4 qg + j][dim_of(n, l % 16)]
+  };
+  // Positions past the last key read the last one (fresh) or their page slot,
+  // which may hold anything (pools).
+  auto load = [&](Tile& t, int kt) {
+    if constexpr (PAGED) {
+      const int64_t blk = ((int64_t)pt[kt] * hkv + c) * (kPage * D);
+      const float* kp = a.k + blk + cl * D + KR * qg;
 #pragma unroll
-    for (int i = 0; i < D / 64; ++i) o[i] = o[i] * alpha + p * val(j, i);
+      for (int i = 0; i < KR / 4; ++i) t.k[i] = load_f32x4(kp + 4 * i);
+      const float* vp = a.v + blk + 4 * qg;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) t.v[n] = load_f32x4(vp + dim_of(n, cl) * kPage);
+    } else {
+      const int key = min(kt * kF32Keys + cl, nkeys - 1);
+      const float* kp = a.k + ((int64_t)(row0 + key) * hkv + c) * D + KR * qg;
+#pragma unroll
+      for (int i = 0; i < KR / 4; ++i) t.k[i] = load_f32x4(kp + 4 * i);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int kj = min(kt * kF32Keys + 4 * qg + j, nkeys - 1);
+        const float* vp = a.v + ((int64_t)(row0 + kj) * hkv + c) * D + NT * cl;
+#pragma unroll
+        for (int n = 0; n < NT; n += 4) {
+          const f32x4 x = load_f32x4(vp + n);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) t.v[n + i][j] = x[i];
+        }
+      }
+    }
+  };
+
+  f32x4 o[NT];
+#pragma unroll
+  for (int n = 0; n < NT; ++n) o[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, lsum = 0.f;  // of this lane's column; lsum of its own keys only
+
+  auto compute = [&](Tile& t, int kt) {
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < KR; i += 2) {
+      s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(t.k[i / 4][i % 4], qv[i], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(t.k[i / 4][i % 4 + 1], qv[i + 1], s1, 0, 0, 0);
+    }
+    const int key0 = kt * kF32Keys + 4 * qg;  // this lane's keys key0 .. key0 + 3
+    f32x4 s = (s0 + s1) * a.scale;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (key0 + j > limit) s[j] = -INFINITY;
+    float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m, mx);
+    const float base = m_new == -INFINITY ? 0.f : m_new;  // (no visible key so far: p = 0)
+    const float alpha = expf(m - base);
+    f32x4 p;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) p[j] = expf(s[j] - base);
+    lsum = lsum * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
     m = m_new;
-  }
-  const float inv = 1.f / l;
 #pragma unroll
-  for (int i = 0; i < D / 64; ++i) o[i] *= inv;
-  lse_out = m + logf(l);
-}
+    for (int n = 0; n < NT; ++n) o[n] *= alpha;
+    bool odd = false;
+    if (kt * kF32Keys + kF32Keys - 1 > first_limit) {  // uniform: some column does not see all keys
+      bool bad = false;
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (key0 + j >= nkeys) t.v[n][j] = 0.f;
+          bad |= !(fabsf(t.v[n][j]) < INFINITY);
+        }
+      odd = __ballot(bad) != 0;
+    }
+    if (!odd) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+          o[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.v[n][j], p[j], o[n], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        for (int src = 0; src < 4; ++src) {  // key 4 src + j of the tile
+          const float pk = __shfl(p[j], 16 * src + cl, 64);
+          const bool seen = kt * kF32Keys + 4 * src + j <= limit;
+#pragma unroll
+          for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {  // V[key][dim_of(n, 4 qg + x)] is lane 16 src + 4 qg + x's
+              const float vk = __shfl(t.v[n][j], 16 * src + 4 * qg + x, 64);
+              o[n][x] = seen ? o[n][x] + pk * vk : o[n][x];
+            }
+        }
+    }
+  };
 
-// Causal varlen prefill, fp32.  Grid: (T, Hq); block: 64.
-template <int D>
-__global__ __launch_bounds__(64) void prefill_f32_kernel(
-    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
-    float* __restrict__ out, float* __restrict__ lse, const int32_t* __restrict__ cu, int nreq,
-    int hq, int hkv, float scale) {
-  const int t = blockIdx.x, h = blockIdx.y, lane = lane_id();
-  int lo = 0, hi = nreq;  // request r with cu[r] <= t < cu[r+1]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) / 2;
-    if (cu[mid] <= t) lo = mid; else hi = mid;
+  if (w < ntiles) {
+    Tile t0, t1;
+    load(t0, w);
+    for (int kt = w; kt < ntiles; kt += 2 * W) {
+      if (kt + W < ntiles) load(t1, kt + W);
+      compute(t0, kt);
+      if (kt + W >= ntiles) break;
+      if (kt + 2 * W < ntiles) load(t0, kt + 2 * W);
+      compute(t1, kt + W);
+    }
   }
-  const int r = lo;
-  const int base = cu[r], i = t - base;
-  const int c = h / (hq / hkv);
-  float qv[D / 64], o[D / 64], ls;
-#pragma unroll
-  for (int x = 0; x < D / 64; ++x) qv[x] = q[((int64_t)t * hq + h) * D + lane + 64 * x];
-  auto key = [&](int j, int x) { return k[((int64_t)(base + j) * hkv + c) * D + lane + 64 * x]; };
-  auto val = [&](int j, int x) { return v[((int64_t)(base + j) * hkv + c) * D + lane + 64 * x]; };
-  attend_row_f32<D>(qv, i + 1, scale, key, val, o, ls);
-#pragma unroll
-  for (int x = 0; x < D / 64; ++x) out[((int64_t)t * hq + h) * D + lane + 64 * x] = o[x];
-  if (lse && lane == 0) lse[(int64_t)t * hq + h] = ls;
-}
-
-// Paged single-query decode, fp32.  Grid: (B, Hq); block: 64.
-template <int D>
-__global__ __launch_bounds__(64) void decode_f32_kernel(
-    const float* __restrict__ q, const float* __restrict__ k_pool,
-    const float* __restrict__ v_pool, const int32_t* __restrict__ page_table, int pt_stride,
-    const int32_t* __restrict__ ctx_lens, int hq, int hkv, float scale, float* __restrict__ out,
-    float* __restrict__ lse) {
-  const int r = blockIdx.x, h = blockIdx.y, lane = lane_id();
-  const int c = h / (hq / hkv);
-  const int n = ctx_lens[r];
-  const int32_t* pt = page_table + (int64_t)r * pt_stride;
-  float qv[D / 64], o[D / 64], ls;
-#pragma unroll
-  for (int x = 0; x < D / 64; ++x) qv[x] = q[((int64_t)r * hq + h) * D + lane + 64 * x];
-  auto key = [&](int j, int x) {
-    const int64_t page = pt[j / kPage];
-    return k_pool[((page * hkv + c) * kPage + j % kPage) * D + lane + 64 * x];
-  };
-  auto val = [&](int j, int x) {
-    const int64_t page = pt[j / kPage];
-    return v_pool[((page * hkv + c) * D + lane + 64 * x) * kPage + j % kPage];
-  };
-  attend_row_f32<D>(qv, n, scale, key, val, o, ls);
-#pragma unroll
-  for (int x = 0; x < D / 64; ++x) out[((int64_t)r * hq + h) * D + lane + 64 * x] = o[x];
-  if (lse && lane == 0) lse[(int64_t)r * hq + h] = ls;
-}
-
-// Chunk prefill over the paged cache, fp32: chunk token i of request r (query
-// row cu[r] + i) attends to cached positions 0 .. prefix[r] + i.  Grid: (T, Hq).
-template <int D>
-__global__ __launch_bounds__(64) void prefill_paged_f32_kernel(
-    const float* __restrict__ q, const float* __restrict__ k_pool,
-    const float* __restrict__ v_pool, const int32_t* __restrict__ page_table, int pt_stride,
-    const int32_t* __restrict__ cu, const int32_t* __restrict__ prefix, int nreq, int hq,
-    int hkv, float scale, float* __restrict__ out, float* __restrict__ lse) {
-  const int t = blockIdx.x, h = blockIdx.y, lane = lane_id();
-  int lo = 0, hi = nreq;  // request r with cu[r] <= t < cu[r+1]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) / 2;
-    if (cu[mid] <= t) lo = mid; else hi = mid;
+  lsum += __shfl_xor(lsum, 16, 64);
+  lsum += __shfl_xor(lsum, 32, 64);
+  if (qg == 0) {
+    s_m[w][cl] = m;
+    s_l[w][cl] = lsum;
   }
-  const int r = lo;
-  const int n = prefix[r] + (t - cu[r]) + 1;
-  const int c = h / (hq / hkv);
-  const int32_t* pt = page_table + (int64_t)r * pt_stride;
-  float qv[D / 64], o[D / 64], ls;
 #pragma unroll
-  for (int x = 0; x < D / 64; ++x) qv[x] = q[((int64_t)t * hq + h) * D + lane + 64 * x];
-  auto key = [&](int j, int x) {
-    const int64_t page = pt[j / kPage];
-    return k_pool[((page * hkv + c) * kPage + j % kPage) * D + lane + 64 * x];
-  };
-  auto val = [&](int j, int x) {
-    const int64_t page = pt[j / kPage];
-    return v_pool[((page * hkv + c) * D + lane + 64 * x) * kPage + j % kPage];
-  };
-  attend_row_f32<D>(qv, n, scale, key, val, o, ls);
+  for (int n = 0; n < NT; ++n)
 #pragma unroll
-  for (int x = 0; x < D / 64; ++x) out[((int64_t)t * hq + h) * D + lane + 64 * x] = o[x];
-  if (lse && lane == 0) lse[(int64_t)t * hq + h] = ls;
+    for (int j = 0; j < 4; ++j) s_o[w][cl][dim_of(n, 4 * qg + j)] = o[n][j];
+  __syncthreads();
+  const int live = min(kF32Cols, ncols - col0);
+  for (int i = tid; i < live * D; i += 64 * W) {
+    const int x = i / D, e = i % D, cx = col0 + x;
+    float M = s_m[0][x];
+#pragma unroll
+    for (int u = 1; u < W; ++u) M = fmaxf(M, s_m[u][x]);
+    float sum = 0.f, acc = 0.f;
+#pragma unroll
+    for (int u = 0; u < W; ++u) {
+      const float f = expf(s_m[u][x] - M);  // a wave that saw no key of the column: 0
+      sum += f * s_l[u][x];
+      acc += f * s_o[u][x][e];
+    }
+    const int64_t row = (int64_t)(row0 + cx / g) * hq + c * g + cx % g;
+    a.out[row * D + e] = acc * (1.f / sum);
+    if (a.lse && e == 0) a.lse[row] = M + logf(sum);
+  }
 }
 
 }  // namespace dopd

@@ -1,0 +1,82 @@
+"""GPU: the fp32 attention kernel at the edges of its tiles (16 columns of
+(row, head) pairs, 16 keys, waves without keys), against the fp64 oracle, and
+values no row may take from keys it does not see."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2511_20982_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _gpu(require_gpu):
+    pass
+
+
+from tests import gpu_util as G  # noqa: E402
+from tests.test_gpu_prefill_paged import paged_case  # noqa: E402
+
+# g = 1, 4, 7, 20: columns that fill tiles evenly, unevenly and more than one
+HEADS = [(2, 2), (8, 2), (7, 1), (20, 1)]
+
+
+@pytest.mark.parametrize("hq,hkv", HEADS)
+@pytest.mark.parametrize("d", [64, 128])
+def test_f32_prefill_and_decode(hq, hkv, d):
+    rng = np.random.default_rng(90 + hq + d)
+    lens = np.array([1, 2, 15, 16, 17, 0, 33, 64, 129, 200], np.int32)
+    q, k, v = I.prefill_batch(rng, lens, hq, hkv, d, "fp32")
+    cu = I.cu_from_lens(lens)
+    shape = G.A.make_shape(hq, hkv, d, "fp32")
+    ref, ref_lse = oracle.prefill(q, k, v, cu, shape.softmax_scale)
+    out, lse = G.gpu_prefill(shape, q, k, v, cu)
+    G.assert_attention_close(out, ref, "fp32", "fp32 prefill")
+    assert np.max(np.abs(lse - ref_lse)) < 1e-5
+
+    w = I.decode_workload("f32", 91 + hq, [1, 16, 17, 127, 128, 129, 500], hq, hkv, d, "fp32")
+    ref, ref_lse = oracle.decode(w.q_dec, w.k_pool, w.v_pool, w.page_table, w.context_lens, w.scale)
+    out, lse = G.gpu_decode(G.shape_of(w), w.q_dec, w.k_pool, w.v_pool, w.page_table, w.context_lens)
+    G.assert_attention_close(out, ref, "fp32", "fp32 decode")
+    assert np.max(np.abs(lse - ref_lse)) < 1e-5
+
+    q, kp, vp, pt, cu, pre = paged_case(92 + hq, [0, 1, 15, 16, 130, 0], [5, 17, 1, 40, 33, 0], hq, hkv, d, "fp32")
+    ref, ref_lse = oracle.prefill_paged(q, kp, vp, pt, cu, pre, shape.softmax_scale)
+    out, lse = G.gpu_prefill_paged(shape, q, kp, vp, pt, cu, pre)
+    G.assert_attention_close(out, ref, "fp32", "fp32 chunk prefill")
+    assert np.max(np.abs(lse - ref_lse)) < 1e-5
+
+
+@pytest.mark.parametrize("scale", [0.0, -0.3, 4.0])
+def test_f32_scales(scale):
+    rng = np.random.default_rng(93)
+    lens = np.array([40, 130], np.int32)
+    q, k, v = I.prefill_batch(rng, lens, 8, 2, 64, "fp32")
+    cu = I.cu_from_lens(lens)
+    ref, _ = oracle.prefill(q, k, v, cu, scale)
+    out, _ = G.gpu_prefill(G.A.make_shape(8, 2, 64, "fp32", scale), q, k, v, cu)
+    # scores up to 4 * 8 sqrt(64) round to 2^-24 of their size each way: at scale 4 that
+    # moves a weight by up to 4e-5 of itself (64 terms), the bar at scale <= 1 otherwise
+    assert np.max(np.abs(out - ref)) < (1e-5 if abs(scale) <= 1 else 1e-4)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_f32_unseen_keys_never_reach_a_row(d, bad):
+    """A V (or K) row that is not finite reaches the rows that see it and no other."""
+    rng = np.random.default_rng(94)
+    lens = np.array([70], np.int32)
+    q, k, v = I.prefill_batch(rng, lens, 8, 2, d, "fp32")
+    cu = I.cu_from_lens(lens)
+    shape = G.A.make_shape(8, 2, d, "fp32")
+    ref, _ = oracle.prefill(q, k, v, cu, shape.softmax_scale)
+    for which in (v, k):
+        t = 37
+        x = which.copy()
+        x[t] = bad
+        kk, vv = (k, x) if which is v else (x, v)
+        out, _ = G.gpu_prefill(shape, q, kk, vv, cu)
+        assert np.max(np.abs(out[:t] - ref[:t])) < 1e-5
+        if which is v:
+            assert not np.isfinite(out[t:]).any()
