@@ -575,6 +575,68 @@ dopd_status dopd_prefill_paged_attn_fp8(const dopd_attn_shape* s, const void* q,
 }
 
 // ---------------------------------------------------------------- kv write
+extern "C++" {
+namespace {
+
+// Page-writer workgroups of one page: kKvwWaves waves of HW heads each.
+template <typename TI, typename TO>
+int write_head_groups(int hkv, int d) {
+  const int per = dopd::kKvwWaves * (d == 64 ? dopd::PageWrite<TI, TO, 64>::HW : dopd::PageWrite<TI, TO, 128>::HW);
+  return (hkv + per - 1) / per;
+}
+
+template <typename TI, typename TO>
+dopd_status launch_kv_write(const dopd_attn_shape* s, const void* k_new, const void* v_new,
+                            const float* k_scale, const float* v_scale, void* k_pool, void* v_pool,
+                            const int32_t* pt, int32_t pt_stride, const int32_t* cu_new,
+                            const int32_t* start_pos, int32_t nreq, int32_t total_new, void* stream) {
+  dopd::KvWriteArgs<TI, TO> a;
+  a.k_new = static_cast<const TI*>(k_new);
+  a.v_new = static_cast<const TI*>(v_new);
+  a.k_scale = k_scale;
+  a.v_scale = v_scale;
+  a.k_pool = static_cast<TO*>(k_pool);
+  a.v_pool = static_cast<TO*>(v_pool);
+  a.page_table = pt;
+  a.cu_new = cu_new;
+  a.start_pos = start_pos;
+  a.pt_stride = pt_stride;
+  a.nreq = nreq;
+  a.hkv = s->num_kv_heads;
+  hipStream_t strm = as_stream(stream);
+  const int d = s->head_dim;
+  if (total_new <= dopd::kKvwAppendMean * (int64_t)nreq) {
+    const int64_t chunks = (int64_t)2 * a.hkv * d * sizeof(TI) / 16;
+    const int64_t groups = (chunks + 255) / 256;
+    if (groups * total_new > INT32_MAX) return DOPD_ERR_INVALID_SHAPE;
+    a.head_groups = (int)groups;
+    const dim3 grid((unsigned)(groups * total_new));
+    if (d == 64)
+      hipLaunchKernelGGL((dopd::kv_append_kernel<TI, TO, 64>), grid, dim3(256), 0, strm, a);
+    else
+      hipLaunchKernelGGL((dopd::kv_append_kernel<TI, TO, 128>), grid, dim3(256), 0, strm, a);
+    return launch_status();
+  }
+  // Touched pages per request <= n / 16 + 2, so this bounds the item count.
+  const int64_t pages = (int64_t)total_new / dopd::kPage + 2 * (int64_t)nreq + 1;
+  a.head_groups = write_head_groups<TI, TO>(a.hkv, d);
+  if (pages * a.head_groups > INT32_MAX) return DOPD_ERR_INVALID_SHAPE;
+  const dim3 grid((unsigned)(pages * a.head_groups)), block(64 * dopd::kKvwWaves);
+  if (d == 64)
+    hipLaunchKernelGGL((dopd::kv_write_kernel<TI, TO, 64>), grid, block, 0, strm, a);
+  else
+    hipLaunchKernelGGL((dopd::kv_write_kernel<TI, TO, 128>), grid, block, 0, strm, a);
+  return launch_status();
+}
+
+// Bounds of the writers' item counts.
+bool kv_write_too_large(const dopd_attn_shape* s, int32_t nreq, int32_t total_new) {
+  return (int64_t)total_new / dopd::kPage + 2 * (int64_t)nreq + 1 > INT32_MAX || s->num_kv_heads > 65535;
+}
+
+}  // namespace
+}  // extern "C++"
+
 dopd_status dopd_kv_write(const dopd_attn_shape* s, const void* k_new, const void* v_new,
                           void* k_pool, void* v_pool, int32_t num_pages, const int32_t* pt,
                           int32_t pt_stride, const int32_t* cu_new, const int32_t* start_pos,
@@ -585,32 +647,12 @@ dopd_status dopd_kv_write(const dopd_attn_shape* s, const void* k_new, const voi
   if (nreq == 0 || total_new == 0) return DOPD_OK;
   if (!k_new || !v_new || !k_pool || !v_pool || !pt || !cu_new || !start_pos)
     return DOPD_ERR_NULL_POINTER;
-  // Touched pages per request <= n/16 + 2, so this bounds the item count.
-  const int64_t blocks = (int64_t)total_new / dopd::kPage + 2 * (int64_t)nreq + 1;
-  if (blocks > INT32_MAX || s->num_kv_heads > 65535) return DOPD_ERR_INVALID_SHAPE;
-  hipStream_t strm = as_stream(stream);
-  const int hkv = s->num_kv_heads, d = s->head_dim;
-  const dim3 grid((unsigned)blocks, (unsigned)hkv), block(dopd::kKvwThreads);
-  if (s->dtype == DOPD_BF16) {
-    auto* kn = (const uint16_t*)k_new; auto* vn = (const uint16_t*)v_new;
-    auto* kp = (uint16_t*)k_pool; auto* vp = (uint16_t*)v_pool;
-    if (d == 64)
-      hipLaunchKernelGGL((dopd::kv_write_kernel<uint16_t, 64>), grid, block, 0, strm, kn, vn, kp, vp, pt,
-                         pt_stride, cu_new, start_pos, nreq, hkv);
-    else
-      hipLaunchKernelGGL((dopd::kv_write_kernel<uint16_t, 128>), grid, block, 0, strm, kn, vn, kp, vp, pt,
-                         pt_stride, cu_new, start_pos, nreq, hkv);
-  } else {
-    auto* kn = (const uint32_t*)k_new; auto* vn = (const uint32_t*)v_new;
-    auto* kp = (uint32_t*)k_pool; auto* vp = (uint32_t*)v_pool;
-    if (d == 64)
-      hipLaunchKernelGGL((dopd::kv_write_kernel<uint32_t, 64>), grid, block, 0, strm, kn, vn, kp, vp, pt,
-                         pt_stride, cu_new, start_pos, nreq, hkv);
-    else
-      hipLaunchKernelGGL((dopd::kv_write_kernel<uint32_t, 128>), grid, block, 0, strm, kn, vn, kp, vp, pt,
-                         pt_stride, cu_new, start_pos, nreq, hkv);
-  }
-  return launch_status();
+  if (kv_write_too_large(s, nreq, total_new)) return DOPD_ERR_INVALID_SHAPE;
+  if (s->dtype == DOPD_BF16)
+    return launch_kv_write<uint16_t, uint16_t>(s, k_new, v_new, nullptr, nullptr, k_pool, v_pool, pt,
+                                               pt_stride, cu_new, start_pos, nreq, total_new, stream);
+  return launch_kv_write<uint32_t, uint32_t>(s, k_new, v_new, nullptr, nullptr, k_pool, v_pool, pt,
+                                             pt_stride, cu_new, start_pos, nreq, total_new, stream);
 }
 
 dopd_status dopd_kv_write_fp8(const dopd_attn_shape* s, const void* k_new, const void* v_new,
@@ -626,22 +668,9 @@ dopd_status dopd_kv_write_fp8(const dopd_attn_shape* s, const void* k_new, const
   if (!k_new || !v_new || !k_scale || !v_scale || !k_pool || !v_pool || !pt || !cu_new ||
       !start_pos)
     return DOPD_ERR_NULL_POINTER;
-  const int64_t blocks = (int64_t)total_new / dopd::kPage + 2 * (int64_t)nreq + 1;
-  if (blocks > INT32_MAX || s->num_kv_heads > 65535) return DOPD_ERR_INVALID_SHAPE;
-  hipStream_t strm = as_stream(stream);
-  const int hkv = s->num_kv_heads;
-  const dim3 grid((unsigned)blocks, (unsigned)hkv), block(dopd::kKvwThreads);
-  auto* kn = (const uint16_t*)k_new;
-  auto* vn = (const uint16_t*)v_new;
-  auto* kp = (uint8_t*)k_pool;
-  auto* vp = (uint8_t*)v_pool;
-  if (s->head_dim == 64)
-    hipLaunchKernelGGL(dopd::kv_write_e4m3_kernel<64>, grid, block, 0, strm, kn, vn, k_scale,
-                       v_scale, kp, vp, pt, pt_stride, cu_new, start_pos, nreq, hkv);
-  else
-    hipLaunchKernelGGL(dopd::kv_write_e4m3_kernel<128>, grid, block, 0, strm, kn, vn, k_scale,
-                       v_scale, kp, vp, pt, pt_stride, cu_new, start_pos, nreq, hkv);
-  return launch_status();
+  if (kv_write_too_large(s, nreq, total_new)) return DOPD_ERR_INVALID_SHAPE;
+  return launch_kv_write<uint16_t, uint8_t>(s, k_new, v_new, k_scale, v_scale, k_pool, v_pool, pt,
+                                            pt_stride, cu_new, start_pos, nreq, total_new, stream);
 }
 
 // ---------------------------------------------------------------- decode
@@ -746,19 +775,20 @@ dopd_status check_fresh_prompts(const int32_t* cu_host, int32_t nreq, int32_t pt
 
 dopd::WritePackArgs write_pack_args(const void* k_new, const void* v_new, void* k_pool,
                                     void* v_pool, const int32_t* pt, int32_t pt_stride,
-                                    const int32_t* cu, int32_t nreq, int hkv,
+                                    const int32_t* cu, int32_t nreq, int hkv, int head_groups,
                                     const int64_t* out_offsets, void* out) {
   dopd::WritePackArgs w;
   w.k_new = (const uint16_t*)k_new;
   w.v_new = (const uint16_t*)v_new;
-  w.k_pool = (uint16_t*)k_pool;
-  w.v_pool = (uint16_t*)v_pool;
+  w.k_pool = k_pool;
+  w.v_pool = v_pool;
   w.page_table = pt;
   w.pt_stride = pt_stride;
   w.cu = cu;
   w.nreq = nreq;
   w.hkv = hkv;
-  w.out = (uint16_t*)out;
+  w.head_groups = head_groups;
+  w.out = out;
   w.out_off = out_offsets;
   w.k_scale = nullptr;
   w.v_scale = nullptr;
@@ -785,11 +815,12 @@ dopd_status dopd_kv_write_pack_for_handoff(const dopd_attn_shape* s, const void*
   int64_t pages = 0;
   st = check_fresh_prompts(cu_host, nreq, pt_stride, &pages);
   if (st != DOPD_OK) return st;
-  const int64_t blocks = pages * s->num_kv_heads;
+  if (pages * s->num_kv_heads > INT32_MAX) return DOPD_ERR_INVALID_SHAPE;
+  const int groups = write_head_groups<uint16_t, uint16_t>(s->num_kv_heads, s->head_dim);
+  const int64_t blocks = pages * groups;
   if (blocks == 0) return DOPD_OK;
-  if (blocks > INT32_MAX) return DOPD_ERR_INVALID_SHAPE;
   const dopd::WritePackArgs w = write_pack_args(k_new, v_new, k_pool, v_pool, pt, pt_stride, cu,
-                                                nreq, s->num_kv_heads, out_offsets, out);
+                                                nreq, s->num_kv_heads, groups, out_offsets, out);
   hipStream_t strm = as_stream(stream);
   if (s->head_dim == 64)
     hipLaunchKernelGGL(dopd::kv_write_pack_kernel<64>, dim3((unsigned)blocks), dim3(256), 0, strm, w);
@@ -879,6 +910,8 @@ static dopd_status pd_step_impl(const dopd_attn_shape* s, const void* q_dec,
     p.n_dec = p.dec.nwg;
   }
   int64_t pf_blocks = 0;
+  const int groups = kv8 ? write_head_groups<uint16_t, uint8_t>(hkv, d)
+                         : write_head_groups<uint16_t, uint16_t>(hkv, d);
   if (num_pre > 0 && cu_host[num_pre] > 0) {
     dopd_attn_shape sb = *s;  // the prefill reads the bf16 fresh rows
     sb.dtype = DOPD_BF16;
@@ -888,13 +921,13 @@ static dopd_status pd_step_impl(const dopd_attn_shape* s, const void* q_dec,
     st = plan_prefill_bf16<false>(p.pf, d, cu_host, nullptr, num_pre, 2, false, &pf_blocks);
     if (st != DOPD_OK) return st;
     p.wp = write_pack_args(k, v, k_pool, v_pool, pre_page_table, pt_stride, cu, num_pre, hkv,
-                           handoff_offsets, handoff_out);
+                           groups, handoff_offsets, handoff_out);
     p.wp.k_scale = k_scale;
     p.wp.v_scale = v_scale;
   }
   p.n_pf = (int)pf_blocks;
   if (pages * hkv > INT32_MAX / 4) return DOPD_ERR_INVALID_SHAPE;
-  p.n_wp = (int)(pages * hkv);
+  p.n_wp = (int)(pages * groups);
   // Block ranges; the prefill range starts on a multiple of the XCD count so
   // its XCD-aware order holds (blocks in the gaps exit at once).
   const int64_t xc = std::max(1, p.pf.order.xcds);

@@ -68,18 +68,21 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(AttnF32Args a) {
 
   // Block: (request, column tile, KV head), the last column tiles (the most
   // keys) of a request first.
-  auto rows_of = [&](int r) { return a.cu ? a.cu[r + 1] - a.cu[r] : 1; };
-  auto tiles_of = [&](int r) { return (rows_of(r) * g + kF32Cols - 1) / kF32Cols; };
+  auto tiles_of = [&](int rows) { return (rows * g + kF32Cols - 1) / kF32Cols; };
+  int row_l = 0, n_l = 0, pre_l = 0;  // this lane's request
+  auto items = [&](int x) {
+    row_l = a.cu ? a.cu[x] : x;
+    n_l = a.cu ? a.cu[x + 1] - row_l : 1;
+    pre_l = a.ctx ? a.ctx[x] - 1 : (a.prefix ? a.prefix[x] : 0);
+    return tiles_of(n_l) * hkv;
+  };
   int r, local;
-  if (!find_owner((int)blockIdx.x, a.nreq, [&](int x) { return tiles_of(x) * hkv; }, r, local))
-    return;  // uniform
-  r = __builtin_amdgcn_readfirstlane(r);
-  local = __builtin_amdgcn_readfirstlane(local);
-  const int L = rows_of(r), row0 = a.cu ? a.cu[r] : r;
-  const int P = a.ctx ? a.ctx[r] - 1 : (a.prefix ? a.prefix[r] : 0);
+  if (!find_owner((int)blockIdx.x, a.nreq, items, r, local)) return;  // uniform
+  const int L = __builtin_amdgcn_readlane(n_l, r % 64), row0 = __builtin_amdgcn_readlane(row_l, r % 64);
+  const int P = __builtin_amdgcn_readlane(pre_l, r % 64);
   const int c = local % hkv;
   const int ncols = L * g;
-  const int col0 = (tiles_of(r) - 1 - local / hkv) * kF32Cols;
+  const int col0 = (tiles_of(L) - 1 - local / hkv) * kF32Cols;
   const int cl = l & 15, qg = l >> 4;
   const int ci = min(col0 + cl, ncols - 1);  // (columns past the end repeat the last; not stored)
   const int limit = P + ci / g;              // last key this lane's column sees

@@ -56,20 +56,25 @@ __device__ __forceinline__ u32x2 bf16x4_from_e4m3x4(uint32_t w) {
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
-// Wave-wide inclusive prefix sum (wave64).
+// Wave-wide inclusive prefix sum (wave64), every lane active: within rows of 16
+// lanes, then the rows' totals, on the VALU's lane shifts (a scan by LDS
+// permutes is six dependent trips of ~60 ns).
 __device__ __forceinline__ int wave_inclusive_scan(int x) {
-  const int l = lane_id();
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int y = __shfl_up(x, o, 64);
-    if (l >= o) x += y;
-  }
+  constexpr int kShr = 0x110, kBcast15 = 0x142, kBcast31 = 0x143;
+  x += __builtin_amdgcn_update_dpp(0, x, kShr + 1, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, kShr + 2, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, kShr + 4, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, kShr + 8, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, kBcast15, 0xa, 0xf, false);  // rows 1, 3: row 0's, 2's total
+  x += __builtin_amdgcn_update_dpp(0, x, kBcast31, 0xc, 0xf, false);  // rows 2, 3: lane 31's
   return x;
 }
 
-// Locates the owner of global item `idx` when request r owns count(r) items,
-// laid out request after request.  Every lane of the wave gets the same answer.
-// Returns false when idx is past the last item.
+// Locates the owner of global item `idx` (the same in every lane) when request
+// r owns count(r) items, laid out request after request.  The answers are
+// uniform.  Returns false when idx is past the last item.  Every lane of the
+// wave takes part; count is called with r < nreq only, and last with the
+// owner's block of 64: what it loaded for the owner is in lane owner % 64.
 template <class CountFn>
 __device__ __forceinline__ bool find_owner(int idx, int nreq, CountFn count, int& owner,
                                            int& local) {
@@ -77,15 +82,15 @@ __device__ __forceinline__ bool find_owner(int idx, int nreq, CountFn count, int
   int base = 0;
   for (int r0 = 0; r0 < nreq; r0 += 64) {
     const int r = r0 + l;
-    const int c = (r < nreq) ? count(r) : 0;
+    const int v = count(min(r, nreq - 1));
+    const int c = r < nreq ? v : 0;
     const int incl = wave_inclusive_scan(c);
-    const int total = __shfl(incl, 63, 64);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
     if (idx < base + total) {
       const unsigned long long hit = __ballot(idx - base < incl);
       const int ol = __ffsll((long long)hit) - 1;
-      const int excl = __shfl(incl - c, ol, 64);
       owner = r0 + ol;
-      local = idx - base - excl;
+      local = idx - base - __builtin_amdgcn_readlane(incl - c, ol);
       return true;
     }
     base += total;

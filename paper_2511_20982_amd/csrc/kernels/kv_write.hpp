@@ -1,168 +1,302 @@
-// Paged KV writer: scatters fresh token-major K/V rows into the page pools.
+// Paged KV writers: scatter fresh token-major K/V rows into the page pools.
 //   k_pool[page][Hkv][16][d]  (token-major page),  v_pool[page][Hkv][d][16]  (dim-major page)
-// One workgroup per (request, touched logical page) x KV head; pure bit copy.
-// K rows are copied in 16-byte chunks; the V block is read as whole token rows
-// (16-byte loads), transposed through LDS and written as 16-byte runs of
-// slots.  Slots of a page outside the written range are never touched.
+// Bit copies (bf16, fp32), or E4M3 pools: each bf16 element x of KV head h
+// becomes the code of sat(x * fp32(1 / scale[h])) (product in fp32, rounded to
+// nearest even; codes rounded to nearest even).  Slots of a page outside the
+// written range are never touched.
+//
+// Two mappings.  The page writer gives a wave one (page, KV head) (two heads
+// at d = 64) and issues all of its 16-byte loads at once; a lane holds 4 tokens
+// of 8 (bf16) or 4 (fp32) dims of V, so the transposition to dim rows is done
+// in registers four tokens at a time and only gathers rows in LDS, privately
+// per wave (no workgroup barrier).  The append writer gives a wave 64 16-byte
+// chunks of one token: with one or two tokens per request every page is partial
+// and V is written element by element either way, and what counts is the chain
+// of loads that finds the request and its page.
+//
+// HBM-bound at size: E4M3 writes of 16 prompts (318 MB, 8 heads, d 128) 74 ->
+// 62 us (5.1 TB/s), bf16 writes of 16 prompts at 32 heads 262 -> 231 us
+// against one workgroup per (page, head) that transposed element by element
+// through LDS; the E4M3 append of 256 requests 15.3 -> 4.7 us.
 #pragma once
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace dopd {
 
-constexpr int kKvwThreads = 256;
+constexpr int kKvwWaves = 4;  // waves of a page-writer workgroup, consecutive heads of one page
 
-template <typename T, int D>  // T: uint16_t (bf16 bits) or uint32_t (fp32 bits)
-__global__ __launch_bounds__(kKvwThreads) void kv_write_kernel(
-    const T* __restrict__ k_new, const T* __restrict__ v_new, T* __restrict__ k_pool,
-    T* __restrict__ v_pool, const int32_t* __restrict__ page_table, int pt_stride,
-    const int32_t* __restrict__ cu_new, const int32_t* __restrict__ start_pos, int nreq, int hkv) {
-  constexpr int kEl = 16 / sizeof(T);  // elements per 16-byte chunk
-  constexpr int CPR = D / kEl;         // chunks per token row
-  constexpr int TP = D + kEl;          // padded LDS row (elements)
-  __shared__ __attribute__((aligned(16))) T s_v[kPage * TP];
+// Calls of at most this many new tokens per request on average take the append
+// writer (256 requests, 8 heads, d 128, kernel time append / pages: one token
+// each 5.4 / 8.7 us, E4M3 4.7 / 8.1; two, E4M3, 6.6 / 8.6; four the pages win).
+constexpr int kKvwAppendMean = 2;
 
-  // Touched logical pages of request r: those holding positions [start, start + n).
-  auto touched = [&](int rr) {
-    const int n = cu_new[rr + 1] - cu_new[rr];
-    if (n <= 0) return 0;
-    const int s = start_pos[rr];
-    return (s + n - 1) / kPage - s / kPage + 1;
-  };
-  int r, local;
-  if (!find_owner(blockIdx.x, nreq, touched, r, local)) return;  // uniform
-  const int h = blockIdx.y;
-  const int tid = threadIdx.x;
+// TI: element type of the fresh rows, TO: of the pools (uint16_t, uint32_t, or
+// uint16_t -> uint8_t for E4M3 pools).
+template <typename TI, typename TO, int D>
+struct PageWrite {
+  static constexpr bool kE4m3 = sizeof(TO) == 1;
+  static_assert(kE4m3 ? sizeof(TI) == 2 : sizeof(TI) == sizeof(TO), "a copy, or bf16 to E4M3");
+  static constexpr int EPC = 16 / (int)sizeof(TI);  // elements of a 16-byte chunk of a row
+  static constexpr int CPR = D / EPC;               // chunks of a row
+  static constexpr int CW = CPR < 16 ? CPR : 16;    // chunks of a row per pass
+  static constexpr int NP = CPR / CW;               // passes
+  static constexpr int HW = 16 / CW;                // heads of a wave
+  static constexpr int RB = kPage * (int)sizeof(TO);  // bytes of a dim row of a V page
+  // V rows in LDS, one row of padding after every EPC rows: the 64 lanes'
+  // pieces of four tokens fall into distinct banks.
+  static constexpr int ROWS = D + D / EPC;
+  static constexpr int kLdsBytes = HW * ROWS * RB;  // of one wave
+  using Out = std::conditional_t<kE4m3, u32x2, u32x4>;  // a chunk as the pools hold it
 
-  const int n = cu_new[r + 1] - cu_new[r];
-  const int start = start_pos[r];
-  const int lp = start / kPage + local;                 // logical page
-  const int p_lo = max(start, lp * kPage);              // first position written in this page
-  const int p_hi = min(start + n, lp * kPage + kPage);  // one past the last
-  const int s0 = p_lo - lp * kPage, s1 = p_hi - lp * kPage;
-  const int64_t page = page_table[(int64_t)r * pt_stride + lp];
-  const int64_t src0 = cu_new[r] + (p_lo - start);      // source row of slot s0
-  const int64_t row_elems = (int64_t)hkv * D;
-  T* kdst = k_pool + (page * hkv + h) * kPage * D;
-  T* vdst = v_pool + (page * hkv + h) * D * kPage;
-
-  // K: slot-major rows, chunk per thread; V rows staged in LDS.
-  for (int i = tid; i < kPage * CPR; i += kKvwThreads) {
-    const int slot = i / CPR, c = i % CPR;
-    if (slot >= s0 && slot < s1) {
-      const int64_t src = (src0 + slot - s0) * row_elems + (int64_t)h * D;  // source row
-      // Streaming (nontemporal) store: the rows are not read again soon, and
-      // they leave the caches now instead of being written back while the
-      // decode that follows streams the pools.
-      __builtin_nontemporal_store(reinterpret_cast<const u32x4*>(k_new + src)[c],
-                                  reinterpret_cast<u32x4*>(kdst + slot * D) + c);
-      *reinterpret_cast<u32x4*>(&s_v[slot * TP + c * kEl]) =
-          reinterpret_cast<const u32x4*>(v_new + src)[c];
+  static __device__ __forceinline__ Out convert(u32x4 x, float inv) {
+    if constexpr (kE4m3) {
+      Out o;
+#pragma unroll
+      for (int w = 0; w < 2; ++w)
+        o[w] = e4m3x4_from_f32(bf16_bits_to_f32(x[2 * w] & 0xffffu) * inv,
+                               bf16_bits_to_f32(x[2 * w] >> 16) * inv,
+                               bf16_bits_to_f32(x[2 * w + 1] & 0xffffu) * inv,
+                               bf16_bits_to_f32(x[2 * w + 1] >> 16) * inv);
+      return o;
+    } else {
+      return x;
     }
   }
-  __syncthreads();
-  // V^T: dim row e holds the page's 16 slots; a thread writes one 16-byte run.
-  constexpr int RUNS = kPage / kEl;  // 16-byte runs per dim row
-  const bool full = (s0 == 0 && s1 == kPage);
-  for (int i = tid; i < D * RUNS; i += kKvwThreads) {
-    const int e = i / RUNS, run = i % RUNS;
-    T* drow = vdst + e * kPage + run * kEl;
-    if (full) {
-      u32x4 x;
+};
+
+// Rows [s0, s1) of page `page` for the HW heads from h0 (those below hkv):
+// k_src / v_src point at KV head 0 of the row that goes to slot s0.  With pk /
+// pv (the handoff block's rows of slot 0, KV head 0; head h follows
+// pack_head elements later) the rows are written there too.  s: the wave's
+// kLdsBytes of LDS, 16-byte aligned.  Every lane of the wave takes part.
+template <typename TI, typename TO, int D, bool PACK>
+__device__ __forceinline__ void write_page_heads(const TI* k_src, const TI* v_src, int64_t row_elems,
+                                                 int h0, int hkv, int s0, int s1, TO* k_pool,
+                                                 TO* v_pool, int64_t page, const float* k_scale,
+                                                 const float* v_scale, TO* pk, TO* pv,
+                                                 int64_t pack_head, bool pack_aligned, uint8_t* s) {
+  using W = PageWrite<TI, TO, D>;
+  using Out = typename W::Out;
+  constexpr int EPC = W::EPC, CW = W::CW, NP = W::NP, HW = W::HW, RB = W::RB;
+  const int l = lane_id();
+  const int c = l % CW, tq = l / CW % 4, sub = l / (4 * CW);
+  const int h = h0 + sub;
+  const bool on = h < hkv;
+  const int64_t col = (int64_t)min(h, hkv - 1) * D + EPC * c;
+  // K: chunk u is token 4u + tq (whole rows in a row); V: token 4tq + u (four
+  // tokens of a dim in one lane).  Tokens outside [s0, s1) read the nearest
+  // one inside, so that no load waits behind a branch.
+  auto row = [&](int t) { return (min(max(t, s0), s1 - 1) - s0) * row_elems + col; };
+  u32x4 kx[NP][4], vx[NP][4];
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        if constexpr (sizeof(T) == 2) {
-          const int s = run * kEl + 2 * w;
-          x[w] = (uint32_t)s_v[s * TP + e] | ((uint32_t)s_v[(s + 1) * TP + e] << 16);
-        } else {
-          x[w] = s_v[(run * kEl + w) * TP + e];
+  for (int p = 0; p < NP; ++p)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      kx[p][u] = *reinterpret_cast<const u32x4*>(k_src + row(4 * u + tq) + EPC * CW * p);
+      vx[p][u] = *reinterpret_cast<const u32x4*>(v_src + row(4 * tq + u) + EPC * CW * p);
+    }
+  float kinv = 1.f, vinv = 1.f;
+  if constexpr (W::kE4m3) {
+    kinv = 1.0f / k_scale[on ? h : h0];
+    vinv = 1.0f / v_scale[on ? h : h0];
+  }
+  TO* kdst = k_pool + (page * hkv + h) * (kPage * D);
+  auto pack = [&](TO* base, int slot, int p, Out x) {
+    TO* d = base + h * pack_head + slot * D + EPC * (c + CW * p);
+    if (pack_aligned) {
+      __builtin_nontemporal_store(x, reinterpret_cast<Out*>(d));
+    } else {
+      const TO* e = reinterpret_cast<const TO*>(&x);
+#pragma unroll
+      for (int i = 0; i < EPC; ++i) d[i] = e[i];
+    }
+  };
+  const bool full = s0 == 0 && s1 == kPage;
+  // Rows out (and in the pack): whole pages of heads that are all there store
+  // without a test, so that no load sinks behind one.
+  Out v[NP][4];
+  auto rows_out = [&](auto whole) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int tk = 4 * u + tq, tv = 4 * tq + u;
+        const Out x = W::convert(kx[p][u], kinv);
+        v[p][u] = W::convert(vx[p][u], vinv);
+        if (whole || (on && tk >= s0 && tk < s1)) {
+          // Streaming stores here and below: the rows are not read again soon,
+          // and they leave the caches now instead of being written back while
+          // the decode that follows streams the pools.
+          __builtin_nontemporal_store(x, reinterpret_cast<Out*>(kdst + tk * D + EPC * (c + CW * p)));
+          if constexpr (PACK) {
+            if (pk) pack(pk, tk, p, x);
+          }
+        }
+        if constexpr (PACK) {
+          if (pv && (whole || (on && tv >= s0 && tv < s1))) pack(pv, tv, p, v[p][u]);
         }
       }
-      *reinterpret_cast<u32x4*>(drow) = x;
+  };
+  if (full && h0 + HW <= hkv) rows_out(std::true_type{});
+  else rows_out(std::false_type{});
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    // Dim i of the chunk: its four tokens side by side, into row e of the head.
+    uint8_t* piece = s + (sub * W::ROWS + (c + CW * p) * (EPC + 1)) * RB + tq * (RB / 4);
+    if constexpr (sizeof(TO) == 4) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<u32x4*>(piece + i * RB) = u32x4{v[p][0][i], v[p][1][i], v[p][2][i], v[p][3][i]};
+    } else if constexpr (sizeof(TO) == 2) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint32_t sel = i % 2 ? 0x07060302u : 0x05040100u;
+        *reinterpret_cast<u32x2*>(piece + i * RB) =
+            u32x2{__builtin_amdgcn_perm(v[p][1][i / 2], v[p][0][i / 2], sel),
+                  __builtin_amdgcn_perm(v[p][3][i / 2], v[p][2][i / 2], sel)};
+      }
     } else {
-      for (int k = 0; k < kEl; ++k) {
-        const int s = run * kEl + k;
-        if (s >= s0 && s < s1) drow[k] = s_v[s * TP + e];
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        const uint32_t a = __builtin_amdgcn_perm(v[p][1][w], v[p][0][w], 0x05010400u);  // t0 t1 of dims 0, 1
+        const uint32_t b = __builtin_amdgcn_perm(v[p][1][w], v[p][0][w], 0x07030602u);  // of dims 2, 3
+        const uint32_t d = __builtin_amdgcn_perm(v[p][3][w], v[p][2][w], 0x05010400u);
+        const uint32_t e = __builtin_amdgcn_perm(v[p][3][w], v[p][2][w], 0x07030602u);
+        uint32_t* r = reinterpret_cast<uint32_t*>(piece + 4 * w * RB);
+        r[0] = __builtin_amdgcn_perm(d, a, 0x05040100u);
+        r[RB / 4] = __builtin_amdgcn_perm(d, a, 0x07060302u);
+        r[2 * RB / 4] = __builtin_amdgcn_perm(e, b, 0x05040100u);
+        r[3 * RB / 4] = __builtin_amdgcn_perm(e, b, 0x07060302u);
+      }
+    }
+  }
+  // The LDS rows are this wave's alone (in order within the wave).
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  constexpr int PPR = RB / 16;       // 16-byte pieces of a dim row
+  constexpr int PIECES = D * PPR;    // of a head
+  constexpr int SPP = 16 / (int)sizeof(TO);  // slots of a piece
+  TO* vdst = v_pool + (page * hkv + h0) * (kPage * D);
+#pragma unroll
+  for (int k = 0; k < HW * PIECES / 64; ++k) {
+    const int i = l + 64 * k;
+    const int hs = i / PIECES, e = i % PIECES / PPR, run = i % PPR;
+    if (h0 + hs >= hkv) continue;
+    const u32x4 x = *reinterpret_cast<const u32x4*>(s + (hs * W::ROWS + e + e / EPC) * RB + 16 * run);
+    TO* d = vdst + (int64_t)hs * (kPage * D) + e * kPage + run * SPP;
+    if (full) {
+      __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(d));
+    } else {
+      const TO* xe = reinterpret_cast<const TO*>(&x);
+#pragma unroll
+      for (int t = 0; t < SPP; ++t) {
+        const int slot = run * SPP + t;
+        if (slot >= s0 && slot < s1) d[t] = xe[t];
       }
     }
   }
 }
 
-// FP8 variant: the same placement, with each bf16 element x of KV head h
-// stored as the E4M3 code of sat(x * fp32(1 / scale[h])) (product in fp32,
-// rounded to nearest even; codes rounded to nearest even).  Pools hold one
-// byte per element.  K rows: 8 elements (16 bytes in, 8 out) per thread; the
-// V codes are staged in LDS and written as dim rows of 16 slots (16 bytes).
-template <int D>
-__global__ __launch_bounds__(kKvwThreads) void kv_write_e4m3_kernel(
-    const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new,
-    const float* __restrict__ k_scale, const float* __restrict__ v_scale,
-    uint8_t* __restrict__ k_pool, uint8_t* __restrict__ v_pool,
-    const int32_t* __restrict__ page_table, int pt_stride, const int32_t* __restrict__ cu_new,
-    const int32_t* __restrict__ start_pos, int nreq, int hkv) {
-  constexpr int CPR = D / 8;  // 8-element chunks per token row
-  constexpr int TP = D + 8;   // padded LDS row (bytes)
-  __shared__ __attribute__((aligned(16))) uint8_t s_v[kPage * TP];
+template <typename TI, typename TO>
+struct KvWriteArgs {
+  const TI* k_new;            // [T][Hkv][D]
+  const TI* v_new;
+  const float* k_scale;       // [Hkv], E4M3 pools only
+  const float* v_scale;
+  TO* k_pool;
+  TO* v_pool;
+  const int32_t* page_table;  // [nreq][pt_stride]
+  const int32_t* cu_new;      // [nreq + 1]
+  const int32_t* start_pos;   // [nreq]
+  int pt_stride, nreq, hkv;
+  int head_groups;            // workgroups of a page (page writer) or of a token (append writer)
+};
 
+// Page writer: workgroup b takes heads kKvwWaves * HW * (b % head_groups) .. of
+// the (b / head_groups)-th touched page.
+template <typename TI, typename TO, int D>
+__global__ __launch_bounds__(64 * kKvwWaves) void kv_write_kernel(KvWriteArgs<TI, TO> a) {
+  using W = PageWrite<TI, TO, D>;
+  __shared__ __attribute__((aligned(16))) uint8_t s[kKvwWaves][W::kLdsBytes];
+  // Touched logical pages of request r: those holding positions [start, start + n).
+  int cu_l = 0, n_l = 0, st_l = 0;  // this lane's request
   auto touched = [&](int rr) {
-    const int n = cu_new[rr + 1] - cu_new[rr];
-    if (n <= 0) return 0;
-    const int s = start_pos[rr];
-    return (s + n - 1) / kPage - s / kPage + 1;
+    cu_l = a.cu_new[rr];
+    n_l = a.cu_new[rr + 1] - cu_l;
+    st_l = a.start_pos[rr];
+    asm volatile("" : "+v"(st_l));  // (loaded beside cu_new, not after the test)
+    return n_l > 0 ? (st_l + n_l - 1) / kPage - st_l / kPage + 1 : 0;
   };
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int h0 = ((int)blockIdx.x % a.head_groups * kKvwWaves + w) * W::HW;
+  if (h0 >= a.hkv) return;
   int r, local;
-  if (!find_owner(blockIdx.x, nreq, touched, r, local)) return;  // uniform
-  const int h = blockIdx.y;
-  const int tid = threadIdx.x;
+  if (!find_owner((int)blockIdx.x / a.head_groups, a.nreq, touched, r, local)) return;
+  const int row0 = __builtin_amdgcn_readlane(cu_l, r % 64), n = __builtin_amdgcn_readlane(n_l, r % 64);
+  const int start = __builtin_amdgcn_readlane(st_l, r % 64);
+  const int lp = start / kPage + local;                 // logical page
+  const int p_lo = max(start, lp * kPage);              // first position written in this page
+  const int p_hi = min(start + n, lp * kPage + kPage);  // one past the last
+  const int64_t page = a.page_table[(int64_t)r * a.pt_stride + lp];
+  const int64_t row_elems = (int64_t)a.hkv * D;
+  const int64_t src = ((int64_t)row0 + (p_lo - start)) * row_elems;
+  write_page_heads<TI, TO, D, false>(a.k_new + src, a.v_new + src, row_elems, h0, a.hkv,
+                                     p_lo - lp * kPage, p_hi - lp * kPage, a.k_pool, a.v_pool, page,
+                                     a.k_scale, a.v_scale, (TO*)nullptr, (TO*)nullptr, 0, false, s[w]);
+}
 
-  const int n = cu_new[r + 1] - cu_new[r];
-  const int start = start_pos[r];
-  const int lp = start / kPage + local;
-  const int p_lo = max(start, lp * kPage);
-  const int p_hi = min(start + n, lp * kPage + kPage);
-  const int s0 = p_lo - lp * kPage, s1 = p_hi - lp * kPage;
-  const int64_t page = page_table[(int64_t)r * pt_stride + lp];
-  const int64_t src0 = cu_new[r] + (p_lo - start);
-  const int64_t row_elems = (int64_t)hkv * D;
-  uint8_t* kdst = k_pool + (page * hkv + h) * kPage * D;
-  uint8_t* vdst = v_pool + (page * hkv + h) * D * kPage;
-  const float kinv = 1.0f / k_scale[h], vinv = 1.0f / v_scale[h];
-
-  auto codes8 = [](u32x4 x, float inv) {  // 8 bf16 -> 8 codes
-    u32x2 o;
-#pragma unroll
-    for (int w = 0; w < 2; ++w)
-      o[w] = e4m3x4_from_f32(bf16_bits_to_f32(x[2 * w] & 0xffffu) * inv,
-                             bf16_bits_to_f32(x[2 * w] >> 16) * inv,
-                             bf16_bits_to_f32(x[2 * w + 1] & 0xffffu) * inv,
-                             bf16_bits_to_f32(x[2 * w + 1] >> 16) * inv);
-    return o;
-  };
-  for (int i = tid; i < kPage * CPR; i += kKvwThreads) {
-    const int slot = i / CPR, c = i % CPR;
-    if (slot >= s0 && slot < s1) {
-      const int64_t src = (src0 + slot - s0) * row_elems + (int64_t)h * D;
-      reinterpret_cast<u32x2*>(kdst + slot * D)[c] =
-          codes8(reinterpret_cast<const u32x4*>(k_new + src)[c], kinv);
-      *reinterpret_cast<u32x2*>(&s_v[slot * TP + c * 8]) =
-          codes8(reinterpret_cast<const u32x4*>(v_new + src)[c], vinv);
-    }
+// The request whose rows hold token t: the last r with cu[r] <= t, found by
+// whole-wave steps (two trips to memory up to 4096 requests).
+__device__ __forceinline__ int find_token_owner(const int32_t* cu, int nreq, int t) {
+  const int l = lane_id();
+  int lo = 0, n = nreq;  // cu[lo] <= t < cu[lo + n]
+  while (n > 1) {
+    const int step = (n + 63) / 64;
+    const bool in = l * step < n;
+    const int v = in ? cu[lo + l * step] : 0;
+    const int j = __popcll(__ballot(in && v <= t)) - 1;
+    lo += j * step;
+    n = min(step, n - j * step);
   }
-  __syncthreads();
-  // V^T: dim row e holds the page's 16 slots, one 16-byte run.
-  const bool full = (s0 == 0 && s1 == kPage);
-  for (int e = tid; e < D; e += kKvwThreads) {
-    uint8_t* drow = vdst + e * kPage;
-    if (full) {
-      u32x4 x;
+  return __builtin_amdgcn_readfirstlane(lo);
+}
+
+// Append writer: workgroup b takes 256 of the 2 x Hkv x (D / EPC) chunks (K's,
+// then V's) of token b / head_groups.
+template <typename TI, typename TO, int D>
+__global__ __launch_bounds__(256) void kv_append_kernel(KvWriteArgs<TI, TO> a) {
+  using W = PageWrite<TI, TO, D>;
+  using Out = typename W::Out;
+  const int t = (int)blockIdx.x / a.head_groups;
+  const int i = (int)blockIdx.x % a.head_groups * 256 + (int)threadIdx.x;
+  const int half = a.hkv * W::CPR;
+  const bool is_v = i >= half, on = i < 2 * half;
+  const int j = is_v ? i - half : i;
+  const int h = j / W::CPR, c = j % W::CPR;
+  u32x4 x = {0, 0, 0, 0};
+  float scale = 1.f;
+  if (on) {
+    x = *reinterpret_cast<const u32x4*>((is_v ? a.v_new : a.k_new) + ((int64_t)t * a.hkv + h) * D + W::EPC * c);
+    if constexpr (W::kE4m3) scale = is_v ? a.v_scale[h] : a.k_scale[h];
+  }
+  if (t >= a.cu_new[a.nreq]) return;  // uniform
+  const int r = find_token_owner(a.cu_new, a.nreq, t);
+  const int pos = a.start_pos[r] + (t - a.cu_new[r]);
+  const int64_t page = a.page_table[(int64_t)r * a.pt_stride + pos / kPage];
+  if (!on) return;
+  const Out y = W::convert(x, W::kE4m3 ? 1.0f / scale : 1.f);
+  const int slot = pos % kPage;
+  const int64_t blk = (page * a.hkv + h) * (kPage * D);
+  if (!is_v) {
+    __builtin_nontemporal_store(y, reinterpret_cast<Out*>(a.k_pool + blk + slot * D + W::EPC * c));
+  } else {
+    const TO* e = reinterpret_cast<const TO*>(&y);
+    TO* d = a.v_pool + blk + W::EPC * c * kPage + slot;
 #pragma unroll
-      for (int w = 0; w < 4; ++w)
-        x[w] = (uint32_t)s_v[(4 * w) * TP + e] | ((uint32_t)s_v[(4 * w + 1) * TP + e] << 8) |
-               ((uint32_t)s_v[(4 * w + 2) * TP + e] << 16) |
-               ((uint32_t)s_v[(4 * w + 3) * TP + e] << 24);
-      *reinterpret_cast<u32x4*>(drow) = x;
-    } else {
-      for (int s = s0; s < s1; ++s) drow[s] = s_v[s * TP + e];
-    }
+    for (int u = 0; u < W::EPC; ++u) d[u * kPage] = e[u];
   }
 }
 

@@ -5,7 +5,7 @@
 // a compute-bound prefill item can share a CU).
 //
 // Block ranges of the grid, in the order the host chose (schedule):
-//   [wp_first, + n_wp)  write + pack: (logical page, KV head) of the prompts
+//   [wp_first, + n_wp)  write + pack: (logical page, heads) of the prompts
 //   [pf_first, + n_pf)  prefill items (the XCD-aware order of the prefill
 //                       kernel; pf_first is a multiple of the XCD count so a
 //                       block's XCD is the one the order assumes)
@@ -31,7 +31,7 @@ struct PdStepArgs {
   DecodeArgs dec;
   PrefillArgs pf;
   WritePackArgs wp;
-  int wp_first, n_wp;    // write + pack blocks (n_wp = pages x Hkv)
+  int wp_first, n_wp;    // write + pack blocks (n_wp = pages x head groups)
   int pf_first, n_pf;    // prefill blocks
   int dec_first, n_dec;  // decode blocks (n_dec = dec.nwg)
 };
@@ -44,7 +44,9 @@ __global__ __launch_bounds__(kPfThreads, 2) void pd_step_kernel(PdStepArgs s) {
   static_assert(2 * dec_wave_o_bytes<D>() <= (int)sizeof(sK0) &&
                     dec_wave_o_bytes<D>() <= (int)sizeof(sK1) && kDecMlBytes <= (int)sizeof(sQ),
                 "decode merge buffers fit the prefill tiles");
-  static_assert(kPage * (D + 8) * 2 <= (int)sizeof(sV0), "writer staging fits a V tile");
+  using PoolT = std::conditional_t<KV8, uint8_t, uint16_t>;
+  static_assert(PageWrite<uint16_t, PoolT, D>::kLdsBytes <= (int)sizeof(sV0) && kPfThreads == 64 * kKvwWaves,
+                "a wave's writer rows fit a tile buffer");
   const int b = blockIdx.x;
   if (b >= s.pf_first && b < s.pf_first + s.n_pf) {
     prefill_workgroup<D, false>(s.pf, b - s.pf_first, sK0, sK1, sV0, sV1, sQ);
@@ -55,11 +57,9 @@ __global__ __launch_bounds__(kPfThreads, 2) void pd_step_kernel(PdStepArgs s) {
                                reinterpret_cast<f32x4*>(sK0 + kWaveElems),
                                reinterpret_cast<f32x4*>(sK1));
   } else if (b >= s.wp_first && b < s.wp_first + s.n_wp) {
-    const int j = b - s.wp_first;
-    if constexpr (KV8)
-      kv_write_pack_e4m3_workgroup<D>(s.wp, j / s.wp.hkv, j % s.wp.hkv, reinterpret_cast<uint8_t*>(sV0));
-    else
-      kv_write_pack_workgroup<D>(s.wp, j / s.wp.hkv, j % s.wp.hkv, sV0);
+    const int w = threadIdx.x >> 6;
+    uint16_t* rows = w == 0 ? sK0 : w == 1 ? sK1 : w == 2 ? sV0 : sV1;
+    kv_write_pack_workgroup<PoolT, D>(s.wp, b - s.wp_first, reinterpret_cast<uint8_t*>(rows));
   }
 }
 

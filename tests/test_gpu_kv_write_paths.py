@@ -1,0 +1,64 @@
+"""GPU: both mappings of the paged writers (whole pages of a few heads per
+workgroup; single tokens), at head counts that leave waves without work, more
+requests than a wave has lanes, empty requests and pages entered midway.  Bit
+for bit against a plain index map."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2511_20982_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _gpu(require_gpu):
+    pass
+
+
+from tests import gpu_util as G  # noqa: E402
+
+
+def lengths(rng, nreq, tokens):
+    """New tokens per request: `tokens` on average, empty ones among them."""
+    n = rng.integers(0, 2 * tokens + 1, nreq)
+    n[-1] = max(1, n[-1])
+    return n.astype(np.int32)
+
+
+# (requests, mean new tokens): one token each, either side of the mapping's
+# line at two per request, whole prompts; 65 and 130 pass one wave's lanes
+@pytest.mark.parametrize("nreq,tokens", [(1, 1), (65, 1), (130, 2), (66, 3), (3, 40)])
+@pytest.mark.parametrize("hkv,d", [(1, 64), (3, 64), (5, 128), (8, 128)])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32", "fp8"])
+def test_paged_write(dtype, hkv, d, nreq, tokens):
+    rng = np.random.default_rng(nreq + 7 * tokens + 31 * hkv + d)
+    fresh = "fp32" if dtype == "fp32" else "bf16"
+    n = lengths(rng, nreq, tokens)
+    start = rng.integers(0, 40, nreq).astype(np.int32)
+    pt, num_pages = I.allocate_pages(rng, n + start)
+    cu = I.cu_from_lens(n)
+    total = int(cu[-1])
+    k, v = I.normal(rng, (total, hkv, d), fresh), I.normal(rng, (total, hkv, d), fresh)
+    shape = G.A.make_shape(hkv, hkv, d, dtype)
+    kp, vp = I.empty_pools(num_pages, hkv, d, fresh)
+    if dtype == "fp8":
+        kp = rng.integers(0, 255, kp.shape, dtype=np.uint8)
+        vp = rng.integers(0, 255, vp.shape, dtype=np.uint8)
+        ks = (0.005 + 0.01 * rng.random(hkv)).astype(np.float32)
+        vs = (0.005 + 0.01 * rng.random(hkv)).astype(np.float32)
+        kw, vw = oracle.e4m3_quantize(k, ks), oracle.e4m3_quantize(v, vs)
+        gk, gv = G.gpu_kv_write_fp8(shape, k, v, ks, vs, kp, vp, pt, cu, start)
+    else:
+        kw, vw = k, v
+        gk, gv = G.gpu_kv_write(shape, k, v, kp, vp, pt, cu, start)
+    ek, ev = kp.copy(), vp.copy()
+    for r in range(nreq):
+        for i in range(int(n[r])):
+            p = int(start[r]) + i
+            page = pt[r, p // 16]
+            ek[page, :, p % 16, :] = kw[cu[r] + i]
+            ev[page, :, :, p % 16] = vw[cu[r] + i]
+    bits = {"bf16": np.uint16, "fp32": np.uint32, "fp8": np.uint8}[dtype]
+    assert np.array_equal(gk.view(bits), ek.view(bits))
+    assert np.array_equal(gv.view(bits), ev.view(bits))
