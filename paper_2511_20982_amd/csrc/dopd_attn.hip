@@ -111,6 +111,16 @@ dopd_status scratch_address(void** ptr) {
 // ---- decode planning --------------------------------------------------------
 constexpr int kMaxGroupBf16 = 16;   // query heads per KV head handled by one decode wave
 
+// The decode's layout: the start of a segment takes a fixed time, so it counts
+// as more pairs where a pair is fewer bytes (measured, 8 / 12 / 16 / 20 units:
+// E4M3 d 128, 256 mixed contexts 234 / 228 / 229 / 233 us; E4M3 d 64, 100 mixed
+// contexts 63 / 58 / 56.5 / 58 us; bf16 d 64 and d 128 are best at 8).
+dopd::DecodeShape decode_shape(const dopd_attn_shape* s) {
+  dopd::DecodeShape ds;
+  if (s->dtype == DOPD_FP8_E4M3) ds.seg = s->head_dim == 64 ? 16 : 12;
+  return ds;
+}
+
 dopd_status check_decode_host(const dopd_attn_shape* s, const int32_t* ctx_host, int32_t n,
                               int32_t split) {
   dopd_status st = check_shape(s);
@@ -171,31 +181,31 @@ struct DecodeMergePlan {
 };
 
 // Decode arguments and workspace layout of the bf16-operand decode (bf16 or
-// E4M3 pools) after the host checks; quarter_wgs: resident decode workgroups
-// per CU, in quarters, the automatic partition plans for.
+// E4M3 pools) after the host checks.
 template <bool KV8>
 dopd_status plan_decode_bf16(const dopd_attn_shape* s, const void* q, const void* k_pool,
                              const void* v_pool, const float* k_scale, const float* v_scale,
                              const int32_t* pt, int32_t pt_stride, const int32_t* ctx,
                              const int32_t* ctx_host, int32_t nreq, int32_t split_tokens,
                              void* out, float* lse, void* workspace, size_t workspace_bytes,
-                             int quarter_wgs, dopd::DecodeArgs* a_out,
+                             const dopd::DecodeShape& ds, dopd::DecodeArgs* a_out,
                              DecodeMergePlan* merge_out) {
   const int hkv = s->num_kv_heads, hq = s->num_q_heads, d = s->head_dim;
-  const int64_t total = dopd::decode_total_units(ctx_host, nreq, hkv);
+  const int64_t total = dopd::decode_total_units(ctx_host, nreq, hkv, ds.seg);
   if (total > INT32_MAX / 2) return DOPD_ERR_INVALID_SHAPE;
   const dopd::DecodeLayout L = dopd::decode_layout(hq / hkv, hkv, d, ctx_host, nreq,
-                                                   split_tokens, machine_shape(), quarter_wgs);
+                                                   split_tokens, machine_shape(), ds);
   const int64_t nwg = L.nwg;
   if (!workspace) return DOPD_ERR_NULL_POINTER;
   if (workspace_bytes < L.total) return DOPD_ERR_WORKSPACE_TOO_SMALL;
   if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return DOPD_ERR_INVALID_SHAPE;
   char* ws = static_cast<char*>(workspace);
   merge_out->count = dopd::decode_merge_list(ctx_host, nreq, hkv, total, nwg,
-                                              merge_out->list.item, dopd::kMergeListMax);
+                                              merge_out->list.item, dopd::kMergeListMax, ds.seg);
   merge_out->list.n = std::max(0, merge_out->count);
   merge_out->needed = merge_out->count > 0 ||
-                      (merge_out->count < 0 && dopd::decode_needs_merge(ctx_host, nreq, hkv, total, nwg));
+                      (merge_out->count < 0 &&
+                       dopd::decode_needs_merge(ctx_host, nreq, hkv, total, nwg, ds.seg));
   dopd::DecodeArgs& a = *a_out;
   a.q = (const uint16_t*)q;
   a.k_pool = k_pool;
@@ -214,6 +224,7 @@ dopd_status plan_decode_bf16(const dopd_attn_shape* s, const void* q, const void
   a.hkv = hkv;
   a.total_units = (int)total;
   a.nwg = (int)nwg;
+  a.seg = ds.seg;
   a.scale_log2 = s->softmax_scale * dopd::kLog2e;
   return DOPD_OK;
 }
@@ -252,11 +263,20 @@ dopd_status launch_decode_bf16(const dopd_attn_shape* s, const void* q, const vo
                                hipStream_t strm) {
   dopd::DecodeArgs a;
   DecodeMergePlan merge;
+  const dopd::DecodeShape ds = decode_shape(s);
   const dopd_status pst = plan_decode_bf16<KV8>(s, q, k_pool, v_pool, k_scale, v_scale, pt,
                                                 pt_stride, ctx, ctx_host, nreq, split_tokens,
                                                 out, lse, workspace, workspace_bytes,
-                                                4 * dopd::kWgPerCu, &a, &merge);
+                                                ds, &a, &merge);
   if (pst != DOPD_OK) return pst;
+  if (dopd::decode_direct(ctx_host, nreq, s->num_kv_heads, split_tokens, machine_shape(), ds)) {
+    const dim3 grid((unsigned)(nreq * s->num_kv_heads)), block(64 * dopd::kDecDirectWaves);
+    if (s->head_dim == 64)
+      hipLaunchKernelGGL((dopd::decode_direct_kernel<64, KV8>), grid, block, 0, strm, a);
+    else
+      hipLaunchKernelGGL((dopd::decode_direct_kernel<128, KV8>), grid, block, 0, strm, a);
+    return launch_status();
+  }
   if (s->head_dim == 64)
     hipLaunchKernelGGL((dopd::decode_split_kernel<64, KV8>), dim3((unsigned)a.nwg), dim3(256), 0, strm, a);
   else
@@ -679,7 +699,7 @@ size_t dopd_decode_workspace_size(const dopd_attn_shape* s, const int32_t* ctx_h
   if (check_decode_host(s, ctx_host, n, split_tokens) != DOPD_OK) return 0;
   if (n == 0 || s->dtype == DOPD_FP32) return 256;
   return dopd::decode_layout(s->num_q_heads / s->num_kv_heads, s->num_kv_heads, s->head_dim,
-                             ctx_host, n, split_tokens, machine_shape())
+                             ctx_host, n, split_tokens, machine_shape(), decode_shape(s))
       .total;
 }
 
@@ -742,7 +762,7 @@ dopd_status dopd_decode_attn_noalloc(const dopd_attn_shape* s, const void* q,
   size_t need = 0;
   if (s->dtype == DOPD_BF16)
     need = dopd::decode_layout(s->num_q_heads / s->num_kv_heads, s->num_kv_heads, s->head_dim,
-                               ctx_host, nreq, split_tokens, machine_shape())
+                               ctx_host, nreq, split_tokens, machine_shape(), decode_shape(s))
                .total;
   if (need > DOPD_DECODE_NOALLOC_SCRATCH_BYTES) return DOPD_ERR_WORKSPACE_TOO_SMALL;
   void* ws = nullptr;
@@ -835,14 +855,16 @@ namespace {
 constexpr int kPdLastSchedule = DOPD_PD_DECODE_FIRST_WIDE;
 constexpr int kPdAutoSchedule = DOPD_PD_PREFILL_FIRST;
 
-// Decode workgroups per CU (in quarters) of a fused-step schedule.
-int pd_decode_quarters(int schedule) {
+// The decode's layout in a fused-step schedule.
+dopd::DecodeShape pd_decode_shape(const dopd_attn_shape* s, int schedule) {
+  dopd::DecodeShape ds = decode_shape(s);
   if (schedule == DOPD_PD_AUTO) schedule = kPdAutoSchedule;
   switch (schedule) {
-    case DOPD_PD_DECODE_FIRST: return 4;       // one per CU
-    case DOPD_PD_DECODE_FIRST_WIDE: return 6;  // three per two CUs
-    default: return 4 * dopd::kWgPerCu;        // every slot
+    case DOPD_PD_DECODE_FIRST: ds.quarter_wgs = 4; break;       // one per CU
+    case DOPD_PD_DECODE_FIRST_WIDE: ds.quarter_wgs = 6; break;  // three per two CUs
+    default: ds.quarter_wgs = 4 * dopd::kWgPerCu;               // every slot (of the step's kernel)
   }
+  return ds;
 }
 }  // namespace
 }  // extern "C++"
@@ -855,7 +877,7 @@ size_t dopd_pd_step_workspace_size(const dopd_attn_shape* s, const int32_t* ctx_
     return 0;
   if (num_dec == 0) return 256;
   return dopd::decode_layout(s->num_q_heads / s->num_kv_heads, s->num_kv_heads, s->head_dim,
-                             ctx_host, num_dec, 0, machine_shape(), pd_decode_quarters(schedule))
+                             ctx_host, num_dec, 0, machine_shape(), pd_decode_shape(s, schedule))
       .total;
 }
 
@@ -900,11 +922,11 @@ static dopd_status pd_step_impl(const dopd_attn_shape* s, const void* q_dec,
   if (num_dec > 0) {
     st = kv8 ? plan_decode_bf16<true>(s, q_dec, k_pool, v_pool, k_scale, v_scale, dec_page_table,
                                       pt_stride, ctx, ctx_host, num_dec, 0, out_dec, lse_dec,
-                                      workspace, workspace_bytes, pd_decode_quarters(schedule),
+                                      workspace, workspace_bytes, pd_decode_shape(s, schedule),
                                       &p.dec, &merge)
              : plan_decode_bf16<false>(s, q_dec, k_pool, v_pool, nullptr, nullptr, dec_page_table,
                                        pt_stride, ctx, ctx_host, num_dec, 0, out_dec, lse_dec,
-                                       workspace, workspace_bytes, pd_decode_quarters(schedule),
+                                       workspace, workspace_bytes, pd_decode_shape(s, schedule),
                                        &p.dec, &merge);
     if (st != DOPD_OK) return st;
     p.n_dec = p.dec.nwg;

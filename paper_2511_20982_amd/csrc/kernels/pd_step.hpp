@@ -41,8 +41,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void pd_step_kernel(PdStepArgs s) {
   __shared__ __attribute__((aligned(16))) uint16_t sK0[pf_tile_elems<D>()], sK1[pf_tile_elems<D>()];
   __shared__ __attribute__((aligned(16))) uint16_t sV0[pf_tile_elems<D>()], sV1[pf_tile_elems<D>()];
   __shared__ __attribute__((aligned(16))) uint16_t sQ[pf_q_lds_elems<D>()];
-  static_assert(2 * dec_wave_o_bytes<D>() <= (int)sizeof(sK0) &&
-                    dec_wave_o_bytes<D>() <= (int)sizeof(sK1) && kDecMlBytes <= (int)sizeof(sQ),
+  static_assert(2 * dec_wave_o_bytes<D>() <= (int)sizeof(sK0) && kDecWaves == 4 &&
+                    dec_ml_bytes<kDecWaves>() <= (int)sizeof(sQ),
                 "decode merge buffers fit the prefill tiles");
   using PoolT = std::conditional_t<KV8, uint8_t, uint16_t>;
   static_assert(PageWrite<uint16_t, PoolT, D>::kLdsBytes <= (int)sizeof(sV0) && kPfThreads == 64 * kKvwWaves,
@@ -52,10 +52,9 @@ __global__ __launch_bounds__(kPfThreads, 2) void pd_step_kernel(PdStepArgs s) {
     prefill_workgroup<D, false>(s.pf, b - s.pf_first, sK0, sK1, sV0, sV1, sQ);
   } else if (b >= s.dec_first && b < s.dec_first + s.n_dec) {
     constexpr int kWaveElems = dec_wave_o_bytes<D>() / 2;  // bf16 elements of one block
-    decode_workgroup<D, KV8>(s.dec, b - s.dec_first, reinterpret_cast<float*>(sQ),
-                               reinterpret_cast<f32x4*>(sK0),
-                               reinterpret_cast<f32x4*>(sK0 + kWaveElems),
-                               reinterpret_cast<f32x4*>(sK1));
+    decode_workgroup<D, KV8>(s.dec, b - s.dec_first, reinterpret_cast<float*>(sQ), [&](int i) {
+      return reinterpret_cast<f32x4*>((i < 2 ? sK0 : sK1) + i % 2 * kWaveElems);
+    });
   } else if (b >= s.wp_first && b < s.wp_first + s.n_wp) {
     const int w = threadIdx.x >> 6;
     uint16_t* rows = w == 0 ? sK0 : w == 1 ? sK1 : w == 2 ? sV0 : sV1;

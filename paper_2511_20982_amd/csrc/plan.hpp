@@ -26,25 +26,32 @@ constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // ---- decode partition ------------------------------------------------------
 // The keys of every (request r, KV head c) are cut into pairs of pages (32
-// tokens); (r, c) is a span of kDecSegCost + pairs work units, spans laid out
-// r-major then c; workgroup b takes units [b * total / nwg, (b+1) * total / nwg).
-constexpr int kDecSegCost = 8;          // work units of a segment start, in pairs
+// tokens); (r, c) is a span of seg + pairs work units, spans laid out r-major
+// then c; workgroup b takes units [b * total / nwg, (b+1) * total / nwg).
+constexpr int kDecSegCost = 8;          // work units of a segment start, in bf16 pairs
 constexpr int kDecMaxSplitTokens = 4096;
 constexpr int64_t kDecMinPairsPerWg = 4;  // one pair per wave at least
+
+// How the decode of one kind of pool is laid on the machine: seg, the work
+// units a segment start counts, and the resident workgroups per CU, in
+// quarters, that the automatic partition fills.
+struct DecodeShape {
+  int seg = kDecSegCost;
+  int quarter_wgs = 4 * kWgPerCu;
+};
 
 constexpr int64_t dec_slice_begin(int64_t b, int64_t total, int64_t nwg) {
   return b * total / nwg;
 }
 
-inline int64_t decode_total_units(const int32_t* ctx, int32_t n, int hkv) {
+inline int64_t decode_total_units(const int32_t* ctx, int32_t n, int hkv, int seg = kDecSegCost) {
   int64_t units = 0;
-  for (int32_t r = 0; r < n; ++r) units += (int64_t)(kDecSegCost + (ctx[r] + 31) / 32) * hkv;
+  for (int32_t r = 0; r < n; ++r) units += (int64_t)(seg + (ctx[r] + 31) / 32) * hkv;
   return units;
 }
 
 // Resident decode workgroup slots the automatic partition fills: quarter_wgs / 4
-// workgroups per CU (8 = two per CU, every slot; fewer leaves slots to the
-// prefill items of a fused step).
+// workgroups per CU.
 inline int64_t decode_slots(const MachineShape& m, int quarter_wgs = 4 * kWgPerCu) {
   return std::max<int64_t>(1, (int64_t)std::max(1, m.cus) * std::max(1, quarter_wgs) / 4);
 }
@@ -63,6 +70,26 @@ inline int64_t decode_nwg(int64_t total_units, int32_t split_tokens, const Machi
                                                   kDecMinPairsPerWg));
 }
 
+// Does a call with the automatic partition run one workgroup of
+// kDecDirectWaves waves per whole (r, c) instead (no partials, no second
+// kernel)?  Steps are pairs one wave takes one after the other, about 2.2 us
+// each in a light call; the partition's merge costs about two of them.  More
+// (r, c) than CUs would take turns.  Measured, partition / direct, 8 KV heads:
+// 16 requests of 500 tokens 15.7 / 11.6 us, 32 of 500 21.4 / 14.8, 32 of 2000
+// 56 / 48, 4 of 1000 15.2 / 15.6, 16 of 2000 33.6 / 35.5, 1 of 2000 11.4 / 22.9.
+constexpr int kDecDirectWaves = 8;
+inline bool decode_direct(const int32_t* ctx, int32_t n, int hkv, int32_t split_tokens,
+                          const MachineShape& m, const DecodeShape& ds) {
+  if (split_tokens > 0 || (int64_t)n * hkv > std::max(1, m.cus)) return false;
+  int32_t most = 0;
+  for (int32_t r = 0; r < n; ++r) most = std::max(most, ctx[r]);
+  const int64_t direct = ((most + 31) / 32 + kDecDirectWaves - 1) / kDecDirectWaves;
+  const int64_t total = decode_total_units(ctx, n, hkv, ds.seg);
+  const int64_t nwg = decode_nwg(total, 0, m, ds.quarter_wgs);
+  const int64_t split = (total + 4 * nwg - 1) / (4 * nwg);  // (a partition workgroup has 4 waves)
+  return direct <= split + (split > 1 ? 1 : 0);
+}
+
 // Workspace of the decode: partial slots, at most one per (workgroup, (r, c))
 // boundary, indexed workgroup + (r * Hkv + c); [slots][g][d] fp32 partial
 // outputs, then [slots][g][2] (m, l), each 256-byte aligned.
@@ -73,9 +100,9 @@ struct DecodeLayout {
 
 inline DecodeLayout decode_layout(int g, int hkv, int d, const int32_t* ctx, int32_t n,
                                   int32_t split_tokens, const MachineShape& m,
-                                  int quarter_wgs = 4 * kWgPerCu) {
+                                  const DecodeShape& ds = DecodeShape{}) {
   DecodeLayout L{};
-  L.nwg = decode_nwg(decode_total_units(ctx, n, hkv), split_tokens, m, quarter_wgs);
+  L.nwg = decode_nwg(decode_total_units(ctx, n, hkv, ds.seg), split_tokens, m, ds.quarter_wgs);
   L.slots = L.nwg + (int64_t)n * hkv;
   L.part_o_off = 0;
   L.part_ml_off = align256((size_t)L.slots * g * d * sizeof(float));
@@ -93,12 +120,12 @@ inline int64_t dec_slice_of(int64_t x, int64_t total, int64_t nwg) {
 
 // Does any (r, c) span two slices (then the merge kernel runs)?
 inline bool decode_needs_merge(const int32_t* ctx, int32_t n, int hkv, int64_t total,
-                               int64_t nwg) {
+                               int64_t nwg, int seg = kDecSegCost) {
   int64_t base = 0;
   for (int32_t r = 0; r < n; ++r) {
-    const int64_t np = (ctx[r] + 31) / 32, span = kDecSegCost + np;
+    const int64_t np = (ctx[r] + 31) / 32, span = seg + np;
     for (int c = 0; c < hkv; ++c) {
-      const int64_t first = base + c * span + kDecSegCost;  // unit of the first pair
+      const int64_t first = base + c * span + seg;  // unit of the first pair
       if (dec_slice_of(first, total, nwg) != dec_slice_of(first + np - 1, total, nwg))
         return true;
     }
@@ -117,14 +144,14 @@ inline bool decode_needs_merge(const int32_t* ctx, int32_t n, int hkv, int64_t t
 constexpr int kMergeRcBits = 14, kMergeB0Bits = 10;
 
 inline int decode_merge_list(const int32_t* ctx, int32_t n, int hkv, int64_t total, int64_t nwg,
-                             uint32_t* items, int max) {
+                             uint32_t* items, int max, int seg = kDecSegCost) {
   if ((int64_t)n * hkv > (1 << kMergeRcBits) || nwg > (1 << kMergeB0Bits)) return -1;
   int cnt = 0;
   int64_t base = 0;
   for (int32_t r = 0; r < n; ++r) {
-    const int64_t np = (ctx[r] + 31) / 32, span = kDecSegCost + np;
+    const int64_t np = (ctx[r] + 31) / 32, span = seg + np;
     for (int c = 0; c < hkv; ++c) {
-      const int64_t first = base + c * span + kDecSegCost;  // unit of the first pair
+      const int64_t first = base + c * span + seg;  // unit of the first pair
       const int64_t b0 = dec_slice_of(first, total, nwg), b1 = dec_slice_of(first + np - 1, total, nwg);
       if (b0 == b1) continue;
       if (cnt == max || b1 - b0 > 255) return -1;
