@@ -2,7 +2,9 @@
 
 Argument marshalling only: every entry point takes torch tensors (device
 memory) or numpy arrays (the ``_host`` copies), passes raw pointers to the
-library, and raises :class:`DopdError` on a non-OK status.  All compute runs
+library, and raises :class:`DopdError` on a non-OK status.  The launching
+calls go through ``_marshal.so`` (``csrc/marshal.cpp``), which converts their
+arguments natively.  All compute runs
 in the library's HIP kernels on the given (default: current) HIP stream.
 The library is loaded on first use; if it has not been built, the call fails
 loudly -- there is no fallback path.
@@ -120,8 +122,28 @@ def lib():
                   "dopd_validate_page_table_host", "dopd_kv_write_pack_for_handoff",
                   "dopd_pd_step", "dopd_pd_step_fp8"):
             getattr(L, f).restype = i32
+        _bind(L)
         _LIB = L
     return _LIB
+
+
+_CALLS = None  # the _marshal module, bound to the loaded library
+
+
+def _bind(L):
+    """Points _marshal's entry points at the library's."""
+    global _CALLS
+    from paper_2511_20982_amd import _marshal
+    for f in dir(_marshal):
+        if f.startswith("dopd_"):
+            _marshal.bind(f, C.cast(getattr(L, f), C.c_void_p).value)
+    _CALLS = _marshal
+
+
+def _calls():
+    if _LIB is None:
+        lib()
+    return _CALLS
 
 
 def status_string(status: int) -> str:
@@ -129,11 +151,6 @@ def status_string(status: int) -> str:
 
 
 # ------------------------------------------------------------------ marshalling
-def _dptr(t):
-    """Device pointer of a tensor (None -> NULL)."""
-    return None if t is None else C.c_void_p(t.data_ptr())
-
-
 def _hptr(a):
     """Host pointer of a contiguous int32/int64 numpy array (None -> NULL)."""
     return None if a is None else a.ctypes.data_as(C.c_void_p)
@@ -143,11 +160,35 @@ def _host_i32(a):
     return None if a is None else np.ascontiguousarray(a, dtype=np.int32)
 
 
+_CURRENT_STREAM = None  # () -> address of the current device's current stream
+
+
+def _find_current_stream():
+    """torch.cuda.current_stream().cuda_stream without the Stream object it
+    makes (2.7 us of a call's host time), where torch offers it."""
+    global _CURRENT_STREAM
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        _CURRENT_STREAM = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+    else:
+        device = torch.cuda.current_device
+        _CURRENT_STREAM = lambda: raw(device())  # noqa: E731
+    return _CURRENT_STREAM
+
+
 def _stream(stream):
+    """Address of the HIP stream (None: the current one)."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        return (_CURRENT_STREAM or _find_current_stream())()
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _nbytes(workspace, workspace_bytes):
+    """workspace_bytes, or the workspace tensor's size."""
+    if workspace_bytes is not None:
+        return int(workspace_bytes)
+    return 0 if workspace is None else workspace.numel() * workspace.element_size()
 
 
 def _check(status: int, where: str):
@@ -159,12 +200,10 @@ def _check(status: int, where: str):
 def dopd_prefill_attn(shape, q, k, v, out, lse, cu_seqlens, cu_seqlens_host, num_reqs,
                       workspace=None, workspace_bytes=None, stream=None):
     cu_h = _host_i32(cu_seqlens_host)
-    if workspace_bytes is None:
-        workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().dopd_prefill_attn(C.byref(shape), _dptr(q), _dptr(k), _dptr(v), _dptr(out),
-                                   _dptr(lse), _dptr(cu_seqlens), _hptr(cu_h), int(num_reqs),
-                                   _dptr(workspace), int(workspace_bytes), _stream(stream)),
-           "dopd_prefill_attn")
+    _check(_calls().dopd_prefill_attn(
+        shape, q, k, v, out, lse, cu_seqlens, cu_h, num_reqs, workspace, _nbytes(workspace,
+        workspace_bytes), _stream(stream)),
+        "dopd_prefill_attn")
 
 
 def dopd_prefill_workspace_size(shape, cu_seqlens_host, num_reqs) -> int:
@@ -177,11 +216,10 @@ def dopd_prefill_paged_attn(shape, q, k_pool, v_pool, num_pages, page_table, pag
                             out, lse, stream=None):
     cu_h = _host_i32(cu_seqlens_host)
     pre_h = _host_i32(prefix_lens_host)
-    _check(lib().dopd_prefill_paged_attn(C.byref(shape), _dptr(q), _dptr(k_pool), _dptr(v_pool),
-                                         int(num_pages), _dptr(page_table), int(page_table_stride),
-                                         _dptr(cu_seqlens), _hptr(cu_h), _dptr(prefix_lens),
-                                         _hptr(pre_h), int(num_reqs), _dptr(out), _dptr(lse),
-                                         _stream(stream)), "dopd_prefill_paged_attn")
+    _check(_calls().dopd_prefill_paged_attn(
+        shape, q, k_pool, v_pool, num_pages, page_table, page_table_stride, cu_seqlens, cu_h,
+        prefix_lens, pre_h, num_reqs, out, lse, _stream(stream)),
+        "dopd_prefill_paged_attn")
 
 
 def dopd_prefill_paged_workspace_size(shape, cu_seqlens_host, prefix_lens_host, num_reqs,
@@ -198,13 +236,11 @@ def dopd_prefill_paged_attn_split(shape, q, k_pool, v_pool, num_pages, page_tabl
                                   workspace_bytes=None, stream=None):
     cu_h = _host_i32(cu_seqlens_host)
     pre_h = _host_i32(prefix_lens_host)
-    if workspace_bytes is None:
-        workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().dopd_prefill_paged_attn_split(
-        C.byref(shape), _dptr(q), _dptr(k_pool), _dptr(v_pool), int(num_pages),
-        _dptr(page_table), int(page_table_stride), _dptr(cu_seqlens), _hptr(cu_h),
-        _dptr(prefix_lens), _hptr(pre_h), int(num_reqs), int(num_splits), _dptr(out), _dptr(lse),
-        _dptr(workspace), int(workspace_bytes), _stream(stream)), "dopd_prefill_paged_attn_split")
+    _check(_calls().dopd_prefill_paged_attn_split(
+        shape, q, k_pool, v_pool, num_pages, page_table, page_table_stride, cu_seqlens, cu_h,
+        prefix_lens, pre_h, num_reqs, num_splits, out, lse, workspace, _nbytes(workspace,
+        workspace_bytes), _stream(stream)),
+        "dopd_prefill_paged_attn_split")
 
 
 def dopd_prefill_paged_fp8_workspace_size(shape, cu_seqlens_host, prefix_lens_host, num_reqs,
@@ -221,34 +257,29 @@ def dopd_prefill_paged_attn_fp8(shape, q, k_pool, v_pool, k_scale, v_scale, num_
                                 workspace, workspace_bytes=None, stream=None):
     cu_h = _host_i32(cu_seqlens_host)
     pre_h = _host_i32(prefix_lens_host)
-    if workspace_bytes is None:
-        workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().dopd_prefill_paged_attn_fp8(
-        C.byref(shape), _dptr(q), _dptr(k_pool), _dptr(v_pool), _dptr(k_scale), _dptr(v_scale),
-        int(num_pages), _dptr(page_table), int(page_table_stride), _dptr(cu_seqlens),
-        _hptr(cu_h), _dptr(prefix_lens), _hptr(pre_h), int(num_reqs), int(num_splits),
-        _dptr(out), _dptr(lse), _dptr(workspace), int(workspace_bytes), _stream(stream)),
+    _check(_calls().dopd_prefill_paged_attn_fp8(
+        shape, q, k_pool, v_pool, k_scale, v_scale, num_pages, page_table, page_table_stride,
+        cu_seqlens, cu_h, prefix_lens, pre_h, num_reqs, num_splits, out, lse, workspace,
+        _nbytes(workspace, workspace_bytes), _stream(stream)),
         "dopd_prefill_paged_attn_fp8")
 
 
 def dopd_kv_write(shape, k_new, v_new, k_pool, v_pool, num_pages, page_table,
                   page_table_stride, cu_new_tokens, start_pos, num_reqs, total_new_tokens,
                   stream=None):
-    _check(lib().dopd_kv_write(C.byref(shape), _dptr(k_new), _dptr(v_new), _dptr(k_pool),
-                               _dptr(v_pool), int(num_pages), _dptr(page_table),
-                               int(page_table_stride), _dptr(cu_new_tokens), _dptr(start_pos),
-                               int(num_reqs), int(total_new_tokens), _stream(stream)),
-           "dopd_kv_write")
+    _check(_calls().dopd_kv_write(
+        shape, k_new, v_new, k_pool, v_pool, num_pages, page_table, page_table_stride,
+        cu_new_tokens, start_pos, num_reqs, total_new_tokens, _stream(stream)),
+        "dopd_kv_write")
 
 
 def dopd_kv_write_fp8(shape, k_new, v_new, k_scale, v_scale, k_pool, v_pool, num_pages,
                       page_table, page_table_stride, cu_new_tokens, start_pos, num_reqs,
                       total_new_tokens, stream=None):
-    _check(lib().dopd_kv_write_fp8(C.byref(shape), _dptr(k_new), _dptr(v_new), _dptr(k_scale),
-                                   _dptr(v_scale), _dptr(k_pool), _dptr(v_pool), int(num_pages),
-                                   _dptr(page_table), int(page_table_stride),
-                                   _dptr(cu_new_tokens), _dptr(start_pos), int(num_reqs),
-                                   int(total_new_tokens), _stream(stream)), "dopd_kv_write_fp8")
+    _check(_calls().dopd_kv_write_fp8(
+        shape, k_new, v_new, k_scale, v_scale, k_pool, v_pool, num_pages, page_table,
+        page_table_stride, cu_new_tokens, start_pos, num_reqs, total_new_tokens, _stream(stream)),
+        "dopd_kv_write_fp8")
 
 
 def dopd_decode_workspace_size(shape, context_lens_host, num_reqs, split_tokens=0) -> int:
@@ -261,13 +292,11 @@ def dopd_decode_attn(shape, q, k_pool, v_pool, num_pages, page_table, page_table
                      context_lens, context_lens_host, num_reqs, split_tokens, out, lse,
                      workspace, workspace_bytes=None, stream=None):
     ctx = _host_i32(context_lens_host)
-    if workspace_bytes is None:
-        workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().dopd_decode_attn(C.byref(shape), _dptr(q), _dptr(k_pool), _dptr(v_pool),
-                                  int(num_pages), _dptr(page_table), int(page_table_stride),
-                                  _dptr(context_lens), _hptr(ctx), int(num_reqs),
-                                  int(split_tokens), _dptr(out), _dptr(lse), _dptr(workspace),
-                                  int(workspace_bytes), _stream(stream)), "dopd_decode_attn")
+    _check(_calls().dopd_decode_attn(
+        shape, q, k_pool, v_pool, num_pages, page_table, page_table_stride, context_lens, ctx,
+        num_reqs, split_tokens, out, lse, workspace, _nbytes(workspace, workspace_bytes),
+        _stream(stream)),
+        "dopd_decode_attn")
 
 
 DECODE_NOALLOC_SCRATCH_BYTES = 32 << 20
@@ -277,61 +306,50 @@ def dopd_decode_attn_noalloc(shape, q, k_pool, v_pool, num_pages, page_table, pa
                              context_lens, context_lens_host, num_reqs, split_tokens, out, lse,
                              stream=None):
     ctx = _host_i32(context_lens_host)
-    _check(lib().dopd_decode_attn_noalloc(C.byref(shape), _dptr(q), _dptr(k_pool), _dptr(v_pool),
-                                          int(num_pages), _dptr(page_table),
-                                          int(page_table_stride), _dptr(context_lens),
-                                          _hptr(ctx), int(num_reqs), int(split_tokens),
-                                          _dptr(out), _dptr(lse), _stream(stream)),
-           "dopd_decode_attn_noalloc")
+    _check(_calls().dopd_decode_attn_noalloc(
+        shape, q, k_pool, v_pool, num_pages, page_table, page_table_stride, context_lens, ctx,
+        num_reqs, split_tokens, out, lse, _stream(stream)),
+        "dopd_decode_attn_noalloc")
 
 
 def dopd_decode_attn_fp8(shape, q, k_pool, v_pool, k_scale, v_scale, num_pages, page_table,
                          page_table_stride, context_lens, context_lens_host, num_reqs,
                          split_tokens, out, lse, workspace, workspace_bytes=None, stream=None):
     ctx = _host_i32(context_lens_host)
-    if workspace_bytes is None:
-        workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().dopd_decode_attn_fp8(C.byref(shape), _dptr(q), _dptr(k_pool), _dptr(v_pool),
-                                      _dptr(k_scale), _dptr(v_scale), int(num_pages),
-                                      _dptr(page_table), int(page_table_stride),
-                                      _dptr(context_lens), _hptr(ctx), int(num_reqs),
-                                      int(split_tokens), _dptr(out), _dptr(lse),
-                                      _dptr(workspace), int(workspace_bytes), _stream(stream)),
-           "dopd_decode_attn_fp8")
+    _check(_calls().dopd_decode_attn_fp8(
+        shape, q, k_pool, v_pool, k_scale, v_scale, num_pages, page_table, page_table_stride,
+        context_lens, ctx, num_reqs, split_tokens, out, lse, workspace, _nbytes(workspace,
+        workspace_bytes), _stream(stream)),
+        "dopd_decode_attn_fp8")
 
 
 def dopd_kv_pack_for_handoff(shape, num_layers, k_pool, v_pool, num_pages, page_table,
                              page_table_stride, req_ids, seq_lens, seq_lens_host, out_offsets,
                              num_handoff, out, stream=None):
     lens_h = _host_i32(seq_lens_host)
-    _check(lib().dopd_kv_pack_for_handoff(C.byref(shape), int(num_layers), _dptr(k_pool),
-                                          _dptr(v_pool), int(num_pages), _dptr(page_table),
-                                          int(page_table_stride), _dptr(req_ids),
-                                          _dptr(seq_lens), _hptr(lens_h), _dptr(out_offsets),
-                                          int(num_handoff), _dptr(out), _stream(stream)),
-           "dopd_kv_pack_for_handoff")
+    _check(_calls().dopd_kv_pack_for_handoff(
+        shape, num_layers, k_pool, v_pool, num_pages, page_table, page_table_stride, req_ids,
+        seq_lens, lens_h, out_offsets, num_handoff, out, _stream(stream)),
+        "dopd_kv_pack_for_handoff")
 
 
 def dopd_kv_unpack_from_handoff(shape, num_layers, buf, in_offsets, req_ids, seq_lens,
                                 seq_lens_host, num_handoff, k_pool, v_pool, num_pages, page_table,
                                 page_table_stride, stream=None):
     lens_h = _host_i32(seq_lens_host)
-    _check(lib().dopd_kv_unpack_from_handoff(C.byref(shape), int(num_layers), _dptr(buf),
-                                             _dptr(in_offsets), _dptr(req_ids), _dptr(seq_lens),
-                                             _hptr(lens_h), int(num_handoff), _dptr(k_pool),
-                                             _dptr(v_pool), int(num_pages), _dptr(page_table),
-                                             int(page_table_stride), _stream(stream)),
-           "dopd_kv_unpack_from_handoff")
+    _check(_calls().dopd_kv_unpack_from_handoff(
+        shape, num_layers, buf, in_offsets, req_ids, seq_lens, lens_h, num_handoff, k_pool, v_pool,
+        num_pages, page_table, page_table_stride, _stream(stream)),
+        "dopd_kv_unpack_from_handoff")
 
 
 def dopd_kv_write_pack_for_handoff(shape, k_new, v_new, k_pool, v_pool, num_pages, page_table,
                                    page_table_stride, cu_seqlens, cu_seqlens_host, num_reqs,
                                    out_offsets, out, stream=None):
     cu_h = _host_i32(cu_seqlens_host)
-    _check(lib().dopd_kv_write_pack_for_handoff(
-        C.byref(shape), _dptr(k_new), _dptr(v_new), _dptr(k_pool), _dptr(v_pool), int(num_pages),
-        _dptr(page_table), int(page_table_stride), _dptr(cu_seqlens), _hptr(cu_h),
-        int(num_reqs), _dptr(out_offsets), _dptr(out), _stream(stream)),
+    _check(_calls().dopd_kv_write_pack_for_handoff(
+        shape, k_new, v_new, k_pool, v_pool, num_pages, page_table, page_table_stride, cu_seqlens,
+        cu_h, num_reqs, out_offsets, out, _stream(stream)),
         "dopd_kv_write_pack_for_handoff")
 
 
@@ -348,15 +366,12 @@ def dopd_pd_step(shape, q_dec, dec_page_table, context_lens, context_lens_host, 
                  stream=None):
     ctx = _host_i32(context_lens_host)
     cu_h = _host_i32(cu_seqlens_host)
-    if workspace_bytes is None:
-        workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().dopd_pd_step(
-        C.byref(shape), _dptr(q_dec), _dptr(dec_page_table), _dptr(context_lens), _hptr(ctx),
-        int(num_dec), _dptr(out_dec), _dptr(lse_dec), _dptr(q), _dptr(k), _dptr(v),
-        _dptr(cu_seqlens), _hptr(cu_h), int(num_pre), _dptr(pre_page_table), _dptr(out_pre),
-        _dptr(lse_pre), _dptr(k_pool), _dptr(v_pool), int(num_pages), int(page_table_stride),
-        _dptr(handoff_offsets), _dptr(handoff_out), int(schedule), _dptr(workspace),
-        int(workspace_bytes), _stream(stream)), "dopd_pd_step")
+    _check(_calls().dopd_pd_step(
+        shape, q_dec, dec_page_table, context_lens, ctx, num_dec, out_dec, lse_dec, q, k, v,
+        cu_seqlens, cu_h, num_pre, pre_page_table, out_pre, lse_pre, k_pool, v_pool, num_pages,
+        page_table_stride, handoff_offsets, handoff_out, schedule, workspace, _nbytes(workspace,
+        workspace_bytes), _stream(stream)),
+        "dopd_pd_step")
 
 
 def dopd_pd_step_fp8(shape, q_dec, dec_page_table, context_lens, context_lens_host, num_dec,
@@ -366,15 +381,11 @@ def dopd_pd_step_fp8(shape, q_dec, dec_page_table, context_lens, context_lens_ho
                      workspace, workspace_bytes=None, stream=None):
     ctx = _host_i32(context_lens_host)
     cu_h = _host_i32(cu_seqlens_host)
-    if workspace_bytes is None:
-        workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().dopd_pd_step_fp8(
-        C.byref(shape), _dptr(q_dec), _dptr(dec_page_table), _dptr(context_lens), _hptr(ctx),
-        int(num_dec), _dptr(out_dec), _dptr(lse_dec), _dptr(q), _dptr(k), _dptr(v),
-        _dptr(cu_seqlens), _hptr(cu_h), int(num_pre), _dptr(pre_page_table), _dptr(out_pre),
-        _dptr(lse_pre), _dptr(k_pool), _dptr(v_pool), _dptr(k_scale), _dptr(v_scale),
-        int(num_pages), int(page_table_stride), _dptr(handoff_offsets), _dptr(handoff_out),
-        int(schedule), _dptr(workspace), int(workspace_bytes), _stream(stream)),
+    _check(_calls().dopd_pd_step_fp8(
+        shape, q_dec, dec_page_table, context_lens, ctx, num_dec, out_dec, lse_dec, q, k, v,
+        cu_seqlens, cu_h, num_pre, pre_page_table, out_pre, lse_pre, k_pool, v_pool, k_scale,
+        v_scale, num_pages, page_table_stride, handoff_offsets, handoff_out, schedule, workspace,
+        _nbytes(workspace, workspace_bytes), _stream(stream)),
         "dopd_pd_step_fp8")
 
 

@@ -1,12 +1,16 @@
-"""Builds libdopd_attn.so (all HIP kernels + the C ABI) for gfx950, in-tree."""
+"""Builds libdopd_attn.so (all HIP kernels + the C ABI) for gfx950 and the
+binding's argument marshalling (_marshal.so, host only), in-tree."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SRC = os.path.join(HERE, "csrc", "dopd_attn.hip")
 LIB = os.path.join(HERE, "libdopd_attn.so")
+MARSHAL_SRC = os.path.join(HERE, "csrc", "marshal.cpp")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -30,7 +34,23 @@ def build(verbose: bool = False, extra=()) -> str:
     if verbose and err.strip():
         print(err, file=sys.stderr)
     os.replace(LIB + ".tmp", LIB)
+    build_marshal(verbose)
     return LIB
+
+
+def build_marshal(verbose: bool = False) -> str:
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
+           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"], MARSHAL_SRC,
+           "-o", MARSHAL + ".tmp"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed ({res.returncode}):\n{res.stderr}")
+    if verbose and res.stderr.strip():
+        print(res.stderr, file=sys.stderr)
+    os.replace(MARSHAL + ".tmp", MARSHAL)
+    return MARSHAL
 
 
 if __name__ == "__main__":

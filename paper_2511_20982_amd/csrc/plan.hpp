@@ -85,7 +85,7 @@ inline bool decode_direct(const int32_t* ctx, int32_t n, int hkv, int32_t split_
   for (int32_t r = 0; r < n; ++r) most = std::max(most, ctx[r]);
   const int64_t direct = ((most + 31) / 32 + kDecDirectWaves - 1) / kDecDirectWaves;
   const int64_t total = decode_total_units(ctx, n, hkv, ds.seg);
-  const int64_t nwg = decode_nwg(total, 0, m, ds.quarter_wgs);
+  const int64_t nwg = decode_nwg(decode_total_units(ctx, n, hkv), 0, m, ds.quarter_wgs);
   const int64_t split = (total + 4 * nwg - 1) / (4 * nwg);  // (a partition workgroup has 4 waves)
   return direct <= split + (split > 1 ? 1 : 0);
 }
@@ -102,7 +102,8 @@ inline DecodeLayout decode_layout(int g, int hkv, int d, const int32_t* ctx, int
                                   int32_t split_tokens, const MachineShape& m,
                                   const DecodeShape& ds = DecodeShape{}) {
   DecodeLayout L{};
-  L.nwg = decode_nwg(decode_total_units(ctx, n, hkv, ds.seg), split_tokens, m, ds.quarter_wgs);
+  // (the count of workgroups, and so the workspace, is that of bf16 pools)
+  L.nwg = decode_nwg(decode_total_units(ctx, n, hkv), split_tokens, m, ds.quarter_wgs);
   L.slots = L.nwg + (int64_t)n * hkv;
   L.part_o_off = 0;
   L.part_ml_off = align256((size_t)L.slots * g * d * sizeof(float));
