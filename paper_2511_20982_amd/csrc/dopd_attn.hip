@@ -1099,38 +1099,41 @@ dopd_status dopd_kv_unpack_from_handoff(const dopd_attn_shape* s, int32_t num_la
   if (max_len == 0) return DOPD_OK;
   const int64_t zdim = (int64_t)num_layers * 2 * s->num_kv_heads;
   if (zdim > 65535 || num_handoff > 65535) return DOPD_ERR_INVALID_SHAPE;
-  dim3 grid((unsigned)((max_len + dopd::kPage - 1) / dopd::kPage), (unsigned)num_handoff,
-            (unsigned)zdim);
   hipStream_t strm = as_stream(stream);
   const int hkv = s->num_kv_heads;
   if (s->dtype == DOPD_FP8_E4M3) {
-    auto* src = (const uint8_t*)in;
-    auto* kp = (uint8_t*)k_pool; auto* vp = (uint8_t*)v_pool;
+    int64_t pages = 0;
+    for (int32_t n = 0; n < num_handoff; ++n) pages += (seq_lens_host[n] + dopd::kPage - 1) / dopd::kPage;
+    const int groups = write_head_groups<uint8_t, uint8_t>(hkv, s->head_dim);
+    const int64_t blocks = pages * num_layers * groups;
+    if (blocks > INT32_MAX) return DOPD_ERR_INVALID_SHAPE;
+    const dopd::UnpackPagesArgs a{(const uint8_t*)in, in_offsets, req_ids, seq_lens, (uint8_t*)k_pool,
+                                  (uint8_t*)v_pool, pt, num_pages, pt_stride, hkv, num_handoff,
+                                  num_layers, groups};
+    const dim3 grid((unsigned)blocks), block(64 * dopd::kKvwWaves);
     if (s->head_dim == 64)
-      hipLaunchKernelGGL((dopd::kv_unpack_kernel<uint8_t, 64>), grid, dim3(256), 0, strm, src,
-                         in_offsets, req_ids, seq_lens, kp, vp, num_pages, pt, pt_stride, hkv);
+      hipLaunchKernelGGL(dopd::kv_unpack_pages_kernel<64>, grid, block, 0, strm, a);
     else
-      hipLaunchKernelGGL((dopd::kv_unpack_kernel<uint8_t, 128>), grid, dim3(256), 0, strm, src,
-                         in_offsets, req_ids, seq_lens, kp, vp, num_pages, pt, pt_stride, hkv);
-  } else if (s->dtype == DOPD_BF16) {
-    auto* src = (const uint16_t*)in;
-    auto* kp = (uint16_t*)k_pool; auto* vp = (uint16_t*)v_pool;
-    if (s->head_dim == 64)
-      hipLaunchKernelGGL((dopd::kv_unpack_kernel<uint16_t, 64>), grid, dim3(256), 0, strm, src,
-                         in_offsets, req_ids, seq_lens, kp, vp, num_pages, pt, pt_stride, hkv);
-    else
-      hipLaunchKernelGGL((dopd::kv_unpack_kernel<uint16_t, 128>), grid, dim3(256), 0, strm, src,
-                         in_offsets, req_ids, seq_lens, kp, vp, num_pages, pt, pt_stride, hkv);
-  } else {
-    auto* src = (const uint32_t*)in;
-    auto* kp = (uint32_t*)k_pool; auto* vp = (uint32_t*)v_pool;
-    if (s->head_dim == 64)
-      hipLaunchKernelGGL((dopd::kv_unpack_kernel<uint32_t, 64>), grid, dim3(256), 0, strm, src,
-                         in_offsets, req_ids, seq_lens, kp, vp, num_pages, pt, pt_stride, hkv);
-    else
-      hipLaunchKernelGGL((dopd::kv_unpack_kernel<uint32_t, 128>), grid, dim3(256), 0, strm, src,
-                         in_offsets, req_ids, seq_lens, kp, vp, num_pages, pt, pt_stride, hkv);
+      hipLaunchKernelGGL(dopd::kv_unpack_pages_kernel<128>, grid, block, 0, strm, a);
+    return launch_status();
   }
+  const dim3 grid((unsigned)((max_len + dopd::kPage - 1) / dopd::kPage), (unsigned)num_handoff,
+                  (unsigned)zdim);
+  auto launch = [&](auto type_tag) {
+    using T = decltype(type_tag);
+    const T* src = static_cast<const T*>(in);
+    T *kp = static_cast<T*>(k_pool), *vp = static_cast<T*>(v_pool);
+    if (s->head_dim == 64)
+      hipLaunchKernelGGL((dopd::kv_unpack_kernel<T, 64>), grid, dim3(256), 0, strm, src, in_offsets,
+                         req_ids, seq_lens, kp, vp, num_pages, pt, pt_stride, hkv);
+    else
+      hipLaunchKernelGGL((dopd::kv_unpack_kernel<T, 128>), grid, dim3(256), 0, strm, src, in_offsets,
+                         req_ids, seq_lens, kp, vp, num_pages, pt, pt_stride, hkv);
+  };
+  if (s->dtype == DOPD_BF16)
+    launch(uint16_t{});
+  else
+    launch(uint32_t{});
   return launch_status();
 }
 

@@ -1,10 +1,17 @@
 // Handoff unpack on the receiving instance: scatters a packed
 // (layer, K/V, head, token, dim) buffer into the local page pools, the inverse
-// of kv_pack.  One workgroup per (page, handoff, layer*2*Hkv + kv*Hkv + head);
-// K rows are copied as they are, V rows are transposed to the dim-major page
-// block through LDS.  Slots past the request's length are never touched.
+// of kv_pack.  Slots past the request's length are never touched.
+//
+// bf16 and fp32 pools: one workgroup per (page, handoff, layer*2*Hkv + kv*Hkv +
+// head); K rows are copied as they are, V rows are transposed to the dim-major
+// page block through LDS.  E4M3 pools: the page writer's mapping, a wave for
+// the K and V of one (handoff, layer, page) and HW heads, which turns V four
+// tokens at a time in registers.  HBM-bound at size.  Measured, workgroup per
+// block / wave per page: 8 requests of 300-900 tokens, 8 heads, 20 layers, E4M3
+// 119 / 79 us (16 one-byte LDS reads a V run are what it saves); 28 layers of 4
+// bf16 heads 91 / 98 us (a wave's 4 + 4 loads lie in eight streams).
 #pragma once
-#include "common.hpp"
+#include "kv_write.hpp"
 
 namespace dopd {
 
@@ -62,11 +69,7 @@ __global__ __launch_bounds__(256) void kv_unpack_kernel(
       u32x4 x;
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
-        if constexpr (sizeof(T) == 1) {
-          const int s = run * kEl + 4 * w;
-          x[w] = (uint32_t)s_v[s * TP + e] | ((uint32_t)s_v[(s + 1) * TP + e] << 8) |
-                 ((uint32_t)s_v[(s + 2) * TP + e] << 16) | ((uint32_t)s_v[(s + 3) * TP + e] << 24);
-        } else if constexpr (sizeof(T) == 2) {
+        if constexpr (sizeof(T) == 2) {
           const int s = run * kEl + 2 * w;
           x[w] = (uint32_t)s_v[s * TP + e] | ((uint32_t)s_v[(s + 1) * TP + e] << 16);
         } else {
@@ -81,6 +84,46 @@ __global__ __launch_bounds__(256) void kv_unpack_kernel(
       }
     }
   }
+}
+
+struct UnpackPagesArgs {
+  const uint8_t* in;
+  const int64_t* in_off;      // [nhand] element offset of each handoff's block
+  const int32_t* req_ids;     // [nhand] page-table rows
+  const int32_t* seq_lens;    // [nhand]
+  uint8_t* k_pool;            // [layers][P][Hkv][16][D]
+  uint8_t* v_pool;            // [layers][P][Hkv][D][16]
+  const int32_t* page_table;
+  int num_pages, pt_stride, hkv, nhand, layers;
+  int head_groups;            // workgroups of a page of one layer
+};
+
+// Workgroup b: heads of group b % head_groups of the (b / head_groups)-th
+// (handoff, layer, page), pages fastest.
+template <int D>
+__global__ __launch_bounds__(64 * kKvwWaves) void kv_unpack_pages_kernel(UnpackPagesArgs a) {
+  using T = uint8_t;
+  using W = PageWrite<T, T, D>;
+  __shared__ __attribute__((aligned(16))) uint8_t s[kKvwWaves][W::kLdsBytes];
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int h0 = ((int)blockIdx.x % a.head_groups * kKvwWaves + w) * W::HW;
+  if (h0 >= a.hkv) return;
+  int len_l = 0, req_l = 0;  // this lane's handoff
+  auto items = [&](int x) {
+    len_l = a.seq_lens[x];
+    req_l = a.req_ids[x];
+    return a.layers * ((len_l + kPage - 1) / kPage);
+  };
+  int n, local;
+  if (!find_owner((int)blockIdx.x / a.head_groups, a.nhand, items, n, local)) return;
+  const int len = __builtin_amdgcn_readlane(len_l, n % 64), r = __builtin_amdgcn_readlane(req_l, n % 64);
+  const int np = (len + kPage - 1) / kPage, layer = local / np, pg = local % np;
+  const int64_t page = (int64_t)layer * a.num_pages + a.page_table[(int64_t)r * a.pt_stride + pg];
+  const T* k_src = a.in + a.in_off[n] + ((int64_t)layer * 2 * a.hkv * len + (int64_t)pg * kPage) * D;
+  write_page_heads<T, T, D, false>(k_src, k_src + (int64_t)a.hkv * len * D, D, (int64_t)len * D, h0, a.hkv, 0,
+                                   min(kPage, len - pg * kPage), a.k_pool, a.v_pool, page,
+                                   (const float*)nullptr, (const float*)nullptr, (T*)nullptr, (T*)nullptr,
+                                   0, false, s[w]);
 }
 
 }  // namespace dopd

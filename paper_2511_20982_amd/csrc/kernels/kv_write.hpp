@@ -36,8 +36,8 @@ constexpr int kKvwAppendMean = 2;
 // uint16_t -> uint8_t for E4M3 pools).
 template <typename TI, typename TO, int D>
 struct PageWrite {
-  static constexpr bool kE4m3 = sizeof(TO) == 1;
-  static_assert(kE4m3 ? sizeof(TI) == 2 : sizeof(TI) == sizeof(TO), "a copy, or bf16 to E4M3");
+  static constexpr bool kE4m3 = sizeof(TO) == 1 && sizeof(TI) == 2;
+  static_assert(kE4m3 || sizeof(TI) == sizeof(TO), "a copy, or bf16 to E4M3");
   static constexpr int EPC = 16 / (int)sizeof(TI);  // elements of a 16-byte chunk of a row
   static constexpr int CPR = D / EPC;               // chunks of a row
   static constexpr int CW = CPR < 16 ? CPR : 16;    // chunks of a row per pass
@@ -66,14 +66,23 @@ struct PageWrite {
   }
 };
 
+// A 16-byte chunk of rows that need not be aligned to more than an element.
+typedef uint32_t u32x4_a1 __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ u32x4 load_chunk(const uint8_t* p) { return *reinterpret_cast<const u32x4_a1*>(p); }
+__device__ __forceinline__ u32x4 load_chunk(const uint16_t* p) { return *reinterpret_cast<const u32x4_a2*>(p); }
+__device__ __forceinline__ u32x4 load_chunk(const uint32_t* p) { return *reinterpret_cast<const u32x4_a4*>(p); }
+
 // Rows [s0, s1) of page `page` for the HW heads from h0 (those below hkv):
-// k_src / v_src point at KV head 0 of the row that goes to slot s0.  With pk /
+// k_src / v_src point at KV head 0 of the row that goes to slot s0; rows are
+// row_elems apart, heads head_elems.  With pk /
 // pv (the handoff block's rows of slot 0, KV head 0; head h follows
 // pack_head elements later) the rows are written there too.  s: the wave's
 // kLdsBytes of LDS, 16-byte aligned.  Every lane of the wave takes part.
 template <typename TI, typename TO, int D, bool PACK>
 __device__ __forceinline__ void write_page_heads(const TI* k_src, const TI* v_src, int64_t row_elems,
-                                                 int h0, int hkv, int s0, int s1, TO* k_pool,
+                                                 int64_t head_elems, int h0, int hkv, int s0, int s1, TO* k_pool,
                                                  TO* v_pool, int64_t page, const float* k_scale,
                                                  const float* v_scale, TO* pk, TO* pv,
                                                  int64_t pack_head, bool pack_aligned, uint8_t* s) {
@@ -84,7 +93,7 @@ __device__ __forceinline__ void write_page_heads(const TI* k_src, const TI* v_sr
   const int c = l % CW, tq = l / CW % 4, sub = l / (4 * CW);
   const int h = h0 + sub;
   const bool on = h < hkv;
-  const int64_t col = (int64_t)min(h, hkv - 1) * D + EPC * c;
+  const int64_t col = min(h, hkv - 1) * head_elems + EPC * c;
   // K: chunk u is token 4u + tq (whole rows in a row); V: token 4tq + u (four
   // tokens of a dim in one lane).  Tokens outside [s0, s1) read the nearest
   // one inside, so that no load waits behind a branch.
@@ -94,8 +103,8 @@ __device__ __forceinline__ void write_page_heads(const TI* k_src, const TI* v_sr
   for (int p = 0; p < NP; ++p)
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      kx[p][u] = *reinterpret_cast<const u32x4*>(k_src + row(4 * u + tq) + EPC * CW * p);
-      vx[p][u] = *reinterpret_cast<const u32x4*>(v_src + row(4 * tq + u) + EPC * CW * p);
+      kx[p][u] = load_chunk(k_src + row(4 * u + tq) + EPC * CW * p);
+      vx[p][u] = load_chunk(v_src + row(4 * tq + u) + EPC * CW * p);
     }
   float kinv = 1.f, vinv = 1.f;
   if constexpr (W::kE4m3) {
@@ -159,7 +168,7 @@ __device__ __forceinline__ void write_page_heads(const TI* k_src, const TI* v_sr
       }
     } else {
 #pragma unroll
-      for (int w = 0; w < 2; ++w) {
+      for (int w = 0; w < EPC / 4; ++w) {
         const uint32_t a = __builtin_amdgcn_perm(v[p][1][w], v[p][0][w], 0x05010400u);  // t0 t1 of dims 0, 1
         const uint32_t b = __builtin_amdgcn_perm(v[p][1][w], v[p][0][w], 0x07030602u);  // of dims 2, 3
         const uint32_t d = __builtin_amdgcn_perm(v[p][3][w], v[p][2][w], 0x05010400u);
@@ -243,7 +252,7 @@ __global__ __launch_bounds__(64 * kKvwWaves) void kv_write_kernel(KvWriteArgs<TI
   const int64_t page = a.page_table[(int64_t)r * a.pt_stride + lp];
   const int64_t row_elems = (int64_t)a.hkv * D;
   const int64_t src = ((int64_t)row0 + (p_lo - start)) * row_elems;
-  write_page_heads<TI, TO, D, false>(a.k_new + src, a.v_new + src, row_elems, h0, a.hkv,
+  write_page_heads<TI, TO, D, false>(a.k_new + src, a.v_new + src, row_elems, D, h0, a.hkv,
                                      p_lo - lp * kPage, p_hi - lp * kPage, a.k_pool, a.v_pool, page,
                                      a.k_scale, a.v_scale, (TO*)nullptr, (TO*)nullptr, 0, false, s[w]);
 }

@@ -60,7 +60,7 @@ __device__ __forceinline__ void kv_write_pack_workgroup(const WritePackArgs& a, 
     // the rest of a chunk's offset is a multiple of its size
     aligned = (reinterpret_cast<uintptr_t>(pk) & (sizeof(typename W::Out) - 1)) == 0;
   }
-  write_page_heads<uint16_t, TO, D, true>(a.k_new + src, a.v_new + src, row_elems, h0, a.hkv, 0, s1,
+  write_page_heads<uint16_t, TO, D, true>(a.k_new + src, a.v_new + src, row_elems, D, h0, a.hkv, 0, s1,
                                           static_cast<TO*>(a.k_pool), static_cast<TO*>(a.v_pool), page,
                                           a.k_scale, a.v_scale, pk, pv, (int64_t)n * D, aligned, s);
 }

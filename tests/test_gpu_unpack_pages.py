@@ -1,0 +1,40 @@
+"""GPU: the E4M3 unpack (a wave per page and heads) at head counts that leave
+waves and lanes without work, ragged lengths and offsets that are aligned to
+one byte only, bit for bit against a plain index map."""
+import numpy as np
+import pytest
+
+from paper_2511_20982_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _gpu(require_gpu):
+    pass
+
+
+from tests import gpu_util as G  # noqa: E402
+
+
+@pytest.mark.parametrize("hkv,d,layers", [(1, 64, 3), (3, 64, 1), (6, 64, 2), (1, 128, 2), (9, 128, 1)])
+@pytest.mark.parametrize("shift", [0, 3])
+def test_unpack_e4m3(hkv, d, layers, shift):
+    rng = np.random.default_rng(hkv + d + shift)
+    lens = np.array([1, 16, 0, 17, 100, 31, 64], np.int32)
+    pt, num_pages = I.allocate_pages(rng, np.maximum(lens[::-1], 1))
+    offs = I.handoff_offsets(lens, layers, hkv, d) + shift * np.arange(len(lens) + 1)
+    buf = rng.integers(0, 256, int(offs[-1]), dtype=np.uint8)
+    kp = rng.integers(0, 256, (layers, num_pages, hkv, 16, d), dtype=np.uint8)
+    vp = rng.integers(0, 256, (layers, num_pages, hkv, d, 16), dtype=np.uint8)
+    req = np.arange(len(lens), dtype=np.int32)[::-1].copy()
+    ek, ev = kp.copy(), vp.copy()
+    for n, r in enumerate(req):
+        x = buf[offs[n]:offs[n] + layers * 2 * hkv * lens[n] * d].reshape(layers, 2, hkv, lens[n], d)
+        for t in range(int(lens[n])):
+            page = pt[r, t // 16]
+            ek[:, page, :, t % 16, :] = x[:, 0, :, t]
+            ev[:, page, :, :, t % 16] = x[:, 1, :, t]
+    shape = G.A.make_shape(hkv, hkv, d, "fp8")
+    gk, gv = G.gpu_unpack(shape, buf, offs[:-1].copy(), req, lens, kp, vp, layers, pt)
+    assert np.array_equal(gk, ek) and np.array_equal(gv, ev)
