@@ -95,8 +95,10 @@ __global__ __launch_bounds__(256) void kv_pack_kernel(PackArgs<T> a) {
   for (int k = 0; k < NPT; ++k) {
     const int c = tid + 256 * k;
     const int j = c / C;  // wave-uniform
+    // (read once: streaming loads leave the caches to the lines on their way;
+    // pack and unpack of 28 layers together 180 -> 173 us with them)
     if (c < PER * C && meta[j].nvalid > 0)
-      x[k] = reinterpret_cast<const u32x4*>(meta[j].src)[c % C];
+      x[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(meta[j].src) + c % C);
   }
   // Into LDS token-major: K chunks as they are, V chunks (EL tokens of one
   // dim) scattered to their token rows.

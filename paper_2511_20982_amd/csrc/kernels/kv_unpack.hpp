@@ -43,7 +43,7 @@ __global__ __launch_bounds__(256) void kv_unpack_kernel(
       // streaming stores (here and below): the pages leave the caches now,
       // not as write-back during the kernels that follow
       for (int i = tid; i < nvalid * CPR; i += 256)
-        __builtin_nontemporal_store(reinterpret_cast<const u32x4*>(src)[i],
+        __builtin_nontemporal_store(__builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src) + i),
                                     reinterpret_cast<u32x4*>(dst) + i);
     } else {
       for (int i = tid; i < nvalid * D; i += 256) dst[i] = src[i];
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void kv_unpack_kernel(
   if (aligned) {
     for (int i = tid; i < nvalid * CPR; i += 256) {
       const int t = i / CPR, c = i % CPR;
-      *reinterpret_cast<u32x4*>(&s_v[t * TP + c * kEl]) = reinterpret_cast<const u32x4*>(src)[i];
+      *reinterpret_cast<u32x4*>(&s_v[t * TP + c * kEl]) = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src) + i);
     }
   } else {
     for (int i = tid; i < nvalid * D; i += 256) s_v[(i / D) * TP + i % D] = src[i];
