@@ -274,12 +274,12 @@ __device__ __forceinline__ int find_token_owner(const int32_t* cu, int nreq, int
 }
 
 // Append writer: workgroup b takes 256 of the 2 x Hkv x (D / EPC) chunks (K's,
-// then V's) of token b / head_groups.
+// then V's) of token b / head_groups, counted from the first request's first.
 template <typename TI, typename TO, int D>
 __global__ __launch_bounds__(256) void kv_append_kernel(KvWriteArgs<TI, TO> a) {
   using W = PageWrite<TI, TO, D>;
   using Out = typename W::Out;
-  const int t = (int)blockIdx.x / a.head_groups;
+  int t = (int)blockIdx.x / a.head_groups;
   const int i = (int)blockIdx.x % a.head_groups * 256 + (int)threadIdx.x;
   const int half = a.hkv * W::CPR;
   const bool is_v = i >= half, on = i < 2 * half;
@@ -287,11 +287,17 @@ __global__ __launch_bounds__(256) void kv_append_kernel(KvWriteArgs<TI, TO> a) {
   const int h = j / W::CPR, c = j % W::CPR;
   u32x4 x = {0, 0, 0, 0};
   float scale = 1.f;
-  if (on) {
+  auto row = [&] {
     x = *reinterpret_cast<const u32x4*>((is_v ? a.v_new : a.k_new) + ((int64_t)t * a.hkv + h) * D + W::EPC * c);
+  };
+  if (on) {
+    row();  // beside the lengths: nearly every call's rows start at 0
     if constexpr (W::kE4m3) scale = is_v ? a.v_scale[h] : a.k_scale[h];
   }
+  const int first = a.cu_new[0];
+  t += first;
   if (t >= a.cu_new[a.nreq]) return;  // uniform
+  if (first != 0 && on) row();
   const int r = find_token_owner(a.cu_new, a.nreq, t);
   const int pos = a.start_pos[r] + (t - a.cu_new[r]);
   const int64_t page = a.page_table[(int64_t)r * a.pt_stride + pos / kPage];

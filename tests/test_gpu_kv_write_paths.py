@@ -62,3 +62,24 @@ def test_paged_write(dtype, hkv, d, nreq, tokens):
     bits = {"bf16": np.uint16, "fp32": np.uint32, "fp8": np.uint8}[dtype]
     assert np.array_equal(gk.view(bits), ek.view(bits))
     assert np.array_equal(gv.view(bits), ev.view(bits))
+
+
+# Rows in front of the first request's belong to nobody and go nowhere, whichever
+# mapping the total (which counts them) chooses.
+@pytest.mark.parametrize("nreq,before", [(2, 1), (70, 5), (3, 9)])
+def test_rows_before_the_first_request(nreq, before):
+    hkv, d = 3, 64
+    rng = np.random.default_rng(nreq + before)
+    start = rng.integers(0, 40, nreq).astype(np.int32)
+    pt, num_pages = I.allocate_pages(rng, start + 1)
+    cu = (before + np.arange(nreq + 1)).astype(np.int32)
+    k, v = (I.normal(rng, (before + nreq, hkv, d), "bf16") for _ in range(2))
+    kp, vp = I.empty_pools(num_pages, hkv, d, "bf16")
+    gk, gv = G.gpu_kv_write(G.A.make_shape(hkv, hkv, d, "bf16"), k, v, kp, vp, pt, cu, start)
+    ek, ev = kp.copy(), vp.copy()
+    for r in range(nreq):
+        page, slot = pt[r, start[r] // 16], start[r] % 16
+        ek[page, :, slot, :] = k[before + r]
+        ev[page, :, :, slot] = v[before + r]
+    assert np.array_equal(gk.view(np.uint16), ek.view(np.uint16))
+    assert np.array_equal(gv.view(np.uint16), ev.view(np.uint16))
