@@ -66,7 +66,8 @@ CALL_KERNELS = {"decode": ("decode_split_kernel", "decode_merge_list_kernel",
                 "prefill_chunked_fp8": ("prefill_bf16_kernel<128, true, true>",
                                         "prefill_bf16_kernel<64, true, true>",
                                         "prefill_split_merge_kernel"),
-                "kv_write": ("kv_write_kernel",), "kv_write_fp8": ("kv_write_e4m3_kernel",),
+                "kv_write": ("kv_write_kernel<unsigned short, unsigned short",),
+                "kv_write_fp8": ("kv_write_kernel<unsigned short, unsigned char",),
                 "plain_copy": ("bitwise_not_kernel",),
                 "pack": ("kv_pack_kernel",), "unpack": ("kv_unpack_kernel",),
                 "pd_step": ("pd_step_kernel", "decode_merge_list_kernel",

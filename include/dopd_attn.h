@@ -299,7 +299,9 @@ dopd_status dopd_kv_write_fp8(const dopd_attn_shape* shape, const void* k_new, c
  * page is read once for all Hq/Hkv query heads of the group (at most 16); a
  * (request, KV head) whose keys fall in several shares is finished by a
  * second kernel that merges the partials exactly (log-sum-exp rescaling), on
- * the same stream.
+ * the same stream.  With the automatic split, a light call (at most one
+ * (request, KV head) per CU, contexts short enough) instead gives every whole
+ * (request, KV head) to one workgroup and writes no partials.
  */
 dopd_status dopd_decode_attn(const dopd_attn_shape* shape, const void* q, const void* k_pool,
                              const void* v_pool, int32_t num_pages, const int32_t* page_table,
@@ -316,8 +318,10 @@ dopd_status dopd_decode_attn(const dopd_attn_shape* shape, const void* q, const 
  * operation with K_j = code * k_scale[c] and V_j = code * v_scale[c] for KV
  * head c; q and out bf16, lse as there.  The codes are widened to bf16
  * (exactly) for the same MFMA path; the K scale multiplies the softmax scale
- * and the V scale the output, in fp32.  Same partition, workspace
- * (dopd_decode_workspace_size with the same shape) and split_tokens rules;
+ * and the V scale the output, in fp32.  Same number of
+ * shares, workspace (dopd_decode_workspace_size with the same shape) and
+ * split_tokens rules (a share counts the start of a context as more of its
+ * tokens, which take half the time here);
  * half the bytes of the bf16 cache per token.
  */
 dopd_status dopd_decode_attn_fp8(const dopd_attn_shape* shape, const void* q,

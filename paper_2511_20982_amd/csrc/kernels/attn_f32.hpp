@@ -15,8 +15,10 @@
 //
 // Bound by latency at small sizes: the columns share each K/V load and the
 // waves share the keys, so a 120-key row is two tiles deep (one wave per (row,
-// head) that visited key after key took 0.3 - 0.45 us a key: prefill of four
-// prompts of up to 120 tokens, 8/2 heads, d 64, 37 us, their decode 55 us).
+// head) that visited key after key took 0.3 - 0.45 us a key).  Four prompts of
+// up to 120 tokens, 8/2 heads, d 64: prefill 37 -> 7.7 us, their decode 55 ->
+// 6.5 us; two prompts of 1500 tokens, 32/8 heads, d 128, with writes and one
+// decode step 6.9 -> 0.79 ms.
 //
 // Keys past a column's limit are masked by select in S^T, and V of positions
 // past the request's last key is replaced by 0.  A tile some columns see and
