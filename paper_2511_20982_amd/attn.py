@@ -134,6 +134,7 @@ def _bind(L):
     """Points _marshal's entry points at the library's."""
     global _CALLS
     from paper_2511_20982_amd import _marshal
+    _marshal.set_shape(Shape)
     for f in dir(_marshal):
         if f.startswith("dopd_"):
             _marshal.bind(f, C.cast(getattr(L, f), C.c_void_p).value)

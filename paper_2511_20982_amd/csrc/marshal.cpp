@@ -20,10 +20,11 @@
 
 namespace {
 
-PyObject* g_data_ptr = nullptr;  // interned "data_ptr"
+PyObject* g_data_ptr = nullptr;      // interned "data_ptr"
+PyTypeObject* g_shape = nullptr;     // the binding's class of dopd_attn_shape (set_shape)
 
 // Kinds of arguments, one character each in an entry point's signature:
-//   s shape (a ctypes structure), d device pointer (an object with data_ptr(),
+//   s shape (an instance of the class given to set_shape), d device pointer (an object with data_ptr(),
 //   or None), h host pointer (an array that exports its buffer, or None),
 //   i int32, z size, p address (the stream)
 struct Arg {
@@ -44,15 +45,29 @@ bool integer(PyObject* o, long long* out) {
   return !(*out == -1 && PyErr_Occurred());
 }
 
+bool host_buffer(PyObject* o, Arg& a) {
+  if (PyObject_GetBuffer(o, &a.buffer, PyBUF_SIMPLE) != 0) return false;
+  a.held = true;
+  a.value = (long long)(uintptr_t)a.buffer.buf;
+  return true;
+}
+
 bool convert(PyObject* o, char kind, Arg& a) {
   switch (kind) {
     case 's':
-    case 'h':
-      if (kind == 'h' && o == Py_None) return true;
-      if (PyObject_GetBuffer(o, &a.buffer, PyBUF_SIMPLE) != 0) return false;
-      a.held = true;
-      a.value = (long long)(uintptr_t)a.buffer.buf;
+      // (other objects export buffers too, of any length)
+      if (!g_shape || !PyObject_TypeCheck(o, g_shape)) {
+        PyErr_Format(PyExc_TypeError, "shape must be a Shape, not %.200s", Py_TYPE(o)->tp_name);
+        return false;
+      }
+      if (!host_buffer(o, a)) return false;
+      if (a.buffer.len < (Py_ssize_t)sizeof(dopd_attn_shape)) {
+        PyErr_SetString(PyExc_TypeError, "the Shape is shorter than the library's");
+        return false;
+      }
       return true;
+    case 'h':
+      return o == Py_None || host_buffer(o, a);
     case 'd': {
       if (o == Py_None) return true;
       PyObject* p = PyObject_CallMethodNoArgs(o, g_data_ptr);
@@ -153,8 +168,21 @@ PyObject* bind(PyObject*, PyObject* args) {
   return nullptr;
 }
 
+// set_shape(class): what a shape argument must be an instance of.
+PyObject* set_shape(PyObject*, PyObject* cls) {
+  if (!PyType_Check(cls)) {
+    PyErr_SetString(PyExc_TypeError, "set_shape takes a class");
+    return nullptr;
+  }
+  Py_INCREF(cls);
+  Py_XDECREF(g_shape);
+  g_shape = reinterpret_cast<PyTypeObject*>(cls);
+  Py_RETURN_NONE;
+}
+
 #define METHOD(name, sig) {#name, (PyCFunction)(void (*)(void))w_##name, METH_FASTCALL, sig},
 PyMethodDef g_methods[] = {ENTRIES(METHOD){"bind", bind, METH_VARARGS, "bind(name, address)"},
+                           {"set_shape", set_shape, METH_O, "set_shape(class)"},
                            {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, g_methods,
                         nullptr, nullptr, nullptr, nullptr};

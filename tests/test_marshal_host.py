@@ -63,6 +63,22 @@ def test_what_is_no_device_pointer_is_refused():
     assert prefill(lse=t, cu_host=[0, 0]) == A.DOPD_OK
 
 
+@pytest.mark.parametrize("shape", [b"", b"\0" * 24, np.array([8, 2, 128, 16, 0, 0], np.int32), bytearray(100), None])
+def test_only_a_shape_is_a_shape(shape):
+    """Whatever exports a buffer is refused before its bytes are read."""
+    with pytest.raises(TypeError):
+        A.dopd_prefill_attn(shape, P, P, P, P, None, P, CU, 1, stream=0)
+    with pytest.raises(TypeError):
+        A.dopd_decode_attn_noalloc(shape, P, P, P, 10, P, 1024, P, [40], 1, 0, P, None, stream=0)
+
+
+def test_a_class_derived_from_shape_is_one():
+    class Named(A.Shape):
+        pass
+
+    assert prefill(Named(6, 4, 128, 16, A.DOPD_BF16, 1.0)) == A.DOPD_ERR_INVALID_SHAPE
+
+
 def test_every_launching_entry_point_is_bound():
     A.lib()
     m = A._calls()
