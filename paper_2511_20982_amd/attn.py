@@ -3,7 +3,7 @@
 Argument marshalling only: every entry point takes torch tensors (device
 memory) or numpy arrays (the ``_host`` copies), passes raw pointers to the
 library, and raises :class:`DopdError` on a non-OK status.  The launching
-calls go through ``_marshal.so`` (``csrc/marshal.cpp``), which converts their
+calls go through ``_marshal`` (``csrc/marshal.cpp``), which converts their
 arguments natively.  All compute runs
 in the library's HIP kernels on the given (default: current) HIP stream.
 The library is loaded on first use; if it has not been built, the call fails
@@ -64,6 +64,27 @@ def make_shape(hq: int, hkv: int, d: int, dtype: str = "bf16", scale: float | No
     return Shape(hq, hkv, d, page_size, dt, 1.0 / math.sqrt(d) if scale is None else scale)
 
 
+# The launching entry points, one character per argument: s shape, d device
+# pointer, h host pointer, i int32, z size, p stream.  The native module holds
+# its own table, checked against the header when it is compiled and against
+# this one when it is loaded.
+LAUNCHES = {
+    "dopd_prefill_attn": "sddddddhidzp",
+    "dopd_prefill_paged_attn": "sdddididhdhiddp",
+    "dopd_prefill_paged_attn_split": "sdddididhdhiidddzp",
+    "dopd_prefill_paged_attn_fp8": "sdddddididhdhiidddzp",
+    "dopd_kv_write": "sddddididdiip",
+    "dopd_kv_write_fp8": "sddddddididdiip",
+    "dopd_decode_attn": "sdddididhiidddzp",
+    "dopd_decode_attn_fp8": "sdddddididhiidddzp",
+    "dopd_decode_attn_noalloc": "sdddididhiiddp",
+    "dopd_kv_pack_for_handoff": "siddididdhdidp",
+    "dopd_kv_unpack_from_handoff": "siddddhiddidip",
+    "dopd_kv_write_pack_for_handoff": "sddddididhiddp",
+    "dopd_pd_step": "sdddhiddddddhidddddiiddidzp",
+    "dopd_pd_step_fp8": "sdddhiddddddhidddddddiiddidzp",
+}
+
 _LIB = None
 
 
@@ -78,72 +99,46 @@ def lib():
             raise RuntimeError(f"{LIB_PATH} is not built; run __graft_entry__.build() "
                                "or python paper_2511_20982_amd/build.py")
         L = C.CDLL(LIB_PATH)
-        P, i32, sz = C.c_void_p, C.c_int32, C.c_size_t
-        SP = C.POINTER(Shape)
-        L.dopd_prefill_attn.argtypes = [SP, P, P, P, P, P, P, P, i32, P, sz, P]
-        L.dopd_prefill_workspace_size.argtypes = [SP, P, i32]
-        L.dopd_prefill_workspace_size.restype = sz
-        L.dopd_prefill_paged_attn.argtypes = [SP, P, P, P, i32, P, i32, P, P, P, P, i32, P, P, P]
-        L.dopd_prefill_paged_attn_split.argtypes = [SP, P, P, P, i32, P, i32, P, P, P, P, i32,
-                                                    i32, P, P, P, sz, P]
-        L.dopd_prefill_paged_workspace_size.argtypes = [SP, P, P, i32, i32]
-        L.dopd_prefill_paged_workspace_size.restype = sz
-        L.dopd_prefill_paged_attn_fp8.argtypes = [SP, P, P, P, P, P, i32, P, i32, P, P, P, P, i32,
-                                                  i32, P, P, P, sz, P]
-        L.dopd_prefill_paged_fp8_workspace_size.argtypes = [SP, P, P, i32, i32]
-        L.dopd_prefill_paged_fp8_workspace_size.restype = sz
-        L.dopd_kv_write.argtypes = [SP, P, P, P, P, i32, P, i32, P, P, i32, i32, P]
-        L.dopd_decode_attn.argtypes = [SP, P, P, P, i32, P, i32, P, P, i32, i32, P, P, P, sz, P]
-        L.dopd_kv_write_fp8.argtypes = [SP, P, P, P, P, P, P, i32, P, i32, P, P, i32, i32, P]
-        L.dopd_decode_attn_fp8.argtypes = [SP, P, P, P, P, P, i32, P, i32, P, P, i32, i32, P, P,
-                                           P, sz, P]
-        L.dopd_decode_attn_noalloc.argtypes = [SP, P, P, P, i32, P, i32, P, P, i32, i32, P, P, P]
-        L.dopd_decode_workspace_size.argtypes = [SP, P, i32, i32]
-        L.dopd_decode_workspace_size.restype = sz
-        L.dopd_kv_pack_for_handoff.argtypes = [SP, i32, P, P, i32, P, i32, P, P, P, P, i32, P, P]
-        L.dopd_kv_unpack_from_handoff.argtypes = [SP, i32, P, P, P, P, P, i32, P, P, i32, P, i32, P]
+        P, i32, sz, SP = C.c_void_p, C.c_int32, C.c_size_t, C.POINTER(Shape)
+        types = {"s": SP, "d": P, "h": P, "p": P, "i": i32, "z": sz}
+        for f, kinds in LAUNCHES.items():
+            getattr(L, f).argtypes = [types[k] for k in kinds]
+            getattr(L, f).restype = i32
+        for f, args in (("dopd_prefill_workspace_size", [SP, P, i32]),
+                        ("dopd_prefill_paged_workspace_size", [SP, P, P, i32, i32]),
+                        ("dopd_prefill_paged_fp8_workspace_size", [SP, P, P, i32, i32]),
+                        ("dopd_decode_workspace_size", [SP, P, i32, i32]),
+                        ("dopd_pd_step_workspace_size", [SP, P, i32, i32])):
+            getattr(L, f).argtypes = args
+            getattr(L, f).restype = sz
         L.dopd_validate_page_table_host.argtypes = [P, i32, i32, P, i32]
-        L.dopd_kv_write_pack_for_handoff.argtypes = [SP, P, P, P, P, i32, P, i32, P, P, i32, P,
-                                                     P, P]
-        L.dopd_pd_step.argtypes = [SP, P, P, P, P, i32, P, P, P, P, P, P, P, i32, P, P, P, P, P,
-                                   i32, i32, P, P, i32, P, sz, P]
-        L.dopd_pd_step_fp8.argtypes = [SP, P, P, P, P, i32, P, P, P, P, P, P, P, i32, P, P, P,
-                                       P, P, P, P, i32, i32, P, P, i32, P, sz, P]
-        L.dopd_pd_step_workspace_size.argtypes = [SP, P, i32, i32]
-        L.dopd_pd_step_workspace_size.restype = sz
+        L.dopd_validate_page_table_host.restype = i32
         L.dopd_status_string.argtypes = [i32]
         L.dopd_status_string.restype = C.c_char_p
         L.dopd_last_hip_error.restype = i32
-        for f in ("dopd_prefill_attn", "dopd_prefill_paged_attn",
-                  "dopd_prefill_paged_attn_split", "dopd_prefill_paged_attn_fp8", "dopd_kv_write",
-                  "dopd_kv_write_fp8", "dopd_decode_attn", "dopd_decode_attn_fp8",
-                  "dopd_decode_attn_noalloc",
-                  "dopd_kv_pack_for_handoff", "dopd_kv_unpack_from_handoff",
-                  "dopd_validate_page_table_host", "dopd_kv_write_pack_for_handoff",
-                  "dopd_pd_step", "dopd_pd_step_fp8"):
-            getattr(L, f).restype = i32
-        _bind(L)
         _LIB = L
     return _LIB
 
 
-_CALLS = None  # the _marshal module, bound to the loaded library
-
-
-def _bind(L):
-    """Points _marshal's entry points at the library's."""
-    global _CALLS
-    from paper_2511_20982_amd import _marshal
-    _marshal.set_shape(Shape)
-    for f in dir(_marshal):
-        if f.startswith("dopd_"):
-            _marshal.bind(f, C.cast(getattr(L, f), C.c_void_p).value)
-    _CALLS = _marshal
+_CALLS = None  # the native module, bound to the loaded library
 
 
 def _calls():
-    if _LIB is None:
-        lib()
+    """The native argument conversion; what launches nothing does without it."""
+    global _CALLS
+    if _CALLS is None:
+        L = lib()
+        try:
+            from paper_2511_20982_amd import _marshal as m
+        except ImportError as e:
+            raise RuntimeError(f"the argument conversion of {LIB_PATH} is not built for this Python ({e}); "
+                               "run __graft_entry__.build() or python paper_2511_20982_amd/build.py") from e
+        if {f: getattr(m, f).__doc__ for f in dir(m) if f.startswith("dopd_")} != LAUNCHES:
+            raise RuntimeError(f"{m.__file__} was built from other sources; build again")
+        m.set_shape(Shape)
+        for f in LAUNCHES:
+            m.bind(f, C.cast(getattr(L, f), C.c_void_p).value)
+        _CALLS = m
     return _CALLS
 
 

@@ -1,5 +1,6 @@
 """Builds libdopd_attn.so (all HIP kernels + the C ABI) for gfx950 and the
-binding's argument marshalling (_marshal.so, host only), in-tree."""
+binding's argument marshalling (_marshal, host only, for the Python that builds
+it), in-tree."""
 import os
 import subprocess
 import sys
@@ -10,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 SRC = os.path.join(HERE, "csrc", "dopd_attn.hip")
 LIB = os.path.join(HERE, "libdopd_attn.so")
 MARSHAL_SRC = os.path.join(HERE, "csrc", "marshal.cpp")
-MARSHAL = os.path.join(HERE, "_marshal.so")
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

@@ -1,6 +1,8 @@
 """CPU: the native argument conversion of the binding's launching calls (every
 call here ends in the library's own argument checks, before any device work)."""
 import re
+import sys
+import types
 
 import numpy as np
 import pytest
@@ -88,3 +90,41 @@ def test_every_launching_entry_point_is_bound():
     for f in bound:
         with pytest.raises(TypeError):
             getattr(m, f)(1, 2)
+
+
+MODULE = "paper_2511_20982_amd._marshal"
+
+
+def replace_module(monkeypatch, m):
+    """The module the binding finds at its next launching call (None: none)."""
+    import paper_2511_20982_amd as package
+    monkeypatch.setattr(A, "_CALLS", None)
+    monkeypatch.delattr(package, "_marshal", raising=False)
+    monkeypatch.setitem(sys.modules, MODULE, m)
+
+
+def test_host_only_calls_need_no_module(monkeypatch):
+    replace_module(monkeypatch, None)
+    shape = A.make_shape(8, 2, 128)
+    assert A.dopd_decode_workspace_size(shape, np.array([40], np.int32), 1) > 0
+    assert A.status_string(A.DOPD_OK)
+    with pytest.raises(RuntimeError, match="not built.*build"):
+        prefill()
+
+
+def test_a_module_of_other_sources_is_refused(monkeypatch):
+    real = A._calls()
+    other = types.ModuleType(MODULE)
+    for f in dir(real):
+        setattr(other, f, getattr(real, f))
+    changed = lambda *a: 0  # noqa: E731
+    changed.__doc__ = A.LAUNCHES["dopd_kv_write"] + "p"
+    other.dopd_kv_write = changed
+    replace_module(monkeypatch, other)
+    with pytest.raises(RuntimeError, match="other sources"):
+        prefill()
+
+
+def test_the_tables_name_every_launching_entry_point():
+    host_only = {f for f in A.EXPORTS if re.search(r"_size$|_host$|status_string|last_hip_error", f)}
+    assert set(A.LAUNCHES) == set(A.EXPORTS) - host_only
