@@ -15,10 +15,17 @@
 //
 // Bound by latency at small sizes: the columns share each K/V load and the
 // waves share the keys, so a 120-key row is two tiles deep (one wave per (row,
-// head) that visited key after key took 0.3 - 0.45 us a key).  Four prompts of
-// up to 120 tokens, 8/2 heads, d 64: prefill 37 -> 7.7 us, their decode 55 ->
-// 6.5 us; two prompts of 1500 tokens, 32/8 heads, d 128, with writes and one
-// decode step 6.9 -> 0.79 ms.
+// head) that visited key after key took 0.3 - 0.45 us a key).  Six prompts of
+// 60-120 tokens, 8/2 heads, d 64: prefill 43 -> 7.8 us, their decode 43 -> 6.5;
+// of 500-1000 tokens, 64/8 heads, d 128: 7.4 -> 0.86 ms and 530 -> 36 us.  Up to
+// about 5 tokens that wave was faster (3.5-4.2 us; here 5-6: a tile's products
+// and a longer program).
+//
+// Rounding: a score's products are added eight at a time and then pair by pair
+// (one chain of d / 2, as two accumulators over all of d make it, left outputs at
+// d 128 a third further from 64 bits than sums over a wave's lanes: six prompts
+// of 8-16 tokens 1.12e-7 against 0.80e-7, now 0.77e-7; of 60-120 tokens 1.71e-7
+// against 1.44e-7, now 1.13e-7), and the division by the row sum rounds once.
 //
 // Keys past a column's limit are masked by select in S^T, and V of positions
 // past the request's last key is replaced by 0.  A tile some columns see and
@@ -32,6 +39,12 @@ namespace dopd {
 // Elements of the caller's fp32 arrays are aligned to 4 bytes only.
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ f32x4 load_f32x4(const float* p) { return *reinterpret_cast<const f32x4_a4*>(p); }
+
+__device__ __forceinline__ void load_to(float* d, const float* p) {
+  const f32x4 x = load_f32x4(p);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) d[i] = x[i];
+}
 
 struct AttnF32Args {
   const float* q;             // [T][Hq][D]
@@ -49,23 +62,37 @@ struct AttnF32Args {
   float scale;
 };
 
+// x / y for several x: 1 / y in two parts, so that the quotient is rounded about
+// once (x * (1 / y) is rounded twice).
+struct F32Quot {
+  float inv, low;
+  __device__ __forceinline__ explicit F32Quot(float y) : inv(1.f / y), low(fmaf(-inv, y, 1.f) * inv) {}
+  __device__ __forceinline__ float operator()(float x) const {
+    return fabsf(x) < INFINITY ? fmaf(x, inv, x * low) : x * inv;
+  }
+};
+
 constexpr int kF32Cols = 16;  // columns of a workgroup
 constexpr int kF32Keys = 16;  // keys of a tile (one page)
 
 // Waves of a workgroup: eight at d = 64; four at d = 128, whose two buffered
-// tiles take more than the registers eight would have.
+// tiles leave a wave no fewer than 256 registers.  Either way two waves share a
+// SIMD, so that calls of more workgroups than CUs run at once (d 128 at one wave:
+// 6 prompts of 8-16 tokens, 64/8 heads, 14.7 us against 9.6; of 500-1000 tokens
+// 1240 against 855).  The tiles are scalars, not vectors: as vectors, whose
+// registers have to lie side by side, 22-34 of them were spilled.
 template <int D>
 constexpr int f32_waves() { return D == 64 ? 8 : 4; }
 
 template <int D, bool PAGED, int W = f32_waves<D>()>
-__global__ __launch_bounds__(64 * W) void attn_f32_kernel(AttnF32Args a) {
+__global__ __launch_bounds__(64 * W, 8 / W) void attn_f32_kernel(AttnF32Args a) {
   constexpr int KR = D / 4;     // elements of a K row one lane holds
   constexpr int NT = D / 16;    // O^T tiles of 16 dims
   constexpr int OP = D + 4;     // padded row of the merge buffer
   __shared__ float s_o[W][kF32Cols][OP];
   __shared__ float s_m[W][kF32Cols], s_l[W][kF32Cols];
-  const int tid = threadIdx.x, l = lane_id();
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int hq = a.hq, hkv = a.hkv, g = hq / hkv;
 
   // Block: (request, column tile, KV head), the last column tiles (the most
@@ -91,17 +118,16 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(AttnF32Args a) {
   const int first_limit = P + col0 / g;      // last key every column sees
   const int nkeys = P + (min(col0 + kF32Cols, ncols) - 1) / g + 1;
   const int ntiles = (nkeys + kF32Keys - 1) / kF32Keys;
+  // One tile: wave 0 stores its result, with no merge (9.6 -> 6.8 us on the 6
+  // prompts of 8-16 tokens above).
+  if (ntiles == 1 && w > 0) return;
 
   // Q^T operand of step i: Q[col][KR qg + i].
   float qv[KR];
   {
     const float* qp = a.q + ((int64_t)(row0 + ci / g) * hq + c * g + ci % g) * D + KR * qg;
 #pragma unroll
-    for (int i = 0; i < KR; i += 4) {
-      const f32x4 x = load_f32x4(qp + i);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) qv[i + j] = x[j];
-    }
+    for (int i = 0; i < KR; i += 4) load_to(qv + i, qp + i);
   }
 
   // Dim of O^T tile n, row x: fresh V rows are read NT dims at a time, pool
@@ -109,8 +135,8 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(AttnF32Args a) {
   auto dim_of = [](int n, int x) { return PAGED ? 16 * n + x : NT * x + n; };
   const int32_t* pt = PAGED ? a.page_table + (int64_t)r * a.pt_stride : nullptr;
   struct Tile {
-    f32x4 k[KR / 4];  // K[key l % 16][KR qg + 0 ..]
-    f32x4 v[NT];      // v[n][j] = V[key 4 qg + j][dim_of(n, l % 16)]
+    float k[KR];     // K[key l % 16][KR qg + 0 ..]
+    float v[NT][4];  // v[n][j] = V[key 4 qg + j][dim_of(n, l % 16)]
   };
   // Positions past the last key read the last one (fresh) or their page slot,
   // which may hold anything (pools).
@@ -119,15 +145,15 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(AttnF32Args a) {
       const int64_t blk = ((int64_t)pt[kt] * hkv + c) * (kPage * D);
       const float* kp = a.k + blk + cl * D + KR * qg;
 #pragma unroll
-      for (int i = 0; i < KR / 4; ++i) t.k[i] = load_f32x4(kp + 4 * i);
+      for (int i = 0; i < KR; i += 4) load_to(t.k + i, kp + i);
       const float* vp = a.v + blk + 4 * qg;
 #pragma unroll
-      for (int n = 0; n < NT; ++n) t.v[n] = load_f32x4(vp + dim_of(n, cl) * kPage);
+      for (int n = 0; n < NT; ++n) load_to(t.v[n], vp + dim_of(n, cl) * kPage);
     } else {
       const int key = min(kt * kF32Keys + cl, nkeys - 1);
       const float* kp = a.k + ((int64_t)(row0 + key) * hkv + c) * D + KR * qg;
 #pragma unroll
-      for (int i = 0; i < KR / 4; ++i) t.k[i] = load_f32x4(kp + 4 * i);
+      for (int i = 0; i < KR; i += 4) load_to(t.k + i, kp + i);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int kj = min(kt * kF32Keys + 4 * qg + j, nkeys - 1);
@@ -148,14 +174,16 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(AttnF32Args a) {
   float m = -INFINITY, lsum = 0.f;  // of this lane's column; lsum of its own keys only
 
   auto compute = [&](Tile& t, int kt) {
-    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+    f32x4 sum[KR / 2];  // of eight products each, then added pair by pair
 #pragma unroll
-    for (int i = 0; i < KR; i += 2) {
-      s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(t.k[i / 4][i % 4], qv[i], s0, 0, 0, 0);
-      s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(t.k[i / 4][i % 4 + 1], qv[i + 1], s1, 0, 0, 0);
+    for (int i = 0; i < KR / 2; ++i) {
+      sum[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.k[2 * i], qv[2 * i], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+      sum[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.k[2 * i + 1], qv[2 * i + 1], sum[i], 0, 0, 0);
+#pragma unroll
+      for (int b = 1; (i + 1) % (2 * b) == 0; b *= 2) sum[i + 1 - 2 * b] += sum[i + 1 - b];
     }
     const int key0 = kt * kF32Keys + 4 * qg;  // this lane's keys key0 .. key0 + 3
-    f32x4 s = (s0 + s1) * a.scale;
+    f32x4 s = sum[0] * a.scale;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       if (key0 + j > limit) s[j] = -INFINITY;
@@ -220,17 +248,34 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(AttnF32Args a) {
   }
   lsum += __shfl_xor(lsum, 16, 64);
   lsum += __shfl_xor(lsum, 32, 64);
-  if (qg == 0) {
-    s_m[w][cl] = m;
-    s_l[w][cl] = lsum;
+  // The lane anew: held over the loop it costs registers the tiles need.
+  int le;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(le));
+  const int ce = le & 15, qe = le >> 4;
+  if (ntiles == 1) {
+    const int cx = col0 + ce;
+    if (cx >= ncols) return;
+    lsum += m - m;  // (no finite score: NaN, as the merge below has it)
+    const F32Quot quot(lsum);
+    const int64_t row = (int64_t)(row0 + cx / g) * hq + c * g + cx % g;
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a.out[row * D + dim_of(n, 4 * qe + j)] = quot(o[n][j]);
+    if (a.lse && qe == 0) a.lse[row] = m + logf(lsum);
+    return;
+  }
+  if (qe == 0) {
+    s_m[w][ce] = m;
+    s_l[w][ce] = lsum;
   }
 #pragma unroll
   for (int n = 0; n < NT; ++n)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) s_o[w][cl][dim_of(n, 4 * qg + j)] = o[n][j];
+    for (int j = 0; j < 4; ++j) s_o[w][ce][dim_of(n, 4 * qe + j)] = o[n][j];
   __syncthreads();
   const int live = min(kF32Cols, ncols - col0);
-  for (int i = tid; i < live * D; i += 64 * W) {
+  for (int i = 64 * w + le; i < live * D; i += 64 * W) {
     const int x = i / D, e = i % D, cx = col0 + x;
     float M = s_m[0][x];
 #pragma unroll
@@ -243,7 +288,7 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(AttnF32Args a) {
       acc += f * s_o[u][x][e];
     }
     const int64_t row = (int64_t)(row0 + cx / g) * hq + c * g + cx % g;
-    a.out[row * D + e] = acc * (1.f / sum);
+    a.out[row * D + e] = F32Quot(sum)(acc);
     if (a.lse && e == 0) a.lse[row] = M + logf(sum);
   }
 }
