@@ -626,15 +626,15 @@ dopd_status launch_kv_write(const dopd_attn_shape* s, const void* k_new, const v
   hipStream_t strm = as_stream(stream);
   const int d = s->head_dim;
   if (total_new <= dopd::kKvwAppendMean * (int64_t)nreq) {
-    const int64_t chunks = (int64_t)2 * a.hkv * d * sizeof(TI) / 16;
-    const int64_t groups = (chunks + 255) / 256;
+    const int64_t waves = 2 * (((int64_t)a.hkv * d * sizeof(TI) / 16 + 63) / 64);
+    const int64_t groups = (waves + dopd::kKvaWaves - 1) / dopd::kKvaWaves;
     if (groups * total_new > INT32_MAX) return DOPD_ERR_INVALID_SHAPE;
     a.head_groups = (int)groups;
-    const dim3 grid((unsigned)(groups * total_new));
+    const dim3 grid((unsigned)(groups * total_new)), block(64 * dopd::kKvaWaves);
     if (d == 64)
-      hipLaunchKernelGGL((dopd::kv_append_kernel<TI, TO, 64>), grid, dim3(256), 0, strm, a);
+      hipLaunchKernelGGL((dopd::kv_append_kernel<TI, TO, 64>), grid, block, 0, strm, a);
     else
-      hipLaunchKernelGGL((dopd::kv_append_kernel<TI, TO, 128>), grid, dim3(256), 0, strm, a);
+      hipLaunchKernelGGL((dopd::kv_append_kernel<TI, TO, 128>), grid, block, 0, strm, a);
     return launch_status();
   }
   // Touched pages per request <= n / 16 + 2, so this bounds the item count.

@@ -5,19 +5,21 @@
 // nearest even; codes rounded to nearest even).  Slots of a page outside the
 // written range are never touched.
 //
-// Two mappings.  The page writer gives a wave one (page, KV head) (two heads
-// at d = 64) and issues all of its 16-byte loads at once; a lane holds 4 tokens
+// Two mappings.  The page writer gives a wave one page of 16 / CW KV heads (CW
+// chunks of a row per pass: one head, or two bf16 heads at d = 64) and issues all
+// of its 16-byte loads at once; a lane holds 4 tokens
 // of 8 (bf16) or 4 (fp32) dims of V, so the transposition to dim rows is done
 // in registers four tokens at a time and only gathers rows in LDS, privately
 // per wave (no workgroup barrier).  The append writer gives a wave 64 16-byte
-// chunks of one token: with one or two tokens per request every page is partial
-// and V is written element by element either way, and what counts is the chain
-// of loads that finds the request and its page.
+// chunks of one token's K or V: with one or two tokens per request every page is
+// partial and V is written element by element either way, and what counts is the
+// chain of loads that finds the request and its page, and the cache lines that
+// the elements of V touch.
 //
 // HBM-bound at size: E4M3 writes of 16 prompts (318 MB, 8 heads, d 128) 74 ->
 // 62 us (5.1 TB/s), bf16 writes of 16 prompts at 32 heads 262 -> 231 us
 // against one workgroup per (page, head) that transposed element by element
-// through LDS; the E4M3 append of 256 requests 15.3 -> 4.7 us.
+// through LDS; the E4M3 append of 256 requests, 8 heads, 9.8 -> 3.9 us.
 #pragma once
 #include <type_traits>
 
@@ -28,9 +30,21 @@ namespace dopd {
 constexpr int kKvwWaves = 4;  // waves of a page-writer workgroup, consecutive heads of one page
 
 // Calls of at most this many new tokens per request on average take the append
-// writer (256 requests, 8 heads, d 128, kernel time append / pages: one token
-// each 5.4 / 8.7 us, E4M3 4.7 / 8.1; two, E4M3, 6.6 / 8.6; four the pages win).
+// writer (256 requests, d 128, kernel time append / pages: one token each, 8 heads
+// bf16 4.7 / 6.7 us, E4M3 3.9 / 6.4, 32 heads 10.4 / 13.0; two, 6.6 / 7.5, E4M3
+// 5.1 / 7.1, 32 heads 12.8 / 14.3; four the pages win).  The host knows only the
+// sum; one long request among single tokens is no slower for it (255 of one token
+// and one of 257: 5.8 / 6.8, 32 heads 13.3 / 13.4), and with thousands of requests
+// it is faster by the search for a token's request (4095 empty ones and one of
+// 8192: 31 / 186, 32 heads 90 / 710).
 constexpr int kKvwAppendMean = 2;
+
+// Waves of an append workgroup, a K wave and a V wave: V's stores are most of the
+// work, so workgroups of V waves alone fill some CUs while others idle (32 heads,
+// 4095 empty requests and one of 8192 tokens, E4M3: workgroups of four K or four V
+// waves 92 us, of two and two 67, of one and one 64; one token of 32 bf16 heads
+// 3.2, 2.8, 2.6).
+constexpr int kKvaWaves = 2;
 
 // TI: element type of the fresh rows, TO: of the pools (uint16_t, uint32_t, or
 // uint16_t -> uint8_t for E4M3 pools).
@@ -273,22 +287,28 @@ __device__ __forceinline__ int find_token_owner(const int32_t* cu, int nreq, int
   return __builtin_amdgcn_readfirstlane(lo);
 }
 
-// Append writer: workgroup b takes 256 of the 2 x Hkv x (D / EPC) chunks (K's,
-// then V's) of token b / head_groups, counted from the first request's first.
+// Append writer: the waves of a token take 64 16-byte chunks of its K row (even
+// waves) or its V row (odd ones) each; workgroup b holds kKvaWaves waves of token
+// b / head_groups, counted from the first request's first.
 template <typename TI, typename TO, int D>
-__global__ __launch_bounds__(256) void kv_append_kernel(KvWriteArgs<TI, TO> a) {
+__global__ __launch_bounds__(64 * kKvaWaves) void kv_append_kernel(KvWriteArgs<TI, TO> a) {
   using W = PageWrite<TI, TO, D>;
   using Out = typename W::Out;
+  constexpr int EPC = W::EPC;
+  __shared__ __attribute__((aligned(16))) TO s[kKvaWaves][64 * EPC];
+  const int l = lane_id(), wl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   int t = (int)blockIdx.x / a.head_groups;
-  const int i = (int)blockIdx.x % a.head_groups * 256 + (int)threadIdx.x;
-  const int half = a.hkv * W::CPR;
-  const bool is_v = i >= half, on = i < 2 * half;
-  const int j = is_v ? i - half : i;
-  const int h = j / W::CPR, c = j % W::CPR;
+  const int w = (int)blockIdx.x % a.head_groups * kKvaWaves + wl;
+  const int half = a.hkv * W::CPR;  // chunks of a row
+  const bool is_v = w & 1;
+  const int c0 = 64 * (w >> 1), i = c0 + l;
+  if (c0 >= half) return;
+  const int h = i / W::CPR, c = i % W::CPR;
+  const bool on = i < half;
   u32x4 x = {0, 0, 0, 0};
   float scale = 1.f;
   auto row = [&] {
-    x = *reinterpret_cast<const u32x4*>((is_v ? a.v_new : a.k_new) + ((int64_t)t * a.hkv + h) * D + W::EPC * c);
+    x = *reinterpret_cast<const u32x4*>((is_v ? a.v_new : a.k_new) + ((int64_t)t * a.hkv + h) * D + EPC * c);
   };
   if (on) {
     row();  // beside the lengths: nearly every call's rows start at 0
@@ -301,18 +321,25 @@ __global__ __launch_bounds__(256) void kv_append_kernel(KvWriteArgs<TI, TO> a) {
   const int r = find_token_owner(a.cu_new, a.nreq, t);
   const int pos = a.start_pos[r] + (t - a.cu_new[r]);
   const int64_t page = a.page_table[(int64_t)r * a.pt_stride + pos / kPage];
-  if (!on) return;
   const Out y = W::convert(x, W::kE4m3 ? 1.0f / scale : 1.f);
   const int slot = pos % kPage;
-  const int64_t blk = (page * a.hkv + h) * (kPage * D);
   if (!is_v) {
-    __builtin_nontemporal_store(y, reinterpret_cast<Out*>(a.k_pool + blk + slot * D + W::EPC * c));
-  } else {
-    const TO* e = reinterpret_cast<const TO*>(&y);
-    TO* d = a.v_pool + blk + W::EPC * c * kPage + slot;
-#pragma unroll
-    for (int u = 0; u < W::EPC; ++u) d[u * kPage] = e[u];
+    if (on)
+      __builtin_nontemporal_store(y, reinterpret_cast<Out*>(a.k_pool + (page * a.hkv + h) * (kPage * D) +
+                                                            slot * D + EPC * c));
+    return;
   }
+  // V elements lie a page row apart: through this wave's LDS, so that the lanes
+  // of a store take neighbouring dims (a quarter to an eighth of the cache lines
+  // of a store by which each lane writes its own chunk).
+  *reinterpret_cast<Out*>(s[wl] + EPC * l) = y;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  TO* d = a.v_pool + (page * a.hkv * D + c0 * EPC + l) * kPage + slot;
+#pragma unroll
+  for (int u = 0; u < EPC; ++u)
+    if (c0 * EPC + 64 * u < a.hkv * D) d[64 * kPage * u] = s[wl][64 * u + l];  // (a row is whole 64s)
 }
 
 }  // namespace dopd

@@ -83,3 +83,31 @@ def test_rows_before_the_first_request(nreq, before):
         ev[page, :, :, slot] = v[before + r]
     assert np.array_equal(gk.view(np.uint16), ek.view(np.uint16))
     assert np.array_equal(gv.view(np.uint16), ev.view(np.uint16))
+
+
+# One long request among empty or single-token ones: at most two tokens per request
+# on average, so its whole pages are written token by token too.  17 heads of 64
+# are two waves of a row and a part of a third.
+@pytest.mark.parametrize("hkv,d", [(1, 64), (17, 64), (8, 128)])
+@pytest.mark.parametrize("others", [0, 1])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32", "fp8"])
+def test_one_long_request_among_many(dtype, others, hkv, d):
+    rng = np.random.default_rng(5 * hkv + d + others)
+    n = np.full(70, others, np.int32)
+    n[41] = 69
+    start = rng.integers(0, 40, 70).astype(np.int32)
+    pt, num_pages = I.allocate_pages(rng, n + start)
+    cu = I.cu_from_lens(n)
+    fresh = "fp32" if dtype == "fp32" else "bf16"
+    k, v = (I.normal(rng, (int(cu[-1]), hkv, d), fresh) for _ in range(2))
+    shape = G.A.make_shape(hkv, hkv, d, dtype)
+    if dtype == "fp8":
+        kp, vp = (rng.integers(0, 255, s, dtype=np.uint8) for s in ((num_pages, hkv, 16, d), (num_pages, hkv, d, 16)))
+        scale = (0.005 + 0.01 * rng.random(hkv)).astype(np.float32)
+        got = G.gpu_kv_write_fp8(shape, k, v, scale, scale, kp, vp, pt, cu, start)
+        k, v = oracle.e4m3_quantize(k, scale), oracle.e4m3_quantize(v, scale)
+    else:
+        kp, vp = I.empty_pools(num_pages, hkv, d, fresh)
+        got = G.gpu_kv_write(shape, k, v, kp, vp, pt, cu, start)
+    for g, e in zip(got, oracle.kv_write(k, v, kp, vp, pt, cu, start)):
+        assert np.array_equal(g.view(np.uint8), e.view(np.uint8))
