@@ -598,10 +598,10 @@ dopd_status dopd_prefill_paged_attn_fp8(const dopd_attn_shape* s, const void* q,
 extern "C++" {
 namespace {
 
-// Page-writer workgroups of one page: kKvwWaves waves of HW heads each.
+// Page-writer workgroups of one page: kKvwWaves waves of K or V of HW heads each.
 template <typename TI, typename TO>
-int write_head_groups(int hkv, int d) {
-  const int per = dopd::kKvwWaves * (d == 64 ? dopd::PageWrite<TI, TO, 64>::HW : dopd::PageWrite<TI, TO, 128>::HW);
+int write_head_groups(int hkv, int d, bool both = false) {
+  const int per = dopd::kKvwWaves / (both ? 1 : 2) * (d == 64 ? dopd::PageWrite<TI, TO, 64>::HW : dopd::PageWrite<TI, TO, 128>::HW);
   return (hkv + per - 1) / per;
 }
 
@@ -932,8 +932,8 @@ static dopd_status pd_step_impl(const dopd_attn_shape* s, const void* q_dec,
     p.n_dec = p.dec.nwg;
   }
   int64_t pf_blocks = 0;
-  const int groups = kv8 ? write_head_groups<uint16_t, uint8_t>(hkv, d)
-                         : write_head_groups<uint16_t, uint16_t>(hkv, d);
+  const int groups = kv8 ? write_head_groups<uint16_t, uint8_t>(hkv, d, true)
+                         : write_head_groups<uint16_t, uint16_t>(hkv, d, true);
   if (num_pre > 0 && cu_host[num_pre] > 0) {
     dopd_attn_shape sb = *s;  // the prefill reads the bf16 fresh rows
     sb.dtype = DOPD_BF16;

@@ -104,9 +104,10 @@ template <int D>
 __global__ __launch_bounds__(64 * kKvwWaves) void kv_unpack_pages_kernel(UnpackPagesArgs a) {
   using T = uint8_t;
   using W = PageWrite<T, T, D>;
-  __shared__ __attribute__((aligned(16))) uint8_t s[kKvwWaves][W::kLdsBytes];
+  __shared__ __attribute__((aligned(16))) uint8_t s[kKvwWaves / 2][W::kLdsBytes];  // of the V waves
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int h0 = ((int)blockIdx.x % a.head_groups * kKvwWaves + w) * W::HW;
+  const int wi = (int)blockIdx.x % a.head_groups * kKvwWaves + w;  // wave of the page: K's, V's, ..
+  const int h0 = (wi >> 1) * W::HW;
   if (h0 >= a.hkv) return;
   int len_l = 0, req_l = 0;  // this lane's handoff
   auto items = [&](int x) {
@@ -119,11 +120,16 @@ __global__ __launch_bounds__(64 * kKvwWaves) void kv_unpack_pages_kernel(UnpackP
   const int len = __builtin_amdgcn_readlane(len_l, n % 64), r = __builtin_amdgcn_readlane(req_l, n % 64);
   const int np = (len + kPage - 1) / kPage, layer = local / np, pg = local % np;
   const int64_t page = (int64_t)layer * a.num_pages + a.page_table[(int64_t)r * a.pt_stride + pg];
-  const T* k_src = a.in + a.in_off[n] + ((int64_t)layer * 2 * a.hkv * len + (int64_t)pg * kPage) * D;
-  write_page_heads<T, T, D, false>(k_src, k_src + (int64_t)a.hkv * len * D, D, (int64_t)len * D, h0, a.hkv, 0,
-                                   min(kPage, len - pg * kPage), a.k_pool, a.v_pool, page,
-                                   (const float*)nullptr, (const float*)nullptr, (T*)nullptr, (T*)nullptr,
-                                   0, false, s[w]);
+  const int64_t half = (int64_t)a.hkv * len * D;  // elements of a layer's K or V
+  const T* k_src = a.in + a.in_off[n] + layer * 2 * half + (int64_t)pg * kPage * D;
+  const int64_t row_elems = D, head_elems = (int64_t)len * D, page_elems = (int64_t)a.hkv * (kPage * D);
+  const int s1 = min(kPage, len - pg * kPage);
+  if (wi & 1)
+    write_page_rows<T, T, D, false, true>(k_src + half, row_elems, head_elems, h0, a.hkv, 0, s1,
+                                          a.v_pool + page * page_elems, nullptr, (T*)nullptr, 0, false, s[w >> 1]);
+  else
+    write_page_rows<T, T, D, false, false>(k_src, row_elems, head_elems, h0, a.hkv, 0, s1,
+                                           a.k_pool + page * page_elems, nullptr, (T*)nullptr, 0, false, nullptr);
 }
 
 }  // namespace dopd

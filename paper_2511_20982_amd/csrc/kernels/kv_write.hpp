@@ -5,12 +5,13 @@
 // nearest even; codes rounded to nearest even).  Slots of a page outside the
 // written range are never touched.
 //
-// Two mappings.  The page writer gives a wave one page of 16 / CW KV heads (CW
-// chunks of a row per pass: one head, or two bf16 heads at d = 64) and issues all
-// of its 16-byte loads at once; a lane holds 4 tokens
-// of 8 (bf16) or 4 (fp32) dims of V, so the transposition to dim rows is done
-// in registers four tokens at a time and only gathers rows in LDS, privately
-// per wave (no workgroup barrier).  The append writer gives a wave 64 16-byte
+// Two mappings.  The page writer gives a wave K or V of one page of 16 / CW KV
+// heads (CW chunks of a row per pass: one head, or two bf16 heads at d = 64) and
+// issues all of its 16-byte loads at once; a lane holds 4 tokens of 8 (bf16) or 4
+// (fp32) dims of V, so the transposition to dim rows is done in registers four
+// tokens at a time and only gathers rows in LDS, privately per wave (no workgroup
+// barrier).  Slots of a page that is written in part leave in the widest aligned
+// stores that fit.  The append writer gives a wave 64 16-byte
 // chunks of one token's K or V: with one or two tokens per request every page is
 // partial and V is written element by element either way, and what counts is the
 // chain of loads that finds the request and its page, and the cache lines that
@@ -19,7 +20,12 @@
 // HBM-bound at size: E4M3 writes of 16 prompts (318 MB, 8 heads, d 128) 74 ->
 // 62 us (5.1 TB/s), bf16 writes of 16 prompts at 32 heads 262 -> 231 us
 // against one workgroup per (page, head) that transposed element by element
-// through LDS; the E4M3 append of 256 requests, 8 heads, 9.8 -> 3.9 us.
+// through LDS; the E4M3 append of 256 requests, 8 heads, 9.8 -> 3.9 us.  Small
+// calls are bound by one wave's work on one page, hence K and V in waves of their
+// own and the wide stores: 5 prompts of 9-40 tokens, 8 heads, one wave for both and
+// element by element 4.6 us (E4M3 5.6, fp32 5.1; 8 chunks of 32 tokens 4.5, 5.3,
+// 5.2), now 3.7 (3.5, 4.2; 3.5, 3.5, 4.6), the workgroup per (page, head) 3.4 (3.6,
+// 3.8; 3.5, 3.5, 4.0).
 #pragma once
 #include <type_traits>
 
@@ -27,7 +33,7 @@
 
 namespace dopd {
 
-constexpr int kKvwWaves = 4;  // waves of a page-writer workgroup, consecutive heads of one page
+constexpr int kKvwWaves = 4;  // waves of a page-writer workgroup: K's and V's of consecutive heads of one page
 
 // Calls of at most this many new tokens per request on average take the append
 // writer (256 requests, d 128, kernel time append / pages: one token each, 8 heads
@@ -88,18 +94,44 @@ __device__ __forceinline__ u32x4 load_chunk(const uint8_t* p) { return *reinterp
 __device__ __forceinline__ u32x4 load_chunk(const uint16_t* p) { return *reinterpret_cast<const u32x4_a2*>(p); }
 __device__ __forceinline__ u32x4 load_chunk(const uint32_t* p) { return *reinterpret_cast<const u32x4_a4*>(p); }
 
-// Rows [s0, s1) of page `page` for the HW heads from h0 (those below hkv):
-// k_src / v_src point at KV head 0 of the row that goes to slot s0; rows are
-// row_elems apart, heads head_elems.  With pk /
-// pv (the handoff block's rows of slot 0, KV head 0; head h follows
-// pack_head elements later) the rows are written there too.  s: the wave's
-// kLdsBytes of LDS, 16-byte aligned.  Every lane of the wave takes part.
-template <typename TI, typename TO, int D, bool PACK>
-__device__ __forceinline__ void write_page_heads(const TI* k_src, const TI* v_src, int64_t row_elems,
-                                                 int64_t head_elems, int h0, int hkv, int s0, int s1, TO* k_pool,
-                                                 TO* v_pool, int64_t page, const float* k_scale,
-                                                 const float* v_scale, TO* pk, TO* pv,
-                                                 int64_t pack_head, bool pack_aligned, uint8_t* s) {
+template <int N>
+using Slots = std::integral_constant<int, N>;
+
+// N slots of each of a lane's PL pieces of SPP slots, at slot `at`; none where
+// !on, and none wider than a piece.
+template <typename TO, int N, int SPP, int PL>
+struct SlotStores {
+  static constexpr int B = N * (int)sizeof(TO);
+  using Word = std::conditional_t<B == 1, uint8_t, std::conditional_t<B == 2, uint16_t,
+               std::conditional_t<B == 4, uint32_t, std::conditional_t<B == 8, u32x2, u32x4>>>>;
+  bool on;
+  int at;
+  Word x[PL];
+  // Takes N slots at lo, if `take`, and moves lo past them.
+  template <class PieceFn>
+  __device__ __forceinline__ SlotStores(bool take, int& lo, PieceFn piece) : on(N <= SPP && take) {
+    if constexpr (N <= SPP) {
+      at = on ? lo : 0;
+      lo += on ? N : 0;
+#pragma unroll
+      for (int k = 0; k < PL; ++k) x[k] = *reinterpret_cast<const Word*>(piece(k) + at * sizeof(TO));
+    }
+  }
+  __device__ __forceinline__ void store(TO* d, int k) const {
+    if constexpr (N <= SPP) *reinterpret_cast<Word*>(d + at) = x[k];
+  }
+};
+
+// Rows [s0, s1) of one page, K's or V's, for the HW heads from h0 (those below
+// hkv): src points at KV head 0 of the row that goes to slot s0; rows are
+// row_elems apart, heads head_elems.  dst: the page in the pool, KV head 0.  With
+// pack (the handoff block's row of slot 0, KV head 0; head h follows pack_head
+// elements later) the rows are written there too.  s: the wave's kLdsBytes of
+// LDS (V's only), 16-byte aligned.  Every lane of the wave takes part.
+template <typename TI, typename TO, int D, bool PACK, bool IS_V>
+__device__ __forceinline__ void write_page_rows(const TI* src, int64_t row_elems, int64_t head_elems, int h0,
+                                                int hkv, int s0, int s1, TO* dst, const float* scale, TO* pack,
+                                                int64_t pack_head, bool pack_aligned, uint8_t* s) {
   using W = PageWrite<TI, TO, D>;
   using Out = typename W::Out;
   constexpr int EPC = W::EPC, CW = W::CW, NP = W::NP, HW = W::HW, RB = W::RB;
@@ -111,59 +143,48 @@ __device__ __forceinline__ void write_page_heads(const TI* k_src, const TI* v_sr
   // K: chunk u is token 4u + tq (whole rows in a row); V: token 4tq + u (four
   // tokens of a dim in one lane).  Tokens outside [s0, s1) read the nearest
   // one inside, so that no load waits behind a branch.
-  auto row = [&](int t) { return (min(max(t, s0), s1 - 1) - s0) * row_elems + col; };
-  u32x4 kx[NP][4], vx[NP][4];
+  auto token = [&](int u) { return IS_V ? 4 * tq + u : 4 * u + tq; };
+  u32x4 x[NP][4];
 #pragma unroll
   for (int p = 0; p < NP; ++p)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      kx[p][u] = load_chunk(k_src + row(4 * u + tq) + EPC * CW * p);
-      vx[p][u] = load_chunk(v_src + row(4 * tq + u) + EPC * CW * p);
-    }
-  float kinv = 1.f, vinv = 1.f;
-  if constexpr (W::kE4m3) {
-    kinv = 1.0f / k_scale[on ? h : h0];
-    vinv = 1.0f / v_scale[on ? h : h0];
-  }
-  TO* kdst = k_pool + (page * hkv + h) * (kPage * D);
-  auto pack = [&](TO* base, int slot, int p, Out x) {
-    TO* d = base + h * pack_head + slot * D + EPC * (c + CW * p);
-    if (pack_aligned) {
-      __builtin_nontemporal_store(x, reinterpret_cast<Out*>(d));
+    for (int u = 0; u < 4; ++u)
+      x[p][u] = load_chunk(src + (min(max(token(u), s0), s1 - 1) - s0) * row_elems + col + EPC * CW * p);
+  float inv = 1.f;
+  if constexpr (W::kE4m3) inv = 1.0f / scale[on ? h : h0];
+  // Streaming stores here and below: the rows are not read again soon, and they
+  // leave the caches now instead of being written back while the decode that
+  // follows streams the pools.
+  auto row_out = [&](TO* d, bool aligned, Out y) {
+    if (aligned) {
+      __builtin_nontemporal_store(y, reinterpret_cast<Out*>(d));
     } else {
-      const TO* e = reinterpret_cast<const TO*>(&x);
+      const TO* e = reinterpret_cast<const TO*>(&y);
 #pragma unroll
       for (int i = 0; i < EPC; ++i) d[i] = e[i];
     }
   };
   const bool full = s0 == 0 && s1 == kPage;
-  // Rows out (and in the pack): whole pages of heads that are all there store
-  // without a test, so that no load sinks behind one.
+  // Rows out (K's to the page, and either to the pack): whole pages of heads that
+  // are all there store without a test, so that no load sinks behind one.
   Out v[NP][4];
   auto rows_out = [&](auto whole) {
 #pragma unroll
     for (int p = 0; p < NP; ++p)
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int tk = 4 * u + tq, tv = 4 * tq + u;
-        const Out x = W::convert(kx[p][u], kinv);
-        v[p][u] = W::convert(vx[p][u], vinv);
-        if (whole || (on && tk >= s0 && tk < s1)) {
-          // Streaming stores here and below: the rows are not read again soon,
-          // and they leave the caches now instead of being written back while
-          // the decode that follows streams the pools.
-          __builtin_nontemporal_store(x, reinterpret_cast<Out*>(kdst + tk * D + EPC * (c + CW * p)));
-          if constexpr (PACK) {
-            if (pk) pack(pk, tk, p, x);
-          }
-        }
+        const int t = token(u), col_out = t * D + EPC * (c + CW * p);
+        v[p][u] = W::convert(x[p][u], inv);
+        if (!(whole || (on && t >= s0 && t < s1))) continue;
+        if constexpr (!IS_V) row_out(dst + (int64_t)h * (kPage * D) + col_out, true, v[p][u]);
         if constexpr (PACK) {
-          if (pv && (whole || (on && tv >= s0 && tv < s1))) pack(pv, tv, p, v[p][u]);
+          if (pack) row_out(pack + h * pack_head + col_out, pack_aligned, v[p][u]);
         }
       }
   };
   if (full && h0 + HW <= hkv) rows_out(std::true_type{});
   else rows_out(std::false_type{});
+  if constexpr (!IS_V) return;
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     // Dim i of the chunk: its four tokens side by side, into row e of the head.
@@ -202,24 +223,48 @@ __device__ __forceinline__ void write_page_heads(const TI* k_src, const TI* v_sr
   constexpr int PPR = RB / 16;       // 16-byte pieces of a dim row
   constexpr int PIECES = D * PPR;    // of a head
   constexpr int SPP = 16 / (int)sizeof(TO);  // slots of a piece
-  TO* vdst = v_pool + (page * hkv + h0) * (kPage * D);
+  constexpr int PL = HW * PIECES / 64;  // pieces of a lane
+  const int run = l % PPR;
+  auto head_of = [&](int k) { return (l + 64 * k) / PIECES; };
+  auto row_of = [&](int k) { return (l + 64 * k) % PIECES / PPR; };
+  auto piece = [&](int k) {
+    const int e = row_of(k);
+    return s + (head_of(k) * W::ROWS + e + e / EPC) * RB + 16 * run;
+  };
+  auto at = [&](int k) { return dst + (int64_t)(h0 + head_of(k)) * (kPage * D) + row_of(k) * kPage + run * SPP; };
+  if (full) {
 #pragma unroll
-  for (int k = 0; k < HW * PIECES / 64; ++k) {
-    const int i = l + 64 * k;
-    const int hs = i / PIECES, e = i % PIECES / PPR, run = i % PPR;
-    if (h0 + hs >= hkv) continue;
-    const u32x4 x = *reinterpret_cast<const u32x4*>(s + (hs * W::ROWS + e + e / EPC) * RB + 16 * run);
-    TO* d = vdst + (int64_t)hs * (kPage * D) + e * kPage + run * SPP;
-    if (full) {
-      __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(d));
-    } else {
-      const TO* xe = reinterpret_cast<const TO*>(&x);
+    for (int k = 0; k < PL; ++k)
+      if (h0 + head_of(k) < hkv)
+        __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(piece(k)), reinterpret_cast<u32x4*>(at(k)));
+  } else {
+    // Slots [lo, hi) of this lane's pieces, in the widest aligned stores that hold
+    // no other slot: the run up to an aligned slot, then down from the widest.
+    // Each half reads LDS for all of its stores before the first of them.
+    int lo = max(s0 - run * SPP, 0);
+    const int hi = min(s1 - run * SPP, SPP);
+    auto up = [&](auto n) { return SlotStores<TO, n, SPP, PL>{(lo & n) != 0 && lo + n <= hi, lo, piece}; };
+    auto down = [&](auto n) { return SlotStores<TO, n, SPP, PL>{lo + n <= hi, lo, piece}; };
+    auto put = [&](const auto& y) {
+      if (y.on) {
 #pragma unroll
-      for (int t = 0; t < SPP; ++t) {
-        const int slot = run * SPP + t;
-        if (slot >= s0 && slot < s1) d[t] = xe[t];
+        for (int k = 0; k < PL; ++k)
+          if (h0 + head_of(k) < hkv) y.store(at(k), k);
       }
+    };
+    if (s0 != 0) {
+      const auto a = up(Slots<1>{});
+      const auto b = up(Slots<2>{});
+      const auto c4 = up(Slots<4>{});
+      const auto d = up(Slots<8>{});
+      put(a), put(b), put(c4), put(d);
     }
+    const auto a = down(Slots<16>{});
+    const auto b = down(Slots<8>{});
+    const auto c4 = down(Slots<4>{});
+    const auto d = down(Slots<2>{});
+    const auto e = down(Slots<1>{});
+    put(a), put(b), put(c4), put(d), put(e);
   }
 }
 
@@ -238,12 +283,13 @@ struct KvWriteArgs {
   int head_groups;            // workgroups of a page (page writer) or of a token (append writer)
 };
 
-// Page writer: workgroup b takes heads kKvwWaves * HW * (b % head_groups) .. of
-// the (b / head_groups)-th touched page.
+// Page writer: workgroup b takes waves kKvwWaves * (b % head_groups) .. of the
+// (b / head_groups)-th touched page; wave i of a page writes K (even) or V (odd)
+// of heads i / 2 * HW ..
 template <typename TI, typename TO, int D>
 __global__ __launch_bounds__(64 * kKvwWaves) void kv_write_kernel(KvWriteArgs<TI, TO> a) {
   using W = PageWrite<TI, TO, D>;
-  __shared__ __attribute__((aligned(16))) uint8_t s[kKvwWaves][W::kLdsBytes];
+  __shared__ __attribute__((aligned(16))) uint8_t s[kKvwWaves / 2][W::kLdsBytes];  // of the V waves
   // Touched logical pages of request r: those holding positions [start, start + n).
   int cu_l = 0, n_l = 0, st_l = 0;  // this lane's request
   auto touched = [&](int rr) {
@@ -254,7 +300,8 @@ __global__ __launch_bounds__(64 * kKvwWaves) void kv_write_kernel(KvWriteArgs<TI
     return n_l > 0 ? (st_l + n_l - 1) / kPage - st_l / kPage + 1 : 0;
   };
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int h0 = ((int)blockIdx.x % a.head_groups * kKvwWaves + w) * W::HW;
+  const int wi = (int)blockIdx.x % a.head_groups * kKvwWaves + w;  // wave of the page
+  const int h0 = (wi >> 1) * W::HW;
   if (h0 >= a.hkv) return;
   int r, local;
   if (!find_owner((int)blockIdx.x / a.head_groups, a.nreq, touched, r, local)) return;
@@ -266,9 +313,15 @@ __global__ __launch_bounds__(64 * kKvwWaves) void kv_write_kernel(KvWriteArgs<TI
   const int64_t page = a.page_table[(int64_t)r * a.pt_stride + lp];
   const int64_t row_elems = (int64_t)a.hkv * D;
   const int64_t src = ((int64_t)row0 + (p_lo - start)) * row_elems;
-  write_page_heads<TI, TO, D, false>(a.k_new + src, a.v_new + src, row_elems, D, h0, a.hkv,
-                                     p_lo - lp * kPage, p_hi - lp * kPage, a.k_pool, a.v_pool, page,
-                                     a.k_scale, a.v_scale, (TO*)nullptr, (TO*)nullptr, 0, false, s[w]);
+  const int64_t page_elems = (int64_t)a.hkv * (kPage * D);
+  if (wi & 1)
+    write_page_rows<TI, TO, D, false, true>(a.v_new + src, row_elems, D, h0, a.hkv, p_lo - lp * kPage,
+                                            p_hi - lp * kPage, a.v_pool + page * page_elems, a.v_scale,
+                                            (TO*)nullptr, 0, false, s[w >> 1]);
+  else
+    write_page_rows<TI, TO, D, false, false>(a.k_new + src, row_elems, D, h0, a.hkv, p_lo - lp * kPage,
+                                             p_hi - lp * kPage, a.k_pool + page * page_elems, a.k_scale,
+                                             (TO*)nullptr, 0, false, nullptr);
 }
 
 // The request whose rows hold token t: the last r with cu[r] <= t, found by

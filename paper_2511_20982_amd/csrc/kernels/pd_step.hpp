@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void pd_step_kernel(PdStepArgs s) {
   } else if (b >= s.wp_first && b < s.wp_first + s.n_wp) {
     const int w = threadIdx.x >> 6;
     uint16_t* rows = w == 0 ? sK0 : w == 1 ? sK1 : w == 2 ? sV0 : sV1;
-    kv_write_pack_workgroup<PoolT, D>(s.wp, b - s.wp_first, reinterpret_cast<uint8_t*>(rows));
+    kv_write_pack_workgroup<PoolT, D, true>(s.wp, b - s.wp_first, reinterpret_cast<uint8_t*>(rows));
   }
 }
 

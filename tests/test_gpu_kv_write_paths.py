@@ -111,3 +111,28 @@ def test_one_long_request_among_many(dtype, others, hkv, d):
         got = G.gpu_kv_write(shape, k, v, kp, vp, pt, cu, start)
     for g, e in zip(got, oracle.kv_write(k, v, kp, vp, pt, cu, start)):
         assert np.array_equal(g.view(np.uint8), e.view(np.uint8))
+
+
+# Every range of slots of a page, each the one touched page of a request: the slots
+# of a dim row leave in pieces of 1 to 16, and none outside the range is touched.
+@pytest.mark.parametrize("hkv,d", [(3, 64), (2, 128)])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32", "fp8"])
+def test_every_range_of_a_page(dtype, hkv, d):
+    rng = np.random.default_rng(hkv + d)
+    start, end = np.array([(a, b) for a in range(16) for b in range(a + 1, 17)], np.int32).T
+    n = end - start
+    pt, num_pages = I.allocate_pages(rng, end)
+    cu = I.cu_from_lens(n)
+    fresh = "fp32" if dtype == "fp32" else "bf16"
+    k, v = (I.normal(rng, (int(cu[-1]), hkv, d), fresh) for _ in range(2))
+    shape = G.A.make_shape(hkv, hkv, d, dtype)
+    if dtype == "fp8":
+        kp, vp = (rng.integers(0, 255, s, dtype=np.uint8) for s in ((num_pages, hkv, 16, d), (num_pages, hkv, d, 16)))
+        scale = (0.005 + 0.01 * rng.random(hkv)).astype(np.float32)
+        got = G.gpu_kv_write_fp8(shape, k, v, scale, scale, kp, vp, pt, cu, start)
+        k, v = oracle.e4m3_quantize(k, scale), oracle.e4m3_quantize(v, scale)
+    else:
+        kp, vp = I.empty_pools(num_pages, hkv, d, fresh)
+        got = G.gpu_kv_write(shape, k, v, kp, vp, pt, cu, start)
+    for g, e in zip(got, oracle.kv_write(k, v, kp, vp, pt, cu, start)):
+        assert np.array_equal(g.view(np.uint8), e.view(np.uint8))

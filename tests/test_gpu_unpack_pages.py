@@ -4,6 +4,7 @@ one byte only, bit for bit against a plain index map."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_2511_20982_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
@@ -38,3 +39,19 @@ def test_unpack_e4m3(hkv, d, layers, shift):
     shape = G.A.make_shape(hkv, hkv, d, "fp8")
     gk, gv = G.gpu_unpack(shape, buf, offs[:-1].copy(), req, lens, kp, vp, layers, pt)
     assert np.array_equal(gk, ek) and np.array_equal(gv, ev)
+
+
+@pytest.mark.parametrize("hkv,d", [(5, 64), (3, 128)])
+def test_unpack_e4m3_last_pages(hkv, d):
+    """Last pages of 1 to 16 tokens."""
+    rng = np.random.default_rng(hkv + d)
+    lens = np.arange(1, 34, dtype=np.int32)
+    pt, num_pages = I.allocate_pages(rng, lens)
+    offs = I.handoff_offsets(lens, 2, hkv, d)
+    buf = rng.integers(0, 256, int(offs[-1]), dtype=np.uint8)
+    kp = rng.integers(0, 256, (2, num_pages, hkv, 16, d), dtype=np.uint8)
+    vp = rng.integers(0, 256, (2, num_pages, hkv, d, 16), dtype=np.uint8)
+    req = np.arange(len(lens), dtype=np.int32)
+    got = G.gpu_unpack(G.A.make_shape(hkv, hkv, d, "fp8"), buf, offs[:-1].copy(), req, lens, kp, vp, 2, pt)
+    for g, e in zip(got, oracle.unpack(buf, offs, req, lens, kp, vp, 2, pt)):
+        assert np.array_equal(g, e)
