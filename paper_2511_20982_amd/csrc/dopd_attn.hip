@@ -1101,9 +1101,12 @@ dopd_status dopd_kv_unpack_from_handoff(const dopd_attn_shape* s, int32_t num_la
   if (zdim > 65535 || num_handoff > 65535) return DOPD_ERR_INVALID_SHAPE;
   hipStream_t strm = as_stream(stream);
   const int hkv = s->num_kv_heads;
+  int64_t pages = 0, tokens = 0;
+  for (int32_t n = 0; n < num_handoff; ++n) {
+    pages += (seq_lens_host[n] + dopd::kPage - 1) / dopd::kPage;
+    tokens += seq_lens_host[n];
+  }
   if (s->dtype == DOPD_FP8_E4M3) {
-    int64_t pages = 0;
-    for (int32_t n = 0; n < num_handoff; ++n) pages += (seq_lens_host[n] + dopd::kPage - 1) / dopd::kPage;
     const int groups = write_head_groups<uint8_t, uint8_t>(hkv, s->head_dim);
     const int64_t blocks = pages * num_layers * groups;
     if (blocks > INT32_MAX) return DOPD_ERR_INVALID_SHAPE;
@@ -1119,21 +1122,23 @@ dopd_status dopd_kv_unpack_from_handoff(const dopd_attn_shape* s, int32_t num_la
   }
   const dim3 grid((unsigned)((max_len + dopd::kPage - 1) / dopd::kPage), (unsigned)num_handoff,
                   (unsigned)zdim);
-  auto launch = [&](auto type_tag) {
+  auto launch = [&](auto type_tag, auto stream_loads) {
     using T = decltype(type_tag);
     const T* src = static_cast<const T*>(in);
     T *kp = static_cast<T*>(k_pool), *vp = static_cast<T*>(v_pool);
     if (s->head_dim == 64)
-      hipLaunchKernelGGL((dopd::kv_unpack_kernel<T, 64>), grid, dim3(256), 0, strm, src, in_offsets,
+      hipLaunchKernelGGL((dopd::kv_unpack_kernel<T, 64, stream_loads>), grid, dim3(256), 0, strm, src, in_offsets,
                          req_ids, seq_lens, kp, vp, num_pages, pt, pt_stride, hkv);
     else
-      hipLaunchKernelGGL((dopd::kv_unpack_kernel<T, 128>), grid, dim3(256), 0, strm, src, in_offsets,
+      hipLaunchKernelGGL((dopd::kv_unpack_kernel<T, 128, stream_loads>), grid, dim3(256), 0, strm, src, in_offsets,
                          req_ids, seq_lens, kp, vp, num_pages, pt, pt_stride, hkv);
   };
-  if (s->dtype == DOPD_BF16)
-    launch(uint16_t{});
-  else
-    launch(uint32_t{});
+  const bool bf16 = s->dtype == DOPD_BF16;
+  const bool large = tokens > dopd::kUnpackStreamBytes / (zdim * s->head_dim * (bf16 ? 2 : 4));
+  if (bf16 && large) launch(uint16_t{}, std::true_type{});
+  else if (bf16) launch(uint16_t{}, std::false_type{});
+  else if (large) launch(uint32_t{}, std::true_type{});
+  else launch(uint32_t{}, std::false_type{});
   return launch_status();
 }
 

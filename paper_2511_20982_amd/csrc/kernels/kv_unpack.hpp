@@ -4,18 +4,28 @@
 //
 // bf16 and fp32 pools: one workgroup per (page, handoff, layer*2*Hkv + kv*Hkv +
 // head); K rows are copied as they are, V rows are transposed to the dim-major
-// page block through LDS.  E4M3 pools: the page writer's mapping, a wave for
-// the K and V of one (handoff, layer, page) and HW heads, which turns V four
-// tokens at a time in registers.  HBM-bound at size.  Measured, workgroup per
-// block / wave per page: 8 requests of 300-900 tokens, 8 heads, 20 layers, E4M3
-// 119 / 79 us (16 one-byte LDS reads a V run are what it saves); 28 layers of 4
-// bf16 heads 91 / 98 us (a wave's 4 + 4 loads lie in eight streams).
+// page block through LDS.  E4M3 pools: the page writer's mapping, a wave for the
+// K or V of one (handoff, layer, page) and HW heads, which turns V four tokens at
+// a time in registers (16 one-byte LDS reads a V run are what it saves).
+// HBM-bound at size.  Measured, workgroup per block / wave per page, 8 requests of
+// 300-900 tokens, 20 layers, buffer from HBM: E4M3 8 heads of 128 112 / 79 us, 32
+// heads 434 / 309, 8 heads of 64 100 / 41; bf16 of d 128 4 heads 67 / 78, 8 heads
+// 135 / 155, 32 heads 577 / 609; fp32 8 heads of 128 273 / 317, of 64 134 / 156.
+// (bf16 of d 64, 104 / 78 and 32 heads 405 / 309, would gain from the second.)
 #pragma once
 #include "kv_write.hpp"
 
 namespace dopd {
 
-template <typename T, int D>
+// Buffers of more than this are read with streaming loads, which leave the caches
+// to the lines on their way out.  A smaller one, with the pages written meanwhile,
+// fits the 256 MiB cache that it came in through and can be read from there (plain
+// / streaming, bf16, 32 heads of 128: 81 MB from that cache 23.5 / 30.2 us, from
+// HBM 32.3 / 29.8; pack and unpack of 240 MB 174.3 / 172.3, unpack of 1.6 GB 588 /
+// 578; fp32, 403 MB 141 / 132).
+constexpr int64_t kUnpackStreamBytes = (int64_t)128 << 20;
+
+template <typename T, int D, bool STREAM>
 __global__ __launch_bounds__(256) void kv_unpack_kernel(
     const T* __restrict__ in, const int64_t* __restrict__ in_off, const int32_t* __restrict__ req_ids,
     const int32_t* __restrict__ seq_lens, T* __restrict__ k_pool, T* __restrict__ v_pool,
@@ -36,6 +46,10 @@ __global__ __launch_bounds__(256) void kv_unpack_kernel(
   const int64_t lpage = (int64_t)layer * num_pages + page;
   const T* src = in + in_off[n] + ((((int64_t)layer * 2 + kv) * hkv + h) * len + (int64_t)pg * kPage) * D;
   const bool aligned = ((reinterpret_cast<uintptr_t>(src) & 15) == 0);
+  auto chunk = [&](int i) {
+    const u32x4* p = reinterpret_cast<const u32x4*>(src) + i;
+    return STREAM ? __builtin_nontemporal_load(p) : *p;
+  };
 
   if (kv == 0) {
     T* dst = k_pool + (lpage * hkv + h) * kPage * D;
@@ -43,8 +57,7 @@ __global__ __launch_bounds__(256) void kv_unpack_kernel(
       // streaming stores (here and below): the pages leave the caches now,
       // not as write-back during the kernels that follow
       for (int i = tid; i < nvalid * CPR; i += 256)
-        __builtin_nontemporal_store(__builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src) + i),
-                                    reinterpret_cast<u32x4*>(dst) + i);
+        __builtin_nontemporal_store(chunk(i), reinterpret_cast<u32x4*>(dst) + i);
     } else {
       for (int i = tid; i < nvalid * D; i += 256) dst[i] = src[i];
     }
@@ -54,7 +67,7 @@ __global__ __launch_bounds__(256) void kv_unpack_kernel(
   if (aligned) {
     for (int i = tid; i < nvalid * CPR; i += 256) {
       const int t = i / CPR, c = i % CPR;
-      *reinterpret_cast<u32x4*>(&s_v[t * TP + c * kEl]) = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src) + i);
+      *reinterpret_cast<u32x4*>(&s_v[t * TP + c * kEl]) = chunk(i);
     }
   } else {
     for (int i = tid; i < nvalid * D; i += 256) s_v[(i / D) * TP + i % D] = src[i];

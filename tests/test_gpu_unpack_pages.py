@@ -55,3 +55,32 @@ def test_unpack_e4m3_last_pages(hkv, d):
     got = G.gpu_unpack(G.A.make_shape(hkv, hkv, d, "fp8"), buf, offs[:-1].copy(), req, lens, kp, vp, 2, pt)
     for g, e in zip(got, oracle.unpack(buf, offs, req, lens, kp, vp, 2, pt)):
         assert np.array_equal(g, e)
+
+
+@pytest.mark.parametrize("dtype,hkv,d,shift", [("bf16", 8, 128, 0), ("bf16", 8, 128, 3), ("fp32", 8, 64, 0)])
+def test_unpack_of_a_large_buffer(dtype, hkv, d, shift):
+    """Buffers above 128 MiB are read with other loads; compared on the GPU."""
+    import torch
+
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    size, t = (2, torch.int16) if dtype == "bf16" else (4, torch.int32)
+    layers = 9
+    lens = np.array([1, 2049, 0, 2100], np.int32)
+    offs = I.handoff_offsets(lens, layers, hkv, d) + shift
+    assert (offs[-1] - shift) * size > 128 << 20
+    pt, num_pages = I.allocate_pages(np.random.default_rng(8), np.maximum(lens, 1))
+    rand = lambda *s: torch.randint(-2 ** 15, 2 ** 15, s, dtype=t, device="cuda", generator=gen)  # noqa: E731
+    buf = rand(int(offs[-1]))
+    kp, vp = rand(layers, num_pages, hkv, 16, d), rand(layers, num_pages, hkv, d, 16)
+    ek, ev = kp.clone(), vp.clone()
+    for r, n in enumerate(lens):
+        x = buf[offs[r]:offs[r] + layers * 2 * hkv * int(n) * d].view(layers, 2, hkv, int(n), d)
+        for i in range((int(n) + 15) // 16):
+            rows = x[:, :, :, 16 * i:16 * (i + 1)]
+            ek[:, pt[r, i], :, :rows.shape[3]] = rows[:, 0]
+            ev[:, pt[r, i], :, :, :rows.shape[3]] = rows[:, 1].transpose(-1, -2)
+    dev = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    G.A.dopd_kv_unpack_from_handoff(G.A.make_shape(hkv, hkv, d, dtype), layers, buf, dev(offs[:-1].copy()),
+                                    dev(np.arange(4, dtype=np.int32)), dev(lens), lens, 4, kp, vp, num_pages,
+                                    dev(pt), pt.shape[1])
+    assert torch.equal(kp, ek) and torch.equal(vp, ev)
