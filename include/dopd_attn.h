@@ -320,9 +320,9 @@ dopd_status dopd_decode_attn(const dopd_attn_shape* shape, const void* q, const 
  * (exactly) for the same MFMA path; the K scale multiplies the softmax scale
  * and the V scale the output, in fp32.  Same number of
  * shares, workspace (dopd_decode_workspace_size with the same shape) and
- * split_tokens rules (a share counts the start of a context as more of its
- * tokens, which take half the time here);
- * half the bytes of the bf16 cache per token.
+ * split_tokens rules (with the automatic split of a call that fills the machine a
+ * share counts the start of a context as more of its tokens, which take half the
+ * time here); half the bytes of the bf16 cache per token.
  */
 dopd_status dopd_decode_attn_fp8(const dopd_attn_shape* shape, const void* q,
                                  const void* k_pool, const void* v_pool, const float* k_scale,

@@ -111,8 +111,8 @@ dopd_status scratch_address(void** ptr) {
 // ---- decode planning --------------------------------------------------------
 constexpr int kMaxGroupBf16 = 16;   // query heads per KV head handled by one decode wave
 
-// The decode's layout: the start of a segment takes a fixed time, so it counts
-// as more pairs where a pair is fewer bytes (measured, 8 / 12 / 16 / 20 units:
+// The decode's layout: the start of a segment takes a fixed time, so in calls that
+// fill the machine it counts as more pairs where a pair is fewer bytes (measured, 8 / 12 / 16 / 20 units:
 // E4M3 d 128, 256 mixed contexts 234 / 228 / 229 / 233 us; E4M3 d 64, 100 mixed
 // contexts 63 / 58 / 56.5 / 58 us; bf16 d 64 and d 128 are best at 8).
 dopd::DecodeShape decode_shape(const dopd_attn_shape* s) {
@@ -191,8 +191,9 @@ dopd_status plan_decode_bf16(const dopd_attn_shape* s, const void* q, const void
                              const dopd::DecodeShape& ds, dopd::DecodeArgs* a_out,
                              DecodeMergePlan* merge_out) {
   const int hkv = s->num_kv_heads, hq = s->num_q_heads, d = s->head_dim;
-  const int64_t total = dopd::decode_total_units(ctx_host, nreq, hkv, ds.seg);
-  if (total > INT32_MAX / 2) return DOPD_ERR_INVALID_SHAPE;
+  const int seg = dopd::decode_seg(ctx_host, nreq, hkv, split_tokens, machine_shape(), ds);
+  const int64_t total = dopd::decode_total_units(ctx_host, nreq, hkv, seg);
+  if (total > dopd::kDecMaxUnits) return DOPD_ERR_INVALID_SHAPE;
   const dopd::DecodeLayout L = dopd::decode_layout(hq / hkv, hkv, d, ctx_host, nreq,
                                                    split_tokens, machine_shape(), ds);
   const int64_t nwg = L.nwg;
@@ -201,11 +202,11 @@ dopd_status plan_decode_bf16(const dopd_attn_shape* s, const void* q, const void
   if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return DOPD_ERR_INVALID_SHAPE;
   char* ws = static_cast<char*>(workspace);
   merge_out->count = dopd::decode_merge_list(ctx_host, nreq, hkv, total, nwg,
-                                              merge_out->list.item, dopd::kMergeListMax, ds.seg);
+                                              merge_out->list.item, dopd::kMergeListMax, seg);
   merge_out->list.n = std::max(0, merge_out->count);
   merge_out->needed = merge_out->count > 0 ||
                       (merge_out->count < 0 &&
-                       dopd::decode_needs_merge(ctx_host, nreq, hkv, total, nwg, ds.seg));
+                       dopd::decode_needs_merge(ctx_host, nreq, hkv, total, nwg, seg));
   dopd::DecodeArgs& a = *a_out;
   a.q = (const uint16_t*)q;
   a.k_pool = k_pool;
@@ -224,7 +225,7 @@ dopd_status plan_decode_bf16(const dopd_attn_shape* s, const void* q, const void
   a.hkv = hkv;
   a.total_units = (int)total;
   a.nwg = (int)nwg;
-  a.seg = ds.seg;
+  a.seg = seg;
   a.scale_log2 = s->softmax_scale * dopd::kLog2e;
   return DOPD_OK;
 }

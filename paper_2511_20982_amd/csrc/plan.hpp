@@ -29,6 +29,7 @@ constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // tokens); (r, c) is a span of seg + pairs work units, spans laid out r-major
 // then c; workgroup b takes units [b * total / nwg, (b+1) * total / nwg).
 constexpr int kDecSegCost = 8;          // work units of a segment start, in bf16 pairs
+constexpr int64_t kDecMaxUnits = INT32_MAX / 2;  // of a call (the kernels count them in an int)
 constexpr int kDecMaxSplitTokens = 4096;
 constexpr int64_t kDecMinPairsPerWg = 4;  // one pair per wave at least
 
@@ -70,13 +71,32 @@ inline int64_t decode_nwg(int64_t total_units, int32_t split_tokens, const Machi
                                                   kDecMinPairsPerWg));
 }
 
+// Work units of a segment start in a call's partition: ds.seg where the call fills
+// the machine.  Smaller calls have one slice per kDecMinPairsPerWg units, counted
+// with kDecSegCost, one pair a wave: heavier starts would make it two (E4M3, d 64,
+// one request of 1000 tokens, 8 KV heads, 8.5 us against 7.7).  An explicit
+// split_tokens counts kDecSegCost too, as do totals that would not fit an int.
+inline int decode_seg(const int32_t* ctx, int32_t n, int hkv, int32_t split_tokens, const MachineShape& m,
+                      const DecodeShape& ds) {
+  const int64_t nwg = decode_nwg(decode_total_units(ctx, n, hkv), split_tokens, m, ds.quarter_wgs);
+  if (split_tokens > 0 || nwg < decode_slots(m, ds.quarter_wgs)) return kDecSegCost;
+  return decode_total_units(ctx, n, hkv, ds.seg) <= kDecMaxUnits ? ds.seg : kDecSegCost;
+}
+
 // Does a call with the automatic partition run one workgroup of
 // kDecDirectWaves waves per whole (r, c) instead (no partials, no second
-// kernel)?  Steps are pairs one wave takes one after the other, about 2.2 us
-// each in a light call; the partition's merge costs about two of them.  More
-// (r, c) than CUs would take turns.  Measured, partition / direct, 8 KV heads:
-// 16 requests of 500 tokens 15.7 / 11.6 us, 32 of 500 21.4 / 14.8, 32 of 2000
-// 56 / 48, 4 of 1000 15.2 / 15.6, 16 of 2000 33.6 / 35.5, 1 of 2000 11.4 / 22.9.
+// kernel)?  A route's steps are the pairs one of its waves takes one after the
+// other: of the longest context here, of a slice and its segment starts (ds.seg
+// units each) in the partition, which is charged one more, for its merge, where it
+// has more than one.  More (r, c) than CUs would take turns.  Measured, partition /
+// direct, 8 KV heads of 128, pages from HBM, * the route taken:
+//   bf16  16 requests of 200 tokens 14.0 / 9.3* us, 4 of 500 10.6* / 10.4, 16 of 500
+//         16.5 / 12.0*, 4 of 750 11.5* / 14.3, 4 of 1000 15.6* / 15.3, 16 of 2000
+//         28.9* / 31.3, 32 of 2000 44.3 / 40.2*, 1 of 2000 12.3* / 24.0
+//   E4M3  1 of 250 8.4 / 7.0*, 4 of 500 9.7 / 8.2*, 4 of 750 10.3 / 10.2*, 1 of 1000
+//         9.8* / 10.8, 16 of 1000 14.8 / 11.9*, 16 of 2000 19.1* / 19.2
+// (Partitions of one step but more workgroups than CUs take longer than this counts:
+// 8 of 500, bf16, 14.5* / 10.6; 8 of 1000, E4M3, 13.0* / 10.9.)
 constexpr int kDecDirectWaves = 8;
 inline bool decode_direct(const int32_t* ctx, int32_t n, int hkv, int32_t split_tokens,
                           const MachineShape& m, const DecodeShape& ds) {

@@ -2,8 +2,11 @@
 // given machine shape: the decode partition and its workspace slots, the
 // prefill's XCD-aware work order and the automatic key-split count.
 // Usage: plan_harness <cus> <xcds>; prints "ok <cases>" or the first failure.
+//        plan_harness route <cus> <seg> <hkv> <context>...; prints "direct" or
+//        "partition", what the automatic split of such a decode takes.
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <random>
 #include <set>
 #include <vector>
@@ -18,13 +21,14 @@ static int fail(const char* what, long a, long b) {
 }
 
 // Walks the slices as the decode kernel does (a slice holds whole or partial
-// spans of kDecSegCost + pairs units; pairs of one (r, c) inside a slice form
-// a segment) and checks the workspace slots the segments write.
+// spans of seg + pairs units; pairs of one (r, c) inside a slice form
+// a segment) and checks the workspace slots the segments write.  The count of
+// workgroups is that of kDecSegCost, whatever the segments' weight.
 static int check_decode(const std::vector<int32_t>& ctx, int hkv, int split, int d,
-                        const MachineShape& m) {
+                        const MachineShape& m, int seg = kDecSegCost) {
   const int n = (int)ctx.size(), g = 4;
-  const int64_t total = decode_total_units(ctx.data(), n, hkv);
-  const DecodeLayout L = decode_layout(g, hkv, d, ctx.data(), n, split, m);
+  const int64_t total = decode_total_units(ctx.data(), n, hkv, seg);
+  const DecodeLayout L = decode_layout(g, hkv, d, ctx.data(), n, split, m, DecodeShape{seg});
   const int64_t nwg = L.nwg;
   if (split == 0 && nwg > (int64_t)kWgPerCu * m.cus) return fail("nwg above resident slots", nwg, m.cus);
   if (nwg < 1) return fail("no workgroup", nwg, total);
@@ -44,14 +48,14 @@ static int check_decode(const std::vector<int32_t>& ctx, int hkv, int split, int
   }
   // segments
   std::vector<int64_t> span_start(n + 1, 0);
-  for (int r = 0; r < n; ++r) span_start[r + 1] = span_start[r] + (int64_t)(kDecSegCost + (ctx[r] + 31) / 32) * hkv;
+  for (int r = 0; r < n; ++r) span_start[r + 1] = span_start[r] + (int64_t)(seg + (ctx[r] + 31) / 32) * hkv;
   std::set<int64_t> partial_slots;
   std::vector<int64_t> pairs_seen((size_t)n * hkv, 0);
   bool merge = false;
   for (int r = 0; r < n; ++r) {
-    const int64_t np = (ctx[r] + 31) / 32, span = kDecSegCost + np;
+    const int64_t np = (ctx[r] + 31) / 32, span = seg + np;
     for (int c = 0; c < hkv; ++c) {
-      const int64_t p_first = span_start[r] + c * span + kDecSegCost;  // unit of pair 0
+      const int64_t p_first = span_start[r] + c * span + seg;  // unit of pair 0
       const int64_t b0 = dec_slice_of(p_first, total, nwg);
       const int64_t b1 = dec_slice_of(p_first + np - 1, total, nwg);
       for (int64_t b = b0; b <= b1; ++b) {
@@ -72,7 +76,7 @@ static int check_decode(const std::vector<int32_t>& ctx, int hkv, int split, int
   for (int r = 0; r < n; ++r)
     for (int c = 0; c < hkv; ++c)
       if (pairs_seen[(size_t)r * hkv + c] != (ctx[r] + 31) / 32) return fail("pairs not covered once", r, c);
-  if (merge != decode_needs_merge(ctx.data(), n, hkv, total, nwg))
+  if (merge != decode_needs_merge(ctx.data(), n, hkv, total, nwg, seg))
     return fail("merge decision", merge, nwg);
   // the merge list: exactly the (r, c) with a partial segment, in (r, c)
   // order, with the slices of their first and last pairs
@@ -81,7 +85,7 @@ static int check_decode(const std::vector<int32_t>& ctx, int hkv, int split, int
   for (int r = 0; r < n && fits; ++r)
     for (int c = 0; c < hkv; ++c) {
       const int64_t np = (ctx[r] + 31) / 32;
-      const int64_t first = span_start[r] + c * (kDecSegCost + np) + kDecSegCost;
+      const int64_t first = span_start[r] + c * (seg + np) + seg;
       const int64_t b0 = dec_slice_of(first, total, nwg), b1 = dec_slice_of(first + np - 1, total, nwg);
       bool split = false;  // from the segment walk: some slice holds only part of (r, c)
       for (int64_t b = b0; b <= b1; ++b)
@@ -93,7 +97,7 @@ static int check_decode(const std::vector<int32_t>& ctx, int hkv, int split, int
                      (uint32_t)(b1 - b0) << (kMergeRcBits + kMergeB0Bits));
     }
   std::vector<uint32_t> got(want.size() + 1);
-  const int cnt = decode_merge_list(ctx.data(), n, hkv, total, nwg, got.data(), (int)got.size());
+  const int cnt = decode_merge_list(ctx.data(), n, hkv, total, nwg, got.data(), (int)got.size(), seg);
   if (!fits) {
     if (cnt != -1) return fail("merge list should not fit", cnt, nwg);
   } else {
@@ -101,9 +105,54 @@ static int check_decode(const std::vector<int32_t>& ctx, int hkv, int split, int
     for (size_t i = 0; i < want.size(); ++i)
       if (got[i] != want[i]) return fail("merge list item", (long)i, (long)got[i]);
     if (!want.empty() && decode_merge_list(ctx.data(), n, hkv, total, nwg, got.data(),
-                                           (int)want.size() - 1) != -1)
+                                           (int)want.size() - 1, seg) != -1)
       return fail("merge list past its capacity", (long)want.size(), 0);
   }
+  return 0;
+}
+
+// The weight of a segment start in a call's partition, the route of the automatic
+// split, and what either may change.
+static int check_decode_rules(const std::vector<int32_t>& ctx, int hkv, int d, const MachineShape& m) {
+  const int n = (int)ctx.size();
+  const int64_t units = decode_total_units(ctx.data(), n, hkv);
+  const bool fills = (units + kDecMinPairsPerWg - 1) / kDecMinPairsPerWg >= decode_slots(m);
+  for (int heavy : {8, 12, 16}) {
+    const DecodeShape ds{heavy};
+    if (decode_seg(ctx.data(), n, hkv, 0, m, ds) != (fills ? heavy : kDecSegCost)) return fail("segment weight", heavy, fills);
+    if (decode_seg(ctx.data(), n, hkv, 64, m, ds) != kDecSegCost) return fail("segment weight of a given split", heavy, 64);
+    if (decode_layout(4, hkv, d, ctx.data(), n, 0, m, ds).total != decode_layout(4, hkv, d, ctx.data(), n, 0, m).total)
+      return fail("workspace depends on the segment weight", heavy, 0);
+    if (check_decode(ctx, hkv, 0, d, m, decode_seg(ctx.data(), n, hkv, 0, m, ds))) return 1;
+    // one pair a wave where the call does not fill the machine
+    const int64_t total = decode_total_units(ctx.data(), n, hkv, decode_seg(ctx.data(), n, hkv, 0, m, ds));
+    const int64_t nwg = decode_nwg(units, 0, m);
+    for (int64_t b = 0; !fills && b < nwg; ++b)
+      if (dec_slice_begin(b + 1, total, nwg) - dec_slice_begin(b, total, nwg) > kDecMinPairsPerWg)
+        return fail("a slice of more than a pair a wave", b, nwg);
+    const bool direct = decode_direct(ctx.data(), n, hkv, 0, m, ds);
+    if (direct && (int64_t)n * hkv > m.cus) return fail("more workgroups than CUs", n, hkv);
+    if (decode_direct(ctx.data(), n, hkv, 64, m, ds)) return fail("direct with a given split", n, hkv);
+  }
+  return 0;
+}
+
+// Totals that fit an int only with the lighter segment starts are not refused.
+static int check_many_units(const MachineShape& m) {
+  const int hkv = 1024, n = 1 << 16;
+  const std::vector<int32_t> ctx(n, 1);
+  const int64_t light = decode_total_units(ctx.data(), n, hkv), heavy = decode_total_units(ctx.data(), n, hkv, 16);
+  if (light > kDecMaxUnits || heavy <= kDecMaxUnits) return fail("units", light, heavy);
+  if (decode_seg(ctx.data(), n, hkv, 0, m, DecodeShape{16}) != kDecSegCost) return fail("segment weight past the limit", 0, 0);
+  return 0;
+}
+
+static int route(int argc, char** argv) {
+  const MachineShape m{std::atoi(argv[2]), 8};
+  std::vector<int32_t> ctx;
+  for (int i = 5; i < argc; ++i) ctx.push_back(std::atoi(argv[i]));
+  const bool direct = decode_direct(ctx.data(), (int)ctx.size(), std::atoi(argv[4]), 0, m, DecodeShape{std::atoi(argv[3])});
+  std::puts(direct ? "direct" : "partition");
   return 0;
 }
 
@@ -145,6 +194,7 @@ static int check_splits(const MachineShape& m) {
 }
 
 int main(int argc, char** argv) {
+  if (argc > 5 && std::strcmp(argv[1], "route") == 0) return route(argc, argv);
   if (argc != 3) return 2;
   const MachineShape m{std::atoi(argv[1]), std::atoi(argv[2])};
   std::mt19937 rng(20982);
@@ -158,7 +208,18 @@ int main(int argc, char** argv) {
         if (check_decode(ctx, hkv, split, 128, m)) return 1;
         ++cases;
       }
+    if (t % 3 == 0)
+      for (int seg : {12, 16}) {
+        if (check_decode(ctx, 4, t % 2 ? 512 : 0, 128, m, seg)) return 1;
+        ++cases;
+      }
+    ctx.resize(1 + t % 2 * (ctx.size() - 1));
+    for (int hkv : {1, 8}) {
+      if (check_decode_rules(ctx, hkv, 64, m)) return 1;
+      ++cases;
+    }
   }
+  if (check_many_units(m)) return 1;
   for (int n_items : {1, 7, 8, 9, 255, 256, 257, 1000, 8100}) {
     if (check_prefill_order(n_items, m)) return 1;
     ++cases;
