@@ -136,6 +136,11 @@ dopd_status check_decode_host(const dopd_attn_shape* s, const int32_t* ctx_host,
   return DOPD_OK;
 }
 
+dim3 grid_of(int64_t blocks) {
+  const dopd::GridShape g = dopd::grid_shape(blocks);
+  return dim3(g.x, g.y);
+}
+
 // ---- fp32 attention ----------------------------------------------------------
 dopd::AttnF32Args f32_args(const dopd_attn_shape* s, const void* q, const void* k, const void* v,
                            void* out, float* lse, int32_t nreq) {
@@ -163,7 +168,7 @@ dopd_status launch_f32(const dopd::AttnF32Args& f, int d, const int32_t* cu_host
     blocks += (rows * g + dopd::kF32Cols - 1) / dopd::kF32Cols * f.hkv;
   }
   if (blocks > INT32_MAX / 2) return DOPD_ERR_INVALID_SHAPE;
-  const dim3 grid((unsigned)blocks);
+  const dim3 grid = grid_of(blocks);
   if (d == 64)
     hipLaunchKernelGGL((dopd::attn_f32_kernel<64, PAGED>), grid, dim3(64 * dopd::f32_waves<64>()), 0, strm, f);
   else
@@ -624,14 +629,15 @@ dopd_status launch_kv_write(const dopd_attn_shape* s, const void* k_new, const v
   a.pt_stride = pt_stride;
   a.nreq = nreq;
   a.hkv = s->num_kv_heads;
+  a.total_new = total_new;
   hipStream_t strm = as_stream(stream);
   const int d = s->head_dim;
   if (total_new <= dopd::kKvwAppendMean * (int64_t)nreq) {
     const int64_t waves = 2 * (((int64_t)a.hkv * d * sizeof(TI) / 16 + 63) / 64);
     const int64_t groups = (waves + dopd::kKvaWaves - 1) / dopd::kKvaWaves;
-    if (groups * total_new > INT32_MAX) return DOPD_ERR_INVALID_SHAPE;
+    if (groups * total_new > dopd::kGridMaxBlocks) return DOPD_ERR_INVALID_SHAPE;
     a.head_groups = (int)groups;
-    const dim3 grid((unsigned)(groups * total_new)), block(64 * dopd::kKvaWaves);
+    const dim3 grid = grid_of(groups * total_new), block(64 * dopd::kKvaWaves);
     if (d == 64)
       hipLaunchKernelGGL((dopd::kv_append_kernel<TI, TO, 64>), grid, block, 0, strm, a);
     else
@@ -641,8 +647,8 @@ dopd_status launch_kv_write(const dopd_attn_shape* s, const void* k_new, const v
   // Touched pages per request <= n / 16 + 2, so this bounds the item count.
   const int64_t pages = (int64_t)total_new / dopd::kPage + 2 * (int64_t)nreq + 1;
   a.head_groups = write_head_groups<TI, TO>(a.hkv, d);
-  if (pages * a.head_groups > INT32_MAX) return DOPD_ERR_INVALID_SHAPE;
-  const dim3 grid((unsigned)(pages * a.head_groups)), block(64 * dopd::kKvwWaves);
+  if (pages * a.head_groups > dopd::kGridMaxBlocks) return DOPD_ERR_INVALID_SHAPE;
+  const dim3 grid = grid_of(pages * a.head_groups), block(64 * dopd::kKvwWaves);
   if (d == 64)
     hipLaunchKernelGGL((dopd::kv_write_kernel<TI, TO, 64>), grid, block, 0, strm, a);
   else
@@ -1110,11 +1116,11 @@ dopd_status dopd_kv_unpack_from_handoff(const dopd_attn_shape* s, int32_t num_la
   if (s->dtype == DOPD_FP8_E4M3) {
     const int groups = write_head_groups<uint8_t, uint8_t>(hkv, s->head_dim);
     const int64_t blocks = pages * num_layers * groups;
-    if (blocks > INT32_MAX) return DOPD_ERR_INVALID_SHAPE;
+    if (blocks > dopd::kGridMaxBlocks) return DOPD_ERR_INVALID_SHAPE;
     const dopd::UnpackPagesArgs a{(const uint8_t*)in, in_offsets, req_ids, seq_lens, (uint8_t*)k_pool,
                                   (uint8_t*)v_pool, pt, num_pages, pt_stride, hkv, num_handoff,
                                   num_layers, groups};
-    const dim3 grid((unsigned)blocks), block(64 * dopd::kKvwWaves);
+    const dim3 grid = grid_of(blocks), block(64 * dopd::kKvwWaves);
     if (s->head_dim == 64)
       hipLaunchKernelGGL(dopd::kv_unpack_pages_kernel<64>, grid, block, 0, strm, a);
     else

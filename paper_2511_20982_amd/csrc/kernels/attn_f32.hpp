@@ -33,6 +33,7 @@
 // selects, so that no column takes 0 * inf from a key it does not see.
 #pragma once
 #include "common.hpp"
+#include "../plan.hpp"
 
 namespace dopd {
 
@@ -106,7 +107,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void attn_f32_kernel(AttnF32Args a) 
     return tiles_of(n_l) * hkv;
   };
   int r, local;
-  if (!find_owner((int)blockIdx.x, a.nreq, items, r, local)) return;  // uniform
+  if (!find_owner(grid_block(blockIdx.x, blockIdx.y), a.nreq, items, r, local)) return;  // uniform
   const int L = __builtin_amdgcn_readlane(n_l, r % 64), row0 = __builtin_amdgcn_readlane(row_l, r % 64);
   const int P = __builtin_amdgcn_readlane(pre_l, r % 64);
   const int c = local % hkv;

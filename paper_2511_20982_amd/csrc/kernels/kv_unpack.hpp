@@ -119,7 +119,8 @@ __global__ __launch_bounds__(64 * kKvwWaves) void kv_unpack_pages_kernel(UnpackP
   using W = PageWrite<T, T, D>;
   __shared__ __attribute__((aligned(16))) uint8_t s[kKvwWaves / 2][W::kLdsBytes];  // of the V waves
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int wi = (int)blockIdx.x % a.head_groups * kKvwWaves + w;  // wave of the page: K's, V's, ..
+  const int b = grid_block(blockIdx.x, blockIdx.y);
+  const int wi = b % a.head_groups * kKvwWaves + w;  // wave of the page: K's, V's, ..
   const int h0 = (wi >> 1) * W::HW;
   if (h0 >= a.hkv) return;
   int len_l = 0, req_l = 0;  // this lane's handoff
@@ -129,7 +130,7 @@ __global__ __launch_bounds__(64 * kKvwWaves) void kv_unpack_pages_kernel(UnpackP
     return a.layers * ((len_l + kPage - 1) / kPage);
   };
   int n, local;
-  if (!find_owner((int)blockIdx.x / a.head_groups, a.nhand, items, n, local)) return;
+  if (!find_owner(b / a.head_groups, a.nhand, items, n, local)) return;
   const int len = __builtin_amdgcn_readlane(len_l, n % 64), r = __builtin_amdgcn_readlane(req_l, n % 64);
   const int np = (len + kPage - 1) / kPage, layer = local / np, pg = local % np;
   const int64_t page = (int64_t)layer * a.num_pages + a.page_table[(int64_t)r * a.pt_stride + pg];

@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "../plan.hpp"
 
 namespace dopd {
 
@@ -279,7 +280,7 @@ struct KvWriteArgs {
   const int32_t* page_table;  // [nreq][pt_stride]
   const int32_t* cu_new;      // [nreq + 1]
   const int32_t* start_pos;   // [nreq]
-  int pt_stride, nreq, hkv;
+  int pt_stride, nreq, hkv, total_new;
   int head_groups;            // workgroups of a page (page writer) or of a token (append writer)
 };
 
@@ -300,11 +301,12 @@ __global__ __launch_bounds__(64 * kKvwWaves) void kv_write_kernel(KvWriteArgs<TI
     return n_l > 0 ? (st_l + n_l - 1) / kPage - st_l / kPage + 1 : 0;
   };
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int wi = (int)blockIdx.x % a.head_groups * kKvwWaves + w;  // wave of the page
+  const int b = grid_block(blockIdx.x, blockIdx.y);
+  const int wi = b % a.head_groups * kKvwWaves + w;  // wave of the page
   const int h0 = (wi >> 1) * W::HW;
   if (h0 >= a.hkv) return;
   int r, local;
-  if (!find_owner((int)blockIdx.x / a.head_groups, a.nreq, touched, r, local)) return;
+  if (!find_owner(b / a.head_groups, a.nreq, touched, r, local)) return;
   const int row0 = __builtin_amdgcn_readlane(cu_l, r % 64), n = __builtin_amdgcn_readlane(n_l, r % 64);
   const int start = __builtin_amdgcn_readlane(st_l, r % 64);
   const int lp = start / kPage + local;                 // logical page
@@ -350,8 +352,10 @@ __global__ __launch_bounds__(64 * kKvaWaves) void kv_append_kernel(KvWriteArgs<T
   constexpr int EPC = W::EPC;
   __shared__ __attribute__((aligned(16))) TO s[kKvaWaves][64 * EPC];
   const int l = lane_id(), wl = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  int t = (int)blockIdx.x / a.head_groups;
-  const int w = (int)blockIdx.x % a.head_groups * kKvaWaves + wl;
+  const int b = grid_block(blockIdx.x, blockIdx.y);
+  int t = b / a.head_groups;
+  if (t >= a.total_new) return;  // uniform
+  const int w = b % a.head_groups * kKvaWaves + wl;
   const int half = a.hkv * W::CPR;  // chunks of a row
   const bool is_v = w & 1;
   const int c0 = 64 * (w >> 1), i = c0 + l;

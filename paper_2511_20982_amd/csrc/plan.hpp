@@ -22,6 +22,20 @@ constexpr MachineShape kDefaultMachine{256, 8};
 // (both are launched with __launch_bounds__(256, 2)).
 constexpr int kWgPerCu = 2;
 
+// Grid of `blocks` workgroups in one or two dimensions: a dimension holds fewer than
+// 2^32 threads, which 2^23 workgroups of 512 reach.  Workgroup (x, y) is block
+// grid_block(x, y); those from `blocks` on, in the last row, have no work.
+constexpr unsigned kGridRow = 1u << 22;
+constexpr int64_t kGridMaxBlocks = (int64_t)INT32_MAX - kGridRow;  // every index fits an int
+struct GridShape {
+  unsigned x, y;
+};
+constexpr GridShape grid_shape(int64_t blocks) {
+  return blocks <= kGridRow ? GridShape{(unsigned)blocks, 1}
+                            : GridShape{kGridRow, (unsigned)((blocks + kGridRow - 1) / kGridRow)};
+}
+constexpr int grid_block(unsigned x, unsigned y) { return (int)(y * kGridRow + x); }
+
 constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // ---- decode partition ------------------------------------------------------

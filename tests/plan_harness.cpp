@@ -147,6 +147,20 @@ static int check_many_units(const MachineShape& m) {
   return 0;
 }
 
+// Every block has a workgroup, in grids that a launch of 512 threads can take.
+static int check_grids() {
+  for (int64_t blocks : {(int64_t)1, (int64_t)1000, (int64_t)kGridRow - 1, (int64_t)kGridRow, (int64_t)kGridRow + 1,
+                         (int64_t)3 * kGridRow, (int64_t)8500000, kGridMaxBlocks}) {
+    const GridShape g = grid_shape(blocks);
+    if ((int64_t)g.x * 512 >= (int64_t)1 << 32 || g.y > 65535) return fail("grid", g.x, g.y);
+    if ((int64_t)g.x * g.y < blocks || (int64_t)g.x * (g.y - 1) >= blocks) return fail("grid rows", g.y, (long)blocks);
+    if (grid_block(0, 0) != 0 || (g.y > 1 && grid_block(0, 1) != grid_block(g.x - 1, 0) + 1)) return fail("grid order", g.x, g.y);
+    if ((int64_t)g.x * g.y - 1 > INT32_MAX || grid_block(g.x - 1, g.y - 1) != (int64_t)g.x * g.y - 1)
+      return fail("grid index", grid_block(g.x - 1, g.y - 1), (long)blocks);
+  }
+  return 0;
+}
+
 static int route(int argc, char** argv) {
   const MachineShape m{std::atoi(argv[2]), 8};
   std::vector<int32_t> ctx;
@@ -219,7 +233,7 @@ int main(int argc, char** argv) {
       ++cases;
     }
   }
-  if (check_many_units(m)) return 1;
+  if (check_many_units(m) || check_grids()) return 1;
   for (int n_items : {1, 7, 8, 9, 255, 256, 257, 1000, 8100}) {
     if (check_prefill_order(n_items, m)) return 1;
     ++cases;

@@ -148,3 +148,20 @@ def test_f32_one_tile(d, bad):
     k[:] = -np.inf
     out, lse = G.gpu_prefill(shape, q, k, v, cu)
     assert np.isnan(out).all() and np.isnan(lse).all()
+
+
+def test_f32_decode_of_more_workgroups_than_a_grid_dimension_takes():
+    """8.4 million (request, KV head) pairs of one key each, whose V they return."""
+    import torch
+
+    n, hkv, d = 1 << 16, 129, 64
+    shape = G.A.make_shape(hkv, hkv, d, "fp32")
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    kp, vp = (torch.randn(s, device="cuda", generator=gen) for s in ((5, hkv, 16, d), (5, hkv, d, 16)))
+    page = torch.arange(n, device="cuda", dtype=torch.int32).remainder(5).view(n, 1).contiguous()
+    ctx = np.ones(n, np.int32)
+    q = torch.randn(n, hkv, d, device="cuda", generator=gen)
+    out = torch.full_like(q, float("nan"))
+    G.A.dopd_decode_attn(shape, q, kp, vp, 5, page, 1, torch.from_numpy(ctx).cuda(), ctx, n, 0, out, None,
+                         G.A.decode_workspace(shape, ctx, n))
+    assert torch.equal(out, vp[page.view(-1).long(), :, :, 0])
