@@ -55,8 +55,9 @@ KERNEL_SOURCES = ("paper_2511_20982_amd/csrc/dopd_attn.hip",
                   "paper_2511_20982_amd/csrc/kernels/kv_unpack.hpp")
 # Kernels behind each timed call (the decode call is a split kernel plus, when
 # some (request, KV head) spans two slices, one of the two merge kernels; a
-# chunk call with key splits adds the prefill merge kernel).
-CALL_KERNELS = {"decode": ("decode_split_kernel", "decode_merge_list_kernel",
+# chunk call with key splits adds the prefill merge kernel).  CALL_ROUTES: the
+# kernels one of which a launch of the call takes by its sizes (else its first).
+CALL_KERNELS = {"decode": ("decode_split_kernel", "decode_direct_kernel", "decode_merge_list_kernel",
                            "decode_merge_kernel"),
                 "prefill": ("prefill_bf16_kernel<128, false, false>",
                             "prefill_bf16_kernel<64, false, false>"),
@@ -66,13 +67,17 @@ CALL_KERNELS = {"decode": ("decode_split_kernel", "decode_merge_list_kernel",
                 "prefill_chunked_fp8": ("prefill_bf16_kernel<128, true, true>",
                                         "prefill_bf16_kernel<64, true, true>",
                                         "prefill_split_merge_kernel"),
-                "kv_write": ("kv_write_kernel<unsigned short, unsigned short",),
-                "kv_write_fp8": ("kv_write_kernel<unsigned short, unsigned char",),
+                "kv_write": ("kv_write_kernel<unsigned short, unsigned short",
+                             "kv_append_kernel<unsigned short, unsigned short"),
+                "kv_write_fp8": ("kv_write_kernel<unsigned short, unsigned char",
+                                 "kv_append_kernel<unsigned short, unsigned char"),
                 "plain_copy": ("bitwise_not_kernel",),
-                "pack": ("kv_pack_kernel",), "unpack": ("kv_unpack_kernel",),
+                "pack": ("kv_pack_kernel",), "unpack": ("kv_unpack_kernel", "kv_unpack_pages_kernel"),
                 "pd_step": ("pd_step_kernel", "decode_merge_list_kernel",
                             "decode_merge_kernel"),
                 "kv_write_pack": ("kv_write_pack_kernel",)}
+CALL_ROUTES = {"decode": CALL_KERNELS["decode"][:2],
+               **{c: CALL_KERNELS[c] for c in ("kv_write", "kv_write_fp8", "unpack")}}
 
 WORKLOADS = {
     "mixed": ("mixed P/D step + handoff: prefill 8x512, decode 192 req ctx lognormal(2048,0.7) "
@@ -217,16 +222,16 @@ def summarize(args):
                        f"{float(row['MinNs']) / 1e3:.2f} | {float(row['MaxNs']) / 1e3:.2f} | "
                        f"{float(row['Percentage']):.1f}% |")
         # Kernel time per C-ABI call: the kernels of the call, each weighted by
-        # its launches per launch of the call's first kernel.
+        # its launches per launch of the call (of its routes' kernels).
         kcalls = {}
         for call, kernels in CALL_KERNELS.items():
-            # a call is present when its first kernel ran (the others it may add
-            # are shared with other calls: the decode merge kernel)
-            if not any(kernels[0] in r["Name"] for r in rows):
+            # a call is present when the kernel of a route of its ran (the others it
+            # may add are shared with other calls: the decode merge kernel)
+            routes = CALL_ROUTES.get(call, kernels[:1])
+            n_calls = sum(float(r["Calls"]) for r in rows if any(k in r["Name"] for k in routes))
+            if not n_calls:
                 continue
             match = [r for r in rows if any(k in r["Name"] for k in kernels)]
-            first = next(r for k in kernels for r in match if k in r["Name"])
-            n_calls = float(first["Calls"])
             us = sum(float(r["AverageNs"]) * float(r["Calls"]) for r in match) / n_calls / 1e3
             kcalls[call] = {"avg_us": round(us, 3), "calls": int(n_calls),
                             "kernels": [r["Name"][:90] for r in match]}
@@ -263,18 +268,24 @@ def summarize(args):
         out.append("| kernel | dispatches | FETCH_SIZE KiB | WRITE_SIZE KiB |")
         out.append("|---|---|---|---|")
         calls = {}
-        present = {call for call, kernels in CALL_KERNELS.items()
-                   if any(kernels[0] in kname for kname in per)}
+        # Dispatches of each call: of its routes' kernels, whose bytes count by their
+        # share of them (the kernels after them run once a call that has them).
+        dispatches = lambda ctrs: max(len(v) for v in ctrs.values())  # noqa: E731
+        launched = {call: sum(dispatches(ctrs) for kname, ctrs in per.items()
+                              if any(k in kname for k in CALL_ROUTES.get(call, kernels[:1])))
+                    for call, kernels in CALL_KERNELS.items()}
         for kname, ctrs in sorted(per.items()):
             f_k = float(np.median(ctrs["FETCH_SIZE"])) if "FETCH_SIZE" in ctrs else float("nan")
             w_k = float(np.median(ctrs["WRITE_SIZE"])) if "WRITE_SIZE" in ctrs else float("nan")
             n = max(len(ctrs.get("FETCH_SIZE", [])), len(ctrs.get("WRITE_SIZE", [])))
             out.append(f"| {kname[:90]} | {n} | {f_k:.0f} | {w_k:.0f} |")
             for call, kernels in CALL_KERNELS.items():
-                if call in present and any(k in kname for k in kernels):
+                if launched[call] and any(k in kname for k in kernels):
                     c = calls.setdefault(call, {"fetch_kib": 0.0, "write_kib": 0.0, "kernels": []})
-                    c["fetch_kib"] += f_k
-                    c["write_kib"] += w_k
+                    route = any(k in kname for k in CALL_ROUTES.get(call, kernels[:1]))
+                    share = dispatches(ctrs) / launched[call] if route else 1.0
+                    c["fetch_kib"] += f_k * share
+                    c["write_kib"] += w_k * share
                     c["kernels"].append(kname)
         for call, c in calls.items():
             ff, fw = factors.get("FETCH_SIZE") or 1.0, factors.get("WRITE_SIZE") or 1.0

@@ -93,6 +93,34 @@ def test_summarize_scales_counters_by_the_calibration_kernel(tmp_path):
     assert "decode_split_kernel" in text and "200.00" in text
 
 
+def test_summarize_counts_every_route_of_a_call(tmp_path):
+    """Two decodes on the partition (one with a merge), one direct; appends only."""
+    names = {"split": "void dopd::decode_split_kernel<128, false>(dopd::DecodeArgs)",
+             "direct": "void dopd::decode_direct_kernel<128, false>(dopd::DecodeArgs)",
+             "merge": "void dopd::decode_merge_list_kernel<128>(dopd::DecodeArgs, dopd::DecodeMergeList)",
+             "append": "void dopd::kv_append_kernel<unsigned short, unsigned char, 128>(dopd::KvWriteArgs)",
+             "pages": "void dopd::kv_unpack_pages_kernel<128>(dopd::UnpackPagesArgs)"}
+    d = tmp_path / "prof"
+    stats = {"split": (2, 100000), "direct": (1, 40000), "merge": (1, 30000), "append": (3, 5000), "pages": (4, 7000)}
+    _write_csv(str(d / "trace" / "t_kernel_stats.csv"), [
+        {"Name": names[k], "Calls": n, "AverageNs": ns, "MinNs": ns, "MaxNs": ns, "Percentage": 20.0}
+        for k, (n, ns) in stats.items()])
+    kib = {"split": 900.0, "direct": 300.0, "append": 10.0, "pages": 20.0}
+    _write_csv(str(d / "pmc" / "p_counter_collection.csv"), [
+        {"Dispatch_Id": f"{k}{ctr}{i}", "Counter_Name": ctr, "Counter_Value": v, "Kernel_Name": names[k]}
+        for k, v in kib.items() for ctr in ("FETCH_SIZE", "WRITE_SIZE") for i in range(stats[k][0])])
+    r = _run("--summarize", str(d), "--label", "routes", "--summary-out", str(tmp_path / "s.md"),
+             "--traffic-dir", str(tmp_path), "--command", "x")
+    assert r.returncode == 0, r.stderr
+    calls = json.load(open(tmp_path / "kernels_routes.json"))["calls"]
+    assert {k: (c["avg_us"], c["calls"]) for k, c in calls.items()} == {
+        "decode": (90.0, 3), "kv_write_fp8": (5.0, 3), "unpack": (7.0, 4)}
+    calls = json.load(open(tmp_path / "traffic_routes.json"))["calls"]
+    # per call two thirds of 900 KiB and one third of 300, read and written
+    assert {k: c["hbm_bytes_per_call"] // 2048 for k, c in calls.items()} == {
+        "decode": 700, "kv_write_fp8": 10, "unpack": 20}
+
+
 def test_repeat_timed_covers_the_requested_time():
     calls = []
     res, n, dt = B.repeat_timed(lambda: calls.append(1) or len(calls), 0.05)
