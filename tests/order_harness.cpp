@@ -20,12 +20,17 @@ static int fail(const char* what, long a, long b) {
 }
 
 static int check(const std::vector<int32_t>& lens, const std::vector<int32_t>& prefix, int hq, int hkv,
-                 int64_t kv_bytes, int xcds) {
+                 int64_t kv_bytes, int xcds, bool split_requests = true) {
   const int n = (int)lens.size(), g = hq / hkv;
   std::vector<int32_t> cu(n + 1, 0);
   for (int r = 0; r < n; ++r) cu[r + 1] = cu[r] + lens[r];
   PfOrder o;
-  pf_build_order(o, cu.data(), prefix.empty() ? nullptr : prefix.data(), n, hq, hkv, kv_bytes, xcds);
+  pf_build_order(o, cu.data(), prefix.empty() ? nullptr : prefix.data(), n, hq, hkv, kv_bytes, xcds,
+                 split_requests);
+  if (!split_requests)  // whole requests: the fused step's order
+    for (int k = 0; k < o.n; ++k)
+      if (o.e[k].tile0 != 0 || o.e[k].nt != (o.e[k].len + kPfTileRows - 1) / kPfTileRows)
+        return fail("part of a request", k, o.e[k].nt);
   if (o.n < 0 || o.n > kPfMaxOrdered) return fail("entries", o.n, n);
   std::map<std::tuple<int, int, int>, int> seen;
   std::vector<long> got(xcds, 0);
@@ -59,6 +64,17 @@ static int check(const std::vector<int32_t>& lens, const std::vector<int32_t>& p
   if ((long)seen.size() != items) return fail("items not covered", (long)seen.size(), items);
   for (auto& s : seen)
     if (s.second != 1) return fail("item taken more than once", std::get<0>(s.first), std::get<1>(s.first));
+  // the kernel's way from a workgroup to its XCD, place and split, where the order
+  // says that its divisions hold
+  for (int nsplit : {1, 3, kPfMaxSplits}) {
+    if (!pf_order_fits(o, nsplit)) return fail("order does not fit", nsplit, o.n);
+    const FastDiv by_split = fast_div((uint32_t)nsplit);
+    const int64_t blocks = (int64_t)pf_order_places(o) * nsplit * xcds;
+    for (int64_t b = 0; b < blocks; b += blocks > 20000 ? 7 : 1) {
+      const int s = fast_quot((int)b, o.by_xcds), place = fast_quot(s, by_split);
+      if (s != b / xcds || place != s / nsplit) return fail("workgroup's place", (long)b, nsplit);
+    }
+  }
   if (hkv % xcds == 0 || xcds % hkv == 0) {
     long lo = got[0], hi = got[0];
     for (int x = 0; x < xcds; ++x) {
@@ -83,6 +99,39 @@ static int check_fast_div() {
   return 0;
 }
 
+// Orders too large for divisions by multiplication say so, and the ones just below
+// divide exactly at their last workgroup.
+static int check_fits(int xcds) {
+  bool some_fit = false, some_do_not = false;
+  for (int hq : {32, 64})
+    for (int nsplit : {1, 16}) {
+      bool fits = true;
+      for (int64_t len = 1 << 20; len <= INT32_MAX; len += len / 3) {
+        const int32_t cu[2] = {0, (int32_t)len};
+        PfOrder o;
+        pf_build_order(o, cu, nullptr, 1, hq, 8, 512, xcds);
+        const int64_t places = (int64_t)pf_order_places(o) * nsplit, blocks = places * xcds;
+        const bool now = pf_order_fits(o, nsplit);
+        if (now && !fits) return fail("a larger order fits", (long)len, nsplit);
+        fits = now;
+        some_fit |= now;
+        some_do_not |= !now;
+        if (!now || blocks > INT32_MAX / 2) continue;  // (refused before the order is asked)
+        const FastDiv by_split = fast_div((uint32_t)nsplit);
+        if (fast_quot((int)(blocks - 1), o.by_xcds) != places - 1 ||
+            fast_quot((int)(places - 1), by_split) != pf_order_places(o) - 1)
+          return fail("last workgroup of an order that fits", (long)len, nsplit);
+        int back = -1, h = -1;
+        for (int x = 0; x < xcds; ++x)
+          if (!o.sliced && pf_entry_item(o, o.e[0].rot, o.e[0].nt, x, pf_order_places(o) - 1, back, h) &&
+              (back < 0 || back >= o.e[0].nt || h < 0 || h >= hq))
+            return fail("last item of an order that fits", back, h);
+      }
+    }
+  if (!some_fit || !some_do_not) return fail("orders on one side of the limit only", some_fit, some_do_not);
+  return 0;
+}
+
 int main(int argc, char** argv) {
   if (argc != 2) return 2;
   const int xcds = std::atoi(argv[1]);
@@ -99,8 +148,10 @@ int main(int argc, char** argv) {
         for (int r = 0; r < n; ++r) prefix.push_back((int)(rng() % 5000));
       for (int64_t kv : {256, 512})
         if (check(lens, prefix, h[0], h[1], kv, xcds)) return 1;
+      if (t < 12 && check(lens, prefix, h[0], h[1], 256, xcds, false)) return 1;
       ++cases;
     }
+  if (check_fits(xcds)) return 1;
   if (check({128}, {}, 32, 32, 512, xcds) || check({0, 1, 0, 129}, {}, 28, 4, 512, xcds)) return 1;
   std::printf("ok %d\n", cases + 2);
   return 0;
