@@ -667,13 +667,17 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs& a, int bid,
     // The wave's priority is raised over the softmax and the next tile's QK
     // products, so its VALU work issues first and the other workgroup's P.V
     // MFMAs fill the slots it leaves (measured 1-2 % faster dense, 3-5 % over
-    // E4M3 and bf16 pages).
+    // E4M3 and bf16 pages of d 128).  Over pages of d 64, where a step has half the
+    // products, it is 1-10 % slower (E4M3: 21 chunks of 36 tokens, 32/8 heads, 27.7
+    // against 24.6 us, 6 of 343 behind 4000, 16/16 heads, 110 against 102; bf16: 5 of
+    // 140 behind 3000 45.6 against 43.8).
+    constexpr bool kRaise = !PAGED || D == 128;
     auto step_full = [&](f32x16* sc, f32x16* sn, auto par) {
       prefetch(j, par);
       if (wave_active) {
-        __builtin_amdgcn_s_setprio(1);
+        if constexpr (kRaise) __builtin_amdgcn_s_setprio(1);
         half_qk(sc, sn, par() ^ 1);
-        __builtin_amdgcn_s_setprio(0);
+        if constexpr (kRaise) __builtin_amdgcn_s_setprio(0);
         pv(par());
       }
       if (j + 1 < je) clear_dead_v(par() ^ 1, j + 1);
