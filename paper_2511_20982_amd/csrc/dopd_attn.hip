@@ -1063,15 +1063,18 @@ dopd_status dopd_kv_pack_for_handoff(const dopd_attn_shape* s, int32_t num_layer
     a.nhand = num_handoff;
     a.nblocks = (int)(zdim * pages);
     a.out = static_cast<T*>(out);
-    if (s->head_dim == 64) {
-      constexpr int per = dopd::pack_blocks_per_wg<T, 64>();
-      hipLaunchKernelGGL((dopd::kv_pack_kernel<T, 64, per>), dim3((a.nblocks + per - 1) / per),
+    auto launch_d = [&](auto d, auto stream_loads) {
+      constexpr int per = dopd::pack_blocks_per_wg<T, d>();
+      hipLaunchKernelGGL((dopd::kv_pack_kernel<T, d, per, stream_loads>), dim3((a.nblocks + per - 1) / per),
                          dim3(256), 0, strm, a);
-    } else {
-      constexpr int per = dopd::pack_blocks_per_wg<T, 128>();
-      hipLaunchKernelGGL((dopd::kv_pack_kernel<T, 128, per>), dim3((a.nblocks + per - 1) / per),
-                         dim3(256), 0, strm, a);
-    }
+    };
+    const bool large = a.nblocks > dopd::kHandoffStreamBytes / (dopd::kPage * s->head_dim * (int)sizeof(T));
+    using D64 = std::integral_constant<int, 64>;
+    using D128 = std::integral_constant<int, 128>;
+    if (s->head_dim == 64 && large) launch_d(D64{}, std::true_type{});
+    else if (s->head_dim == 64) launch_d(D64{}, std::false_type{});
+    else if (large) launch_d(D128{}, std::true_type{});
+    else launch_d(D128{}, std::false_type{});
   };
   if (s->dtype == DOPD_FP8_E4M3)
     launch(uint8_t{});
@@ -1141,7 +1144,7 @@ dopd_status dopd_kv_unpack_from_handoff(const dopd_attn_shape* s, int32_t num_la
                          req_ids, seq_lens, kp, vp, num_pages, pt, pt_stride, hkv);
   };
   const bool bf16 = s->dtype == DOPD_BF16;
-  const bool large = tokens > dopd::kUnpackStreamBytes / (zdim * s->head_dim * (bf16 ? 2 : 4));
+  const bool large = tokens > dopd::kHandoffStreamBytes / (zdim * s->head_dim * (bf16 ? 2 : 4));
   if (bf16 && large) launch(uint16_t{}, std::true_type{});
   else if (bf16) launch(uint16_t{}, std::false_type{});
   else if (large) launch(uint32_t{}, std::true_type{});

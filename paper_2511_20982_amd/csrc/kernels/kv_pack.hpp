@@ -49,7 +49,20 @@ constexpr int pack_blocks_per_wg() {
   return kPackBytesPerWg >= kPage * D * (int)sizeof(T) ? kPackBytesPerWg / (kPage * D * (int)sizeof(T)) : 1;
 }
 
-template <typename T, int D, int PER>
+// Buffers of more than this are packed and unpacked with streaming loads, which leave
+// the caches to the lines on their way out.  Of a smaller one both the pages and the
+// buffer fit the 256 MiB cache, from where they can be read if they have just been
+// written.  Measured, plain / streaming:
+//   pack, pages from HBM: bf16 40 MB 18.3 / 17.0 us, 201 MB 73 / 68, 1.6 GB 569 / 545;
+//     from the cache: bf16 71 MB 23.2 / 24.9, 99 MB 31.6 / 35.6, E4M3 85 MB 28.7 / 34.1
+//   unpack, bf16, 32 heads of 128, 81 MB: from the cache 23.5 / 30.2, from HBM 32.3 /
+//     29.8; 1.6 GB 588 / 578; fp32 403 MB 141 / 132
+//   both, one after the other on the same pages and buffer: bf16 29 MB 28.0 / 26.9,
+//     71 MB 53.7 / 55.1, 99 MB 83.4 / 87.5, 240 MB 174.3 / 172.3 (streaming in one of
+//     them alone: the pack 32.0, 58.2, 90.5; the unpack 26.0, 52.9, 82.8)
+constexpr int64_t kHandoffStreamBytes = (int64_t)128 << 20;
+
+template <typename T, int D, int PER, bool STREAM>
 __global__ __launch_bounds__(256) void kv_pack_kernel(PackArgs<T> a) {
   constexpr int C = D * (int)sizeof(T);      // 16-byte chunks per block
   constexpr int NPT = (PER * C + 255) / 256;  // chunks per thread
@@ -95,13 +108,10 @@ __global__ __launch_bounds__(256) void kv_pack_kernel(PackArgs<T> a) {
   for (int k = 0; k < NPT; ++k) {
     const int c = tid + 256 * k;
     const int j = c / C;  // wave-uniform
-    // (read once: streaming loads leave the caches to the lines on their way out.
-    // Plain / streaming, bf16, pages from HBM: 40 MB 19 / 16 us, 201 MB 73 / 68, 1.6
-    // GB 569 / 545; pages that are still in the 256 MiB cache, which takes a pack
-    // right after the write of all its layers: 40 MB 15 / 14, 81 MB 27 / 29, 201 MB
-    // 61 / 67)
-    if (c < PER * C && meta[j].nvalid > 0)
-      x[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(meta[j].src) + c % C);
+    if (c < PER * C && meta[j].nvalid > 0) {
+      const u32x4* p = reinterpret_cast<const u32x4*>(meta[j].src) + c % C;
+      x[k] = STREAM ? __builtin_nontemporal_load(p) : *p;
+    }
   }
   // Into LDS token-major: K chunks as they are, V chunks (EL tokens of one
   // dim) scattered to their token rows.

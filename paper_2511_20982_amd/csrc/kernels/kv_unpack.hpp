@@ -13,18 +13,12 @@
 // 135 / 155, 32 heads 577 / 609; fp32 8 heads of 128 273 / 317, of 64 134 / 156.
 // (bf16 of d 64, 104 / 78 and 32 heads 405 / 309, would gain from the second.)
 #pragma once
+#include "kv_pack.hpp"
 #include "kv_write.hpp"
 
 namespace dopd {
 
-// Buffers of more than this are read with streaming loads, which leave the caches
-// to the lines on their way out.  A smaller one, with the pages written meanwhile,
-// fits the 256 MiB cache that it came in through and can be read from there (plain
-// / streaming, bf16, 32 heads of 128: 81 MB from that cache 23.5 / 30.2 us, from
-// HBM 32.3 / 29.8; pack and unpack of 240 MB 174.3 / 172.3, unpack of 1.6 GB 588 /
-// 578; fp32, 403 MB 141 / 132).
-constexpr int64_t kUnpackStreamBytes = (int64_t)128 << 20;
-
+// STREAM: streaming loads, for buffers of more than kHandoffStreamBytes.
 template <typename T, int D, bool STREAM>
 __global__ __launch_bounds__(256) void kv_unpack_kernel(
     const T* __restrict__ in, const int64_t* __restrict__ in_off, const int32_t* __restrict__ req_ids,

@@ -84,3 +84,33 @@ def test_unpack_of_a_large_buffer(dtype, hkv, d, shift):
                                     dev(np.arange(4, dtype=np.int32)), dev(lens), lens, 4, kp, vp, num_pages,
                                     dev(pt), pt.shape[1])
     assert torch.equal(kp, ek) and torch.equal(vp, ev)
+
+
+@pytest.mark.parametrize("dtype,hkv,d,shift", [("bf16", 8, 128, 0), ("bf16", 8, 64, 3), ("fp32", 4, 128, 0),
+                                               ("fp32", 8, 64, 1), ("fp8", 16, 128, 0), ("fp8", 16, 64, 5)])
+def test_pack_of_a_large_buffer(dtype, hkv, d, shift):
+    """Buffers above 128 MiB are packed with other loads; compared on the GPU."""
+    import torch
+
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    t = {"bf16": torch.int16, "fp32": torch.int32, "fp8": torch.uint8}[dtype]
+    layers = 9 * 128 // d
+    lens = np.array([1, 2049, 0, 2100], np.int32)
+    offs = I.handoff_offsets(lens, layers, hkv, d) + shift
+    assert (offs[-1] - shift) * t.itemsize > 128 << 20
+    pt, num_pages = I.allocate_pages(np.random.default_rng(10), np.maximum(lens, 1))
+    lo, hi = (0, 256) if dtype == "fp8" else (-2 ** 15, 2 ** 15)
+    rand = lambda *s: torch.randint(lo, hi, s, dtype=t, device="cuda", generator=gen)  # noqa: E731
+    buf = rand(int(offs[-1]))
+    kp, vp = rand(layers, num_pages, hkv, 16, d), rand(layers, num_pages, hkv, d, 16)
+    want = buf.clone()
+    for r, n in enumerate(lens):
+        x = want[offs[r]:offs[r] + layers * 2 * hkv * int(n) * d].view(layers, 2, hkv, int(n), d)
+        for i in range((int(n) + 15) // 16):
+            rows = x[:, :, :, 16 * i:16 * (i + 1)]
+            rows[:, 0] = kp[:, pt[r, i], :, :rows.shape[3]]
+            rows[:, 1] = vp[:, pt[r, i], :, :, :rows.shape[3]].transpose(-1, -2)
+    dev = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    G.A.dopd_kv_pack_for_handoff(G.A.make_shape(hkv, hkv, d, dtype), layers, kp, vp, num_pages, dev(pt), pt.shape[1],
+                                 dev(np.arange(4, dtype=np.int32)), dev(lens), lens, dev(offs[:-1].copy()), 4, buf)
+    assert torch.equal(buf, want)
