@@ -6,16 +6,16 @@
 // written range are never touched.
 //
 // Two mappings.  The page writer gives a wave K or V of one page of 16 / CW KV
-// heads (CW chunks of a row per pass: one head, or two bf16 heads at d = 64) and
-// issues all of its 16-byte loads at once; a lane holds 4 tokens of 8 (bf16) or 4
-// (fp32) dims of V, so the transposition to dim rows is done in registers four
-// tokens at a time and only gathers rows in LDS, privately per wave (no workgroup
-// barrier).  Slots of a page that is written in part leave in the widest aligned
-// stores that fit.  The append writer gives a wave 64 16-byte
-// chunks of one token's K or V: with one or two tokens per request every page is
-// partial and V is written element by element either way, and what counts is the
-// chain of loads that finds the request and its page, and the cache lines that
-// the elements of V touch.
+// heads (CW chunks of a row per pass: one head, or two bf16 heads at d = 64; of the
+// E4M3 codes of an unpack two, at d = 64 four) and issues all of its 16-byte loads at
+// once; a lane holds 4 tokens of 8 (bf16) or 4 (fp32) dims of V, so the transposition
+// to dim rows is done in registers four tokens at a time and only gathers rows in LDS,
+// privately per wave (no workgroup barrier).  Slots of a page that is written in part
+// leave in the widest aligned stores that fit.  The append writer gives a wave 64
+// 16-byte chunks of one token's K or V: with one or two tokens per request every page
+// is partial and V is written element by element either way, and what counts is the
+// chain of loads that finds the request and its page, and the cache lines that the
+// elements of V touch.
 //
 // HBM-bound at size: E4M3 writes of 16 prompts (318 MB, 8 heads, d 128) 74 ->
 // 62 us (5.1 TB/s), bf16 writes of 16 prompts at 32 heads 262 -> 231 us
