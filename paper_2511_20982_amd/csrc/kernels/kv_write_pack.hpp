@@ -30,18 +30,24 @@ struct WritePackArgs {
 };
 
 // Workgroup b: heads of group b % head_groups of logical page b / head_groups of
-// the concatenated page lists, K and V in waves of their own (even, odd), or BOTH
-// one after the other in a wave.  The fused step takes the latter: its writer
-// workgroups hold slots the prefill waits for, and twice as many of them cost more
-// than their shorter life gives (mixed step 220.5 against 216.9 us, E4M3 142.7
-// against 138.5).  s: this wave's PageWrite<...>::kLdsBytes of LDS (K waves: any).
+// the concatenated page lists, K and V in waves of their own (a page's waves of K
+// come first), or BOTH one after the other in a wave.  The fused step takes the
+// latter: its writer workgroups hold slots the prefill waits for, and twice as many
+// of them cost more than their shorter life gives (mixed step 220.5 against 216.9
+// us, E4M3 142.7 against 138.5).  K and V of the same heads side by side would store
+// to handoff rows and pages that are a power of two apart when a prompt's length is:
+// 8 prompts of 512, d 64, 8 / 16 heads 6.3 / 9.8 us against 4.8 / 7.8 (BOTH 5.1 /
+// 7.4, but one prompt of 20 tokens 4.4 against 3.4).  s: this wave's
+// PageWrite<...>::kLdsBytes of LDS.
 template <typename TO, int D, bool BOTH>
 __device__ __forceinline__ void kv_write_pack_workgroup(const WritePackArgs& a, int b, uint8_t* s) {
   using W = PageWrite<uint16_t, TO, D>;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int wi = b % a.head_groups * kKvwWaves + w;  // wave of the page: K's, V's, .. (or both)
-  const int h0 = (BOTH ? wi : wi >> 1) * W::HW;
-  if (h0 >= a.hkv) return;
+  const int nk = (a.hkv + W::HW - 1) / W::HW;        // waves of a page's K
+  const int wi = b % a.head_groups * kKvwWaves + w;  // wave of the page: K's, then V's (or both)
+  if (wi >= (BOTH ? nk : 2 * nk)) return;
+  const bool is_v = wi >= nk;
+  const int h0 = (is_v ? wi - nk : wi) * W::HW;
   int cu_l = 0, n_l = 0;  // this lane's request
   auto pages = [&](int rr) {
     cu_l = a.cu[rr];
@@ -66,11 +72,11 @@ __device__ __forceinline__ void kv_write_pack_workgroup(const WritePackArgs& a, 
     aligned = (reinterpret_cast<uintptr_t>(pk) & (sizeof(typename W::Out) - 1)) == 0;
   }
   const int64_t page_elems = (int64_t)a.hkv * (kPage * D);
-  if (BOTH || !(wi & 1))
+  if (BOTH || !is_v)
     write_page_rows<uint16_t, TO, D, true, false>(a.k_new + src, row_elems, D, h0, a.hkv, 0, s1,
                                                   static_cast<TO*>(a.k_pool) + page * page_elems, a.k_scale, pk,
                                                   (int64_t)n * D, aligned, s);
-  if (BOTH || (wi & 1))
+  if (BOTH || is_v)
     write_page_rows<uint16_t, TO, D, true, true>(a.v_new + src, row_elems, D, h0, a.hkv, 0, s1,
                                                  static_cast<TO*>(a.v_pool) + page * page_elems, a.v_scale, pv,
                                                  (int64_t)n * D, aligned, s);
@@ -78,8 +84,8 @@ __device__ __forceinline__ void kv_write_pack_workgroup(const WritePackArgs& a, 
 
 template <int D>
 __global__ __launch_bounds__(64 * kKvwWaves) void kv_write_pack_kernel(WritePackArgs a) {
-  __shared__ __attribute__((aligned(16))) uint8_t s[kKvwWaves / 2][PageWrite<uint16_t, uint16_t, D>::kLdsBytes];
-  kv_write_pack_workgroup<uint16_t, D, false>(a, (int)blockIdx.x, s[threadIdx.x >> 7]);
+  __shared__ __attribute__((aligned(16))) uint8_t s[kKvwWaves][PageWrite<uint16_t, uint16_t, D>::kLdsBytes];
+  kv_write_pack_workgroup<uint16_t, D, false>(a, (int)blockIdx.x, s[threadIdx.x >> 6]);
 }
 
 }  // namespace dopd

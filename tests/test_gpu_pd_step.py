@@ -67,6 +67,28 @@ def test_write_pack_matches_write_then_pack(d, shift):
     assert np.array_equal(A.to_host(kpd2), rk) and np.array_equal(A.to_host(vpd2), rv)
 
 
+@pytest.mark.parametrize("hkv,d", [(1, 64), (3, 64), (5, 64), (17, 64), (1, 128), (3, 128), (5, 128)])
+def test_write_pack_head_counts(hkv, d):
+    """Heads that fill the waves and workgroups of a page in part."""
+    rng = np.random.default_rng(510 + hkv + d)
+    lens = np.array([1, 33, 0, 16], np.int32)
+    _, k, v = I.prefill_batch(rng, lens, hkv, hkv, d, "bf16")
+    pt, num_pages = I.allocate_pages(rng, np.maximum(lens, 1))
+    kp, vp = I.empty_pools(num_pages, hkv, d, "bf16")
+    cu = I.cu_from_lens(lens)
+    offs = I.handoff_offsets(lens, 1, hkv, d)
+    rk, rv, ref_h = _handoff_ref(k, v, kp, vp, pt, cu, lens, offs, hkv, d)
+    kpd, vpd = A.to_device(kp), A.to_device(vp)
+    out, obuf, margin = G.guarded((int(offs[-1]),), torch.bfloat16)
+    A.dopd_kv_write_pack_for_handoff(A.make_shape(hkv, hkv, d), A.to_device(k), A.to_device(v), kpd, vpd, num_pages,
+                                     A.to_device(pt), pt.shape[1], A.to_device(cu), cu, len(lens),
+                                     A.to_device(offs), out)
+    torch.cuda.synchronize()
+    assert G.canary_intact(obuf, margin, int(offs[-1]) * 2)
+    assert np.array_equal(A.to_host(kpd), rk) and np.array_equal(A.to_host(vpd), rv)
+    assert np.array_equal(A.to_host(out), ref_h)
+
+
 def _run_pd_step(w, sh, schedule, with_lse=True, handoff=True):
     n_pre, n_dec = len(w.prefill_lens), len(w.context_lens)
     stride = w.page_table.shape[1]
