@@ -59,13 +59,13 @@ KERNEL_SOURCES = ("paper_2511_20982_amd/csrc/dopd_attn.hip",
 # kernels one of which a launch of the call takes by its sizes (else its first).
 CALL_KERNELS = {"decode": ("decode_split_kernel", "decode_direct_kernel", "decode_merge_list_kernel",
                            "decode_merge_kernel"),
-                "prefill": ("prefill_bf16_kernel<128, false, false>",
-                            "prefill_bf16_kernel<64, false, false>"),
-                "prefill_chunked": ("prefill_bf16_kernel<128, true, false>",
-                                    "prefill_bf16_kernel<64, true, false>",
+                "prefill": ("prefill_bf16_kernel<128, false, false",
+                            "prefill_bf16_kernel<64, false, false"),
+                "prefill_chunked": ("prefill_bf16_kernel<128, true, false",
+                                    "prefill_bf16_kernel<64, true, false",
                                     "prefill_split_merge_kernel"),
-                "prefill_chunked_fp8": ("prefill_bf16_kernel<128, true, true>",
-                                        "prefill_bf16_kernel<64, true, true>",
+                "prefill_chunked_fp8": ("prefill_bf16_kernel<128, true, true",
+                                        "prefill_bf16_kernel<64, true, true",
                                         "prefill_split_merge_kernel"),
                 "kv_write": ("kv_write_kernel<unsigned short, unsigned short",
                              "kv_append_kernel<unsigned short, unsigned short"),

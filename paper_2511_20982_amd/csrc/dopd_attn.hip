@@ -332,13 +332,13 @@ extern "C++" {
 namespace {
 
 // Fills the work-order fields of `a` for chunk lengths cu_host (and, on the
-// paged path, cached prefixes prefix_host) and returns the prefill's block
-// count: items are (q tile, request, head), with at most kPfMaxOrdered
+// paged path, cached prefixes prefix_host) and returns the prefill's counts of
+// blocks and of items times key splits: items are (q tile, request, head), with at most kPfMaxOrdered
 // requests in the XCD-aware order, else heaviest q tile first.
 template <bool PAGED>
 dopd_status plan_prefill_bf16(dopd::PrefillArgs& a, int d, const int32_t* cu_host,
                               const int32_t* prefix_host, int32_t nreq, int elem_bytes,
-                              bool split_requests, int64_t* blocks_out) {
+                              bool split_requests, int64_t* blocks_out, int64_t* items_out) {
   int max_len = 0;
   int64_t tiles = 0;
   for (int32_t r = 0; r < nreq; ++r) {
@@ -364,6 +364,7 @@ dopd_status plan_prefill_bf16(dopd::PrefillArgs& a, int d, const int32_t* cu_hos
   blocks *= a.nsplit;  // (nsplit > 1 only on the paged path)
   if (blocks > INT32_MAX / 2) return DOPD_ERR_INVALID_SHAPE;
   *blocks_out = blocks;
+  *items_out = items * a.nsplit;
   return DOPD_OK;
 }
 
@@ -374,17 +375,20 @@ dopd_status plan_prefill_bf16(dopd::PrefillArgs& a, int d, const int32_t* cu_hos
 template <bool PAGED, bool KV8 = false>
 dopd_status launch_prefill_bf16(dopd::PrefillArgs a, int d, const int32_t* cu_host,
                                 const int32_t* prefix_host, int32_t nreq, hipStream_t strm) {
-  int64_t blocks = 0;
+  int64_t blocks = 0, items = 0;
   const dopd_status pst =
-      plan_prefill_bf16<PAGED>(a, d, cu_host, prefix_host, nreq, KV8 ? 1 : 2, true, &blocks);
+      plan_prefill_bf16<PAGED>(a, d, cu_host, prefix_host, nreq, KV8 ? 1 : 2, true, &blocks, &items);
   if (pst != DOPD_OK) return pst;
   if (blocks == 0) return DOPD_OK;
+  const dim3 grid((unsigned)blocks), block(dopd::kPfThreads);
+  const bool one_round = items <= (int64_t)dopd::kWgPerCu * machine_shape().cus;  // (the line of pf_raise)
   if (d == 64)
-    hipLaunchKernelGGL((dopd::prefill_bf16_kernel<64, PAGED, KV8>), dim3((unsigned)blocks),
-                       dim3(dopd::kPfThreads), 0, strm, a);
+    hipLaunchKernelGGL((dopd::prefill_bf16_kernel<64, PAGED, KV8>), grid, block, 0, strm, a);
+  else if (one_round)
+    hipLaunchKernelGGL((dopd::prefill_bf16_kernel<128, PAGED, KV8>), grid, block, 0, strm, a);
   else
-    hipLaunchKernelGGL((dopd::prefill_bf16_kernel<128, PAGED, KV8>), dim3((unsigned)blocks),
-                       dim3(dopd::kPfThreads), 0, strm, a);
+    hipLaunchKernelGGL((dopd::prefill_bf16_kernel<128, PAGED, KV8, dopd::pf_raise(128, PAGED, KV8, false)>), grid,
+                       block, 0, strm, a);
   const dopd_status st = launch_status();
   if (st != DOPD_OK || a.nsplit == 1) return st;
   const int64_t threads = (int64_t)a.part_rows * a.hq * (d / 4);
@@ -938,7 +942,7 @@ static dopd_status pd_step_impl(const dopd_attn_shape* s, const void* q_dec,
     if (st != DOPD_OK) return st;
     p.n_dec = p.dec.nwg;
   }
-  int64_t pf_blocks = 0;
+  int64_t pf_blocks = 0, pf_items = 0;
   const int groups = kv8 ? write_head_groups<uint16_t, uint8_t>(hkv, d, true)
                          : write_head_groups<uint16_t, uint16_t>(hkv, d, true);
   if (num_pre > 0 && cu_host[num_pre] > 0) {
@@ -947,7 +951,7 @@ static dopd_status pd_step_impl(const dopd_attn_shape* s, const void* q_dec,
     p.pf = prefill_args(&sb, q, out_pre, lse_pre, cu);
     p.pf.k = (const uint16_t*)k;
     p.pf.v = (const uint16_t*)v;
-    st = plan_prefill_bf16<false>(p.pf, d, cu_host, nullptr, num_pre, 2, false, &pf_blocks);
+    st = plan_prefill_bf16<false>(p.pf, d, cu_host, nullptr, num_pre, 2, false, &pf_blocks, &pf_items);
     if (st != DOPD_OK) return st;
     p.wp = write_pack_args(k, v, k_pool, v_pool, pre_page_table, pt_stride, cu, num_pre, hkv,
                            groups, handoff_offsets, handoff_out);

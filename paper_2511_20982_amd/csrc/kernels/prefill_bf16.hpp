@@ -181,7 +181,23 @@ constexpr int pf_q_lds_elems() { return (D / 32) * kPfThreads * 8; }
 // not wait for them.
 // PAGED = false: fresh prompts, K/V token-major beside Q (dopd_prefill_attn).
 // PAGED = true: chunks attending to the paged cache (dopd_prefill_paged_attn).
-template <int D, bool PAGED, bool KV8 = false>
+// RAISE: the wave's priority is raised over the softmax and the next tile's QK
+// products, so its VALU work issues first and the other workgroup's P.V MFMAs fill
+// the slots it leaves.  Measured, raised / not:
+//   dense: 1-2 % faster raised
+//   bf16 pages of d 128: 16 chunks of 512 312 / 314 us, a batch of long chunks 498 / 555
+//   E4M3 pages of d 128, calls that fit the workgroup slots at once: 4 chunks of 317
+//     behind 1500, 32/8 heads, 57.5 / 62.3, 5 of 300 behind 7100 223 / 240; longer
+//     calls: 9 of 47 behind 3100, 64/8 heads, 165.5 / 150.5, 5 of 196 43.6 / 39.6, 19 of
+//     348 behind 5700 1305 / 1282
+//   pages of d 64, where a step has half the products: 21 chunks of 36 tokens, E4M3,
+//     32/8 heads, 27.7 / 24.6, 6 of 343 behind 4000, 16/16 heads, 110 / 102; bf16, 5 of
+//     140 behind 3000, 45.6 / 43.8
+constexpr bool pf_raise(int d, bool paged, bool kv8, bool one_round) {
+  return !paged || (d == 128 && (!kv8 || one_round));
+}
+
+template <int D, bool PAGED, bool KV8 = false, bool RAISE = pf_raise(D, PAGED, KV8, true)>
 __device__ __forceinline__ void prefill_workgroup(const PrefillArgs& a, int bid, uint16_t* sK0,
                                                   uint16_t* sK1, uint16_t* sV0, uint16_t* sV1,
                                                   uint16_t* sQ) {
@@ -664,20 +680,12 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs& a, int bid,
     };
     auto even = [] { return 0; };
     auto odd = [] { return 1; };
-    // The wave's priority is raised over the softmax and the next tile's QK
-    // products, so its VALU work issues first and the other workgroup's P.V
-    // MFMAs fill the slots it leaves (measured 1-2 % faster dense, 3-5 % over
-    // E4M3 and bf16 pages of d 128).  Over pages of d 64, where a step has half the
-    // products, it is 1-10 % slower (E4M3: 21 chunks of 36 tokens, 32/8 heads, 27.7
-    // against 24.6 us, 6 of 343 behind 4000, 16/16 heads, 110 against 102; bf16: 5 of
-    // 140 behind 3000 45.6 against 43.8).
-    constexpr bool kRaise = !PAGED || D == 128;
     auto step_full = [&](f32x16* sc, f32x16* sn, auto par) {
       prefetch(j, par);
       if (wave_active) {
-        if constexpr (kRaise) __builtin_amdgcn_s_setprio(1);
+        if constexpr (RAISE) __builtin_amdgcn_s_setprio(1);
         half_qk(sc, sn, par() ^ 1);
-        if constexpr (kRaise) __builtin_amdgcn_s_setprio(0);
+        if constexpr (RAISE) __builtin_amdgcn_s_setprio(0);
         pv(par());
       }
       if (j + 1 < je) clear_dead_v(par() ^ 1, j + 1);
@@ -770,12 +778,12 @@ __device__ __forceinline__ void prefill_workgroup(const PrefillArgs& a, int bid,
   }
 }
 
-template <int D, bool PAGED, bool KV8 = false>
+template <int D, bool PAGED, bool KV8 = false, bool RAISE = pf_raise(D, PAGED, KV8, true)>
 __global__ __launch_bounds__(kPfThreads, 2) void prefill_bf16_kernel(PrefillArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t sK0[pf_tile_elems<D>()], sK1[pf_tile_elems<D>()];
   __shared__ __attribute__((aligned(16))) uint16_t sV0[pf_tile_elems<D>()], sV1[pf_tile_elems<D>()];
   __shared__ __attribute__((aligned(16))) uint16_t sQ[pf_q_lds_elems<D>()];
-  prefill_workgroup<D, PAGED, KV8>(a, (int)blockIdx.x, sK0, sK1, sV0, sV1, sQ);
+  prefill_workgroup<D, PAGED, KV8, RAISE>(a, (int)blockIdx.x, sK0, sK1, sV0, sV1, sQ);
 }
 
 // Combines the key splits of the paged prefill.  Thread = one 4-dim chunk of

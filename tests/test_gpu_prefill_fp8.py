@@ -85,6 +85,27 @@ def test_prefill_paged_fp8_many_requests():
         assert np.max(np.abs(lse - ref_lse)) < 2e-2
 
 
+@pytest.mark.parametrize("d", [128, 64])
+def test_prefill_paged_fp8_rounds_of_items(d):
+    """Calls whose items fit the workgroup slots at once (8 requests of one q tile, 64
+    heads) and just do not (9): at d 128 different instantiations of the kernel."""
+    import torch
+
+    per = 2 * torch.cuda.get_device_properties(0).multi_processor_count // 64
+    rng = np.random.default_rng(94)
+    prefix = rng.integers(130, 400, per + 1).astype(np.int32)
+    chunk = rng.integers(20, 70, per + 1).astype(np.int32)
+    q, k8, v8, ks, vs, pt, cu, pre = fp8_case(94 + d, prefix, chunk, 64, 8, d)
+    ref, ref_lse = oracle.prefill_paged_e4m3(q, k8, v8, ks, vs, pt, cu, pre, 1 / np.sqrt(d))
+    sh = G.A.make_shape(64, 8, d, "fp8")
+    out, lse = G.gpu_prefill_paged_fp8(sh, q, k8, v8, ks, vs, pt, cu, pre, splits=1)
+    G.assert_attention_close(out, ref, "bf16", "fp8 chunk prefill, more than one round")
+    assert np.max(np.abs(lse - ref_lse)) < 2e-2
+    n = cu[per]  # the same rows without the last request: the same bits
+    out1, lse1 = G.gpu_prefill_paged_fp8(sh, q[:n], k8, v8, ks, vs, pt[:per], cu[:per + 1], pre[:per], splits=1)
+    assert np.array_equal(out1, out[:n]) and np.array_equal(lse1, lse[:n])
+
+
 def test_prefill_paged_fp8_chunk_of_one_matches_fp8_decode():
     q, k8, v8, ks, vs, pt, cu, pre = fp8_case(97, [30, 0, 17, 2047], [1, 1, 1, 1], 28, 4, 128)
     sh = G.A.make_shape(28, 4, 128, "fp8")
